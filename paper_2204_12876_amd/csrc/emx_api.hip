@@ -106,15 +106,17 @@ Consts make_consts(const emx_params& p) {
   return c;
 }
 
-// One buffer set: seven 4-byte layers, two byte layers, the clearing block
-// maxima, the upper bound layer if the map keeps one, then the fusion's four
-// planes of fixed-point sums (8 bytes per cell each); each 256-aligned.
+// One buffer set: seven 4-byte layers, two byte layers, the clearing maxima per
+// block and superblock, the upper bound layer if the map keeps one, then
+// the fusion's four planes of fixed-point sums (8 bytes per cell each); each
+// 256-aligned.
 size_t set_layout(const emx_params& p, char* base, Layers* L) {
   const size_t C = (size_t)p.nx * (size_t)p.ny;
   const size_t l4 = align256(C * 4);
   const size_t l1 = align256(C);
-  const int bl = block_log_of(p.nx, p.ny);
-  const size_t lb = align256((size_t)blocks_of(p.nx, bl) * blocks_of(p.ny, bl) * 4);
+  const size_t nb = (size_t)blocks_of(p.nx, kBlockLog) * blocks_of(p.ny, kBlockLog);
+  const size_t ns = (size_t)blocks_of(p.nx, kSuperLog) * blocks_of(p.ny, kSuperLog);
+  const size_t lb = align256(nb * 4) + align256(ns * 4);
   if (L && base) {
     L->h = (float*)(base + 0 * l4);
     L->v = (float*)(base + 1 * l4);
@@ -126,6 +128,7 @@ size_t set_layout(const emx_params& p, char* base, Layers* L) {
     L->valid = (uint8_t*)(base + 7 * l4);
     L->mark = (uint8_t*)(base + 7 * l4 + l1);
     L->cmax = (float*)(base + 7 * l4 + 2 * l1);
+    L->smax = (float*)(base + 7 * l4 + 2 * l1 + align256(nb * 4));
     L->ub = p.upper_bound ? (float*)(base + 7 * l4 + 2 * l1 + lb) : nullptr;
     L->fx = (uint64_t*)(base + 7 * l4 + 2 * l1 + lb + (p.upper_bound ? l4 : 0));
     L->fxs = (int64_t)(align256(C * 8) / 8);
@@ -137,7 +140,7 @@ size_t clr_bytes(const emx_params& p) { return align256((size_t)p.nx * (size_t)p
 
 int tiles_of(const emx_params& p) { return tiles_x_of(p.nx) * tiles_y_of(p.ny); }
 
-int64_t ctl_words(const emx_params& p) { return (int64_t)kCtlWords + tiles_of(p); }
+int64_t ctl_words(const emx_params& p) { return tiles_of(p); }
 
 // A persistent grid of per_cu workgroups per compute unit of the current device.
 int persistent_grid(int per_cu) {
@@ -175,13 +178,15 @@ emx_status make_item(const emx_map* m, const emx_frame* f, Item* it) {
   it->L = m->L;
   it->tiles_x = tiles_x_of(m->p.nx);
   it->T = tiles_of(m->p);
-  it->bl = block_log_of(m->p.nx, m->p.ny);
-  it->bx = blocks_of(m->p.nx, it->bl);
-  it->by = blocks_of(m->p.ny, it->bl);
-  it->nb = it->bx * it->by;
-  it->bpw = clear_blocks_per_wave(it->nb);
-  it->nprep = clear_block_units(it->nb);
-  it->fs.tcnt = m->ctl + kCtlWords;
+  it->bx = blocks_of(m->p.nx, kBlockLog);
+  it->by = blocks_of(m->p.ny, kBlockLog);
+  it->sbx = blocks_of(m->p.nx, kSuperLog);
+  it->sby = blocks_of(m->p.ny, kSuperLog);
+  // a sample travels at most ray_step along an axis; short steps stop at 32
+  // samples to a group, so that one thread's share of a long ray stays small
+  const double per = floor(7.0 * m->p.resolution / (double)m->p.ray_step);
+  it->grp = per < 1.0 ? 1 : (per > 32.0 ? 32 : (int)per);
+  it->fs.tcnt = m->ctl;
   if (!f) return EMX_OK;
   for (int k = 0; k < 12; ++k)
     if (!isfinite(f->pose[k])) return fail(EMX_EINVAL, "pose has a non-finite entry");
@@ -250,7 +255,7 @@ size_t emx_scratch_bytes(const emx_params* params, int64_t max_points) {
   const int64_t count_cells =
       params->wall_min_count > 0 ? (int64_t)params->nx * params->ny : 0;
   const size_t f = fuse_scratch_layout(count_cells, nullptr, nullptr);
-  const size_t c = clear_scratch_layout(max_points, kDefaultSeg, nullptr, nullptr);
+  const size_t c = clear_scratch_bytes(max_points, kDefaultSeg);
   return f > c ? f : c;
 }
 
@@ -282,9 +287,7 @@ emx_status emx_init_map(const emx_params* params, double cx, double cy, int64_t 
   m->state = (char*)d_state;
   const size_t set_bytes = set_layout(*params, m->state, &m->L);
   m->L.clr = (float2*)(m->state + set_bytes);
-  m->ctr_sel = 0;
   m->ctl = (uint32_t*)(m->state + set_bytes + clr_bytes(*params));
-  m->march_grid = persistent_grid(kMarchPerCU);
   hipError_t e =
       launch_fill_prior(m->c, m->L, m->ctl, (int)ctl_words(*params), (hipStream_t)stream);
   if (e != hipSuccess) {
@@ -454,24 +457,16 @@ emx_status emx_clear_visibility(emx_map* m, const emx_frame* f, void* d_scratch,
   Item it;
   if ((s = make_item(m, f, &it)) != EMX_OK) return s;
   if (f->n > 0) {
-    const size_t need = clear_scratch_layout(f->n, kDefaultSeg, nullptr, nullptr);
+    const size_t need = clear_scratch_bytes(f->n, kDefaultSeg);
     if (!d_scratch) return fail(EMX_EINVAL, "d_scratch is NULL");
     if (((uintptr_t)d_scratch & 255u) != 0)
       return fail(EMX_EINVAL, "d_scratch must be 256-byte aligned");
     if (scratch_bytes < need)
       return fail(EMX_ENOMEM, "scratch has %zu bytes, needs %zu", scratch_bytes, need);
-    clear_scratch_layout(f->n, kDefaultSeg, (char*)d_scratch, &it.cq);
   }
-  it.cq.counter = m->ctl + m->ctr_sel * kCtrWords;
-  it.cq.counter_next = m->ctl + (1 - m->ctr_sel) * kCtrWords;
-  it.cq.seg = kDefaultSeg;
   it.out_cleared = d_out_cleared;
   it.stages = kStageClear;
-  bool ran = false;
-  hipError_t e = launch_clear(it, m->march_grid, (hipStream_t)stream, &ran);
-  // once the setup ran, this call's counter set is spent and the other one
-  // is being zeroed: switch, whatever happened after
-  if (ran) m->ctr_sel = 1 - m->ctr_sel;
+  hipError_t e = launch_clear(it, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "clear_visibility");
   return EMX_OK;
 }

@@ -127,14 +127,12 @@ int64_t frame_points(const emx_batch_item& b) {
   return (b.stages & (EMX_STAGE_FUSE | EMX_STAGE_CLEAR)) ? b.frame.n : 0;
 }
 
-// Scratch layout: the device table, the clearing queue counters (zeroed by the
-// batch's first launch), each item's fusion scratch, then one clearing queue
-// shared by the batch.
-constexpr size_t kCounterOffset = (sizeof(Batch) + 255) & ~(size_t)255;
-constexpr size_t kCounterBytes = kCtrWords * sizeof(uint32_t);
+// Scratch layout: the device table, each item's fusion scratch, then what the
+// size contract keeps for clearing.
+constexpr size_t kTableBytes = (sizeof(Batch) + 255) & ~(size_t)255;
 
 size_t batch_layout(const emx_batch_item* items, int32_t n, int seg, char* base, Batch* tab) {
-  size_t off = align256(kCounterOffset + kCounterBytes);
+  size_t off = kTableBytes;
   int64_t rays = 0;
   for (int32_t i = 0; i < n; ++i) {
     const int64_t np = frame_points(items[i]);
@@ -145,22 +143,9 @@ size_t batch_layout(const emx_batch_item* items, int32_t n, int seg, char* base,
       if (tab && base) fuse_scratch_layout(cc, base + off, &tab->items[i].fs);
       off = align256(off + f);
     }
-    if (tab) {
-      tab->items[i].ray_base = rays;
-      tab->rays[i] = rays;
-    }
     if (items[i].stages & EMX_STAGE_CLEAR) rays += np;
   }
-  if (tab) tab->rays[n] = rays;
-  ClearQueue cq = {};
-  const size_t c = clear_scratch_layout(rays, seg, base ? base + off : nullptr, &cq);
-  if (tab && base)
-    for (int32_t i = 0; i < n; ++i) {
-      tab->items[i].cq = cq;
-      tab->items[i].cq.counter = (uint32_t*)(base + kCounterOffset);
-      tab->items[i].cq.counter_next = nullptr;  // zeroed by the batch's first launch
-    }
-  return off + c;
+  return off + clear_scratch_bytes(rays, seg);
 }
 
 }  // namespace
@@ -271,8 +256,7 @@ size_t emx_batch_scratch_bound(const emx_batch* b, const emx_params* largest, in
   const int64_t cc =
       largest->wall_min_count > 0 ? (int64_t)max_items * largest->nx * largest->ny : 0;
   const size_t fuse = fuse_scratch_layout(cc, nullptr, nullptr) + (size_t)max_items * 256;
-  return align256(kCounterOffset + kCounterBytes) + fuse +
-         clear_scratch_layout(max_points, b->tune.seg, nullptr, nullptr);
+  return kTableBytes + fuse + clear_scratch_bytes(max_points, b->tune.seg);
 }
 
 emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t n,
@@ -343,11 +327,8 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
     cgy[i] = tmp.cgy;
   }
   batch_layout(items, n, b->tune.seg, (char*)d_scratch, tab);
-  int64_t clear_rays = 0;
   for (int32_t i = 0; i < n; ++i) {
     Item& it = tab->items[i];
-    it.cq.seg = b->tune.seg;
-    if (it.stages & EMX_STAGE_CLEAR) clear_rays += it.n;
     const uint32_t st = it.stages;
     const bool moved = (st & EMX_STAGE_MOVE) && (it.sx != 0 || it.sy != 0);
     const bool fuse = (st & EMX_STAGE_FUSE) && it.n > 0;
@@ -365,15 +346,14 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
     tab->off[kBTile][i + 1] = tab->off[kBTile][i] + (fuse ? it.T : 0);
     tab->off[kBVar][i + 1] = tab->off[kBVar][i] + (var ? var_units(cells) : 0);
     tab->off[kBSetup][i + 1] =
-        tab->off[kBSetup][i] +
-        (clear ? clear_setup_units(it.n, it.nprep, it.out_cleared != nullptr) : 0);
+        tab->off[kBSetup][i] + (clear && (it.n > 0 || it.out_cleared) ? setup_units(it) : 0);
+    tab->off[kBRays][i + 1] = tab->off[kBRays][i] + (clear ? ray_units(it.n) : 0);
     tab->off[kBCells][i + 1] =
         tab->off[kBCells][i] +
         ((st & (EMX_STAGE_NORMALS | EMX_STAGE_TRAV)) ? cells_units(it.c.nx, it.c.ny) : 0);
   }
 
-  // ---- grids: the tuned size, capped at the stage's work (power of two);
-  // the march gets about two threads per ray
+  // ---- grids: the tuned size, capped at the stage's work (power of two)
   const Tuning& t = b->tune;
   auto cap = [](int tuned, int64_t units) {
     return (int)(units < 1 ? 1 : (pow2_at_least(units) < tuned ? pow2_at_least(units) : tuned));
@@ -389,7 +369,7 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   key.grid[4] = cap(t.grid_tile, tab->off[kBTile][n]);
   key.grid[5] = cap_opt(t.grid_cells, tab->off[kBVar][n]);
   key.grid[6] = cap(t.grid_setup, tab->off[kBSetup][n]);
-  key.grid[7] = cap(t.grid_march, (2 * clear_rays + 255) / 256);
+  key.grid[7] = cap(t.grid_march, tab->off[kBRays][n]);
   key.grid[8] = cap(t.grid_cells, tab->off[kBCells][n]);
 
   // ---- enqueue: the table upload, then a cached graph or the same launches

@@ -285,27 +285,25 @@ __global__ __launch_bounds__(kNTf) void k_normals_trav(Item it) {
   cells_body(it, xcd_unit(blockIdx.x, gridDim.x), true, true);
 }
 
-// The batch's first launch: also zeroes the clearing queue counters, which
-// the later setup launch increments.
 __global__ __launch_bounds__(kNTf) void k_move_b(const Batch* bt) {
-  if (blockIdx.x == 0 && threadIdx.x <= kSubQ)  // the sub-queues' and the overflow counter
-    bt->items[0].cq.counter[threadIdx.x * kCtrStride] = 0u;
-  const int64_t total = bt->off[kBMove][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBMove, w);
-    move_body(bt->items[i], w - bt->off[kBMove][i]);
+  const UnitFinder units(bt, kBMove);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    move_body(bt->items[i], unit);
   }
 }
 
 // Each XCD takes a contiguous range of the batch's tiles (xcd_unit_k).
 __global__ __launch_bounds__(kNTf) void k_cells_b(const Batch* bt) {
-  const int64_t total = bt->off[kBCells][bt->n];
+  const UnitFinder units(bt, kBCells);
   for (int64_t k = 0;; ++k) {
-    const int64_t w = xcd_unit_k(blockIdx.x, gridDim.x, total, k);
+    const int64_t w = xcd_unit_k(blockIdx.x, gridDim.x, units.total(), k);
     if (w < 0) break;
-    const int i = batch_item(bt, kBCells, w);
+    int64_t unit;
+    const int i = units.find(w, unit);
     const Item& it = bt->items[i];
-    cells_body(it, w - bt->off[kBCells][i], (it.stages & kStageNormals) != 0,
+    cells_body(it, unit, (it.stages & kStageNormals) != 0,
                (it.stages & kStageTrav) != 0);
     __syncthreads();
   }

@@ -1,58 +1,57 @@
 // Visibility clean-up by ray casting (Sec. II-E, Eq. 3 and Eq. 4).
 //
-// The samples of a ray are q_k = o + (k/K) d for k = 1..K-1, in float32.
-// Their number varies from 0 to a few hundred per ray, so one thread per ray
-// leaves the long rays on the critical path.  The work is therefore split in
-// two launches:
+// The samples of a ray are q_k = o + (k/K) d for k = 1..K-1, in float32.  Most
+// of them pass above every cell that a ray could still remove: on 400 x 400
+// maps in use a ray has 22 samples in the map, of which 0.1 to 2 lie below the
+// largest removable height of their 8 x 8 block.  The work is therefore to find
+// those samples without evaluating the others.
 //
-// setup, two roles in one grid:
-//   - Block role: per block of 2^b x 2^b cells, the largest height of a cell
-//     that a ray could still remove: valid, older than the minimum age, with a
-//     normal.  It is -inf if there is none.  In blocks with such a cell the
-//     same pass writes each cell's 8-byte clearing record {h, or -inf if no
-//     ray may remove it, v}, so that the march's height test takes one load.
-//     Other blocks prune every sample, so their records are never read.
-//     The cells' loads come in two rounds, each issued at once: validity,
-//     then the update time, normal z and height of valid cells (or the upper
-//     bound of invalid ones).
-//   - Ray role, one thread per point:
-//       - the ray's exact in-map range of k.  A sample's cell is in the map over
-//         a contiguous range of k, because q_k.x and q_k.y are monotone in k:
-//         each is a correctly rounded chain of monotone operations.  The range
-//         is found by binary search with the very sample evaluation the march
-//         uses.
-//       - the range is cut into segments of `seg` samples.  Each workgroup
-//         reserves its segments with one integer atomic, in one of kSubQ
-//         sub-queues, so no counter is contended.  An entry names the ray by
-//         its point (8 bytes: the ray, the first sample and the count); the
-//         march rebuilds the ray from the point, so no per-ray record is
-//         written.  A ray that would overflow its bounded sub-queue goes whole
-//         to an overflow list (one entry per ray at most, so the list cannot
-//         overflow).
-//   - Block 0 zeroes the counter set of the next plain call, and the block
-//     role zeroes the caller's removed-cell mask.
-// march: a persistent grid drains the queue, one segment per thread.
-//   - A segment's consecutive samples mostly stay in one block: the block
-//     maximum is loaded again only when the block changes.
-//   - A sample at height q.z >= the block maximum passes above every cell that
-//     could be removed, since removal needs h > q.z.  It is skipped without
-//     reading the cell: exact pruning.
-//   - Other samples read their cell's clearing record (and the normal only
-//     if the height test passes).
+// setup: one workgroup per 32 x 32 cells, one wave per row of four 8 x 8
+// blocks, a lane's four cells two rows apart in one column (128-byte rows of
+// loads, and the block maxima in four shuffles for four blocks).
+//   - Per 8 x 8 block (cmax) and per 32 x 32 superblock (smax): the largest
+//     height of a cell that a ray could still remove: valid, older than the
+//     minimum age, with a normal.  It is -inf if there is none.
+//   - Each cell's 8-byte clearing record {h, or -inf if no ray may remove it,
+//     v}, so that the march's height test takes one load.
+//   - Loads come in two rounds: validity, then the update time, normal z,
+//     height and variance of valid cells (or the upper bound of invalid ones).
+//   - The caller's removed-cell mask is zeroed here.
+// march: one workgroup per 128 rays (256 in a batch).
+//   - The ray is cut into groups of Item::grp consecutive samples, at most 7
+//     cells of travel, and spans of four groups.  Lower bounds of a group's
+//     cells and height come from the ray's line, widened by more than the
+//     samples' float32 evaluation can differ from it.  If the height is not
+//     below the maxima of the 2 x 2 blocks from the lowest cell on, no sample of
+//     the group can act: the group is skipped.  Long rays' spans are tested
+//     first, the same way, against the superblocks.  This is exact pruning: it
+//     never skips a sample that could act, and costs no sample evaluation.
+//   - Three phases hand lists in LDS to each other, so that every phase has an
+//     equal share for each thread whatever the rays' lengths: spans (one ray
+//     per thread), groups (one surviving span per thread), samples (half a
+//     surviving group per thread).  One thread per ray through all phases was
+//     1.5 times slower on 400 x 400 maps: the longest ray's chain of lookups, a
+//     microsecond each, set the time.
+//   - Every sample of a surviving half group is evaluated exactly and compared
+//     with its cell's record; the few below it read the cell's normal.
 //   - A sample that removes its cell resets the cell to the prior on the spot
 //     (and flags it in the caller's mask).  The march reads only the setup's
 //     records and the normals, never the heights, variances or validity it
 //     resets, so every ray still sees the state as it was when the call
-//     started.  Resets are idempotent stores of the same values, so the queue
+//     started.  Resets are idempotent stores of the same values, so their
 //     order never shows in the result.
-//   - The overflow list's rays are marched after the queue, whole.
+// Measured on MI355X, setup + march, against a queue of 16-sample segments whose
+// every sample was evaluated: 4M LiDAR rays on 2000 x 2000 cells 1197 -> 288 us,
+// 300k rays on 400 x 400 cells 25.4 -> 22.9 us, 16 maps with 4.6M rays in a batch
+// 302 -> 180 us.  The march is bound by VALU issue on the large frames (0.83 of
+// the SIMDs' issue slots) and by its chain of lookups on the small ones.
 // There is no separate pass to apply the removals.
 //
 // Upper bound layer (Sec. II-H), on maps that keep one: a sample in a cell
 // without an estimate lowers the cell's bound to the sample height, by an
 // integer atomic minimum (order-free, so deterministic).  Such cells count in
-// the block maximum with their current bound, so pruning stays exact: a
-// sample at or above it can neither remove a cell nor lower a bound.
+// the maxima with their current bound, so pruning stays exact: a sample at or
+// above it can neither remove a cell nor lower a bound.
 #include "emx_kernels.h"
 
 namespace emx {
@@ -60,11 +59,23 @@ namespace emx {
 namespace {
 
 constexpr int kNTc = 256;
+// Rays of a march workgroup.  A single frame's few workgroups are balanced
+// better by 128 (400 x 400: 17.0 against 19.4 us; 128 x 128: 6.3 against 10.0);
+// a batch has enough of them, and 256 halve the work's fixed part (16 maps:
+// 137 against 167 us).  4M rays alone: the same.
+constexpr int kRaysPlain = 128;
+constexpr int kRaysBatch = 256;
+constexpr int kSpanGroups = 4;  // groups in a span
+constexpr int kSpans = 8;       // spans of a ray looked up together
+constexpr int kParts = 2;       // parts of a group, looked up together
 
+// A ray: direction from the sensor origin (Pose32::t), 1/K correctly rounded
+// in double, the last sample that can lie in the map, and the end point's cell.
 struct Ray {
-  float ox, oy, oz;
   float dx, dy, dz;
-  double rK;  // 1/K, correctly rounded in double
+  int end_cell;  // or -1
+  double rK;
+  int k1;
 };
 
 // t = float32(k / K), correctly rounded, without a float32 division.
@@ -73,79 +84,7 @@ struct Ray {
 // ulp, and k/K equal to one would need K > k >= 2^24.  The double product
 // k * RN(1/K) carries at most 2^-52 relative error, so it rounds to the same
 // float32 as k/K.
-__device__ __forceinline__ float t_of(const Ray& r, int k) {
-  return (float)((double)k * r.rK);
-}
-
-// f(k) = q_k.x * inv_r (or .y), exactly as binning computes it
-template <bool kIsX>
-__device__ __forceinline__ float f_of(const Ray& r, int k, float inv_r) {
-  const float t = t_of(r, k);
-  return kIsX ? (r.ox + t * r.dx) * inv_r : (r.oy + t * r.dy) * inv_r;
-}
-
-// Smallest k in [lo, hi] with p(k), for p false then true over [lo, hi];
-// hi + 1 if p holds nowhere.  g is a guess of the answer: p is evaluated at g
-// and its neighbour, and a binary search over the rest of the range runs only
-// if the guess is off by more than one.  The answer never depends on g.
-template <class Pred>
-__device__ __forceinline__ int first_true(int lo, int hi, int g, Pred p) {
-  g = min(max(g, lo), hi);
-  int a, b;  // answer in [a, b]; b == hi + 1 stands for "nowhere"
-  if (p(g)) {
-    if (g == lo || !p(g - 1)) return g;
-    a = lo;
-    b = g - 1;
-  } else {
-    if (g == hi) return hi + 1;
-    if (p(g + 1)) return g + 1;
-    a = g + 2;
-    b = hi + 1;
-  }
-  while (a < b) {
-    const int m = (a + b) >> 1;
-    if (p(m)) b = m;
-    else a = m + 1;
-  }
-  return a;
-}
-
-// Guess of the first k at which o + (k/K) d crosses the line value w,
-// rounded up; any int if the crossing is undefined.
-__device__ __forceinline__ int crossing_guess(float o, float d, float w, int K) {
-  const double k = ((double)w - (double)o) * (double)K / (double)d;
-  return (k > -1.0 && k < 2.0e9) ? (int)ceil(k) : 1;
-}
-
-// Range [lo, hi] of k in [1, K-1] where 0 <= f(k) < lim, for f monotone in k
-// (non-decreasing if inc).  Empty range: lo > hi.
-template <bool kIsX>
-__device__ __forceinline__ void axis_range(const Ray& r, int K, float inv_r, float lim, bool inc,
-                                           int& lo, int& hi) {
-  auto in = [&](int k) {
-    const float v = f_of<kIsX>(r, k, inv_r);
-    return v >= 0.0f && v < lim;
-  };
-  lo = 1;
-  hi = K - 1;
-  if (in(lo) && in(hi)) return;
-  // "v >= 0" and "v < lim" are each monotone in k.  P(k) = (inc ? f >= 0 :
-  // f < lim) turns true once; Q(k) = (inc ? f < lim : f >= 0) turns false
-  // once.  The guesses come from the real line o + (k/K) d in metres.
-  const float o = kIsX ? r.ox : r.oy;
-  const float d = kIsX ? r.dx : r.dy;
-  const float wlim = lim / inv_r;
-  auto P = [&](int k) {
-    const float v = f_of<kIsX>(r, k, inv_r);
-    return inc ? (v >= 0.0f) : (v < lim);
-  };
-  auto notQ = [&](int k) {
-    const float v = f_of<kIsX>(r, k, inv_r);
-    return inc ? !(v < lim) : !(v >= 0.0f);
-  };
-  lo = first_true(1, K - 1, crossing_guess(o, d, inc ? 0.0f : wlim, K), P);
-  hi = first_true(1, K - 1, crossing_guess(o, d, inc ? wlim : 0.0f, K), notQ) - 1;
-}
+__device__ __forceinline__ float t_of(double rK, int k) { return (float)((double)k * rK); }
 
 // Lowers *a to v if v is smaller (v not NaN), as an integer atomic on the
 // float's bits: non-negative floats order like their bits as signed
@@ -171,352 +110,429 @@ __device__ __forceinline__ void clear_cell(const Item& it, int64_t pc, int lc) {
   if (it.out_cleared) it.out_cleared[lc] = 1;
 }
 
-// The removal test of sample q (height qz) in cell c, from the cell's
-// clearing record {h, v}, written by the setup: one 8-byte load for the height
-// test (which most samples fail), and the normal only when it passes.  A cell
-// no ray may clear holds -inf, which fails hd > 0 for every finite sample
-// height.  On maps with an upper bound layer, a cell without an estimate holds
-// NaN in place of the height (no other record does), which sends the sample
-// to its bound.
-__device__ __forceinline__ void test_cell_rec(const Item& it, const Ray& r, int lc, int64_t pc,
-                                              float qz, float an2dd, const float2 k) {
-  if (isnan(k.x)) {
-    atomic_min_f32(it.L.ub + pc, qz);
-    return;
-  }
-  const float hd = k.x - qz;
-  if (!(hd > 0.0f) || !((hd * hd) > k.y)) return;
-  const float dot = (r.dx * it.L.nx[pc] + r.dy * it.L.ny[pc]) + r.dz * it.L.nz[pc];
-  if ((dot * dot) > an2dd) clear_cell(it, pc, lc);
+// Narrows [lo, hi], in samples, to where o + (k/K) d lies in [0, W], widened
+// by more than the float32 evaluation of a sample and of this line can be off:
+// the samples outside are certainly outside the map, those inside are tested
+// one by one.  A coordinate that does not change (d = 0) keeps or empties the
+// whole range.
+__device__ __forceinline__ void clip(float o, float d, float W, float K, float& lo, float& hi) {
+  const float eps = (fabsf(o) + fabsf(d) + W) * 0x1p-18f;
+  const float s = K * __builtin_amdgcn_rcpf(d);
+  const float a = (-eps - o) * s;
+  const float b = ((W + eps) - o) * s;
+  lo = fmaxf(lo, fminf(a, b));
+  hi = fminf(hi, fmaxf(a, b));
 }
 
-// The ray of point i of the item: origin, direction, sample count K and the
-// end point's cell (or -1 outside).  False if the point casts no ray (not
-// valid, too long a ray, or K < 2: no samples).  The setup and the march both
-// build rays here, so a queued ray is rebuilt bit for bit from its point.
-__device__ __forceinline__ bool ray_of(const Item& it, int64_t i, Ray& r, int& K, int& end_cell) {
-  r.ox = it.P.t[0];
-  r.oy = it.P.t[1];
-  r.oz = it.P.t[2];
+// The ray of point i of the item and its first sample k0.  False if the point
+// casts no ray (not valid, too long a ray, or K < 2: no samples) or no sample
+// can lie in the map.
+__device__ __forceinline__ bool ray_of(const Item& it, int64_t i, Ray& r, int& k0) {
   const PointEval e = eval_point(it.P, it.c, it.x[i], it.y[i], it.z[i]);
-  r.dx = e.xm - r.ox;
-  r.dy = e.ym - r.oy;
-  r.dz = e.zm - r.oz;
+  r.dx = e.xm - it.P.t[0];
+  r.dy = e.ym - it.P.t[1];
+  r.dz = e.zm - it.P.t[2];
   const float m = fmaxf(fabsf(r.dx), fabsf(r.dy));
   const float ks = m * it.c.inv_step;
   if (!e.valid || !(ks < 16777216.0f)) return false;
-  K = (int)ceilf(ks);
-  if (K < 2) return false;
-  r.rK = 1.0 / (double)K;
+  const float Kf = ceilf(ks);
+  if (!(Kf >= 2.0f)) return false;
+  float lo = 1.0f, hi = Kf - 1.0f;
+  const float r32 = __builtin_amdgcn_rcpf(it.c.inv_r);
+  clip(it.P.t[0], r.dx, it.c.nxf * r32, Kf, lo, hi);
+  clip(it.P.t[1], r.dy, it.c.nyf * r32, Kf, lo, hi);
+  lo = fmaxf(lo - (fabsf(lo) * 0x1p-18f + 2.0f), 1.0f);
+  hi = fminf(hi + (fabsf(hi) * 0x1p-18f + 2.0f), Kf - 1.0f);
+  if (!(lo <= hi)) return false;
+  k0 = (int)lo;
+  r.k1 = (int)hi;
+  r.rK = 1.0 / (double)Kf;
   int ex, ey;
-  end_cell = bin_xy(e.xm, e.ym, it.c, ex, ey) ? ey * it.c.nx + ex : -1;
+  r.end_cell = bin_xy(e.xm, e.ym, it.c, ex, ey) ? ey * it.c.nx + ex : -1;
   return true;
 }
 
-constexpr int kUnroll = 8;
+// Lower bounds of the samples of a step: x and y, in blocks of 2^kLog cells,
+// bound the exact samples k .. k + step of the ray at line(k), z the height of
+// samples k .. k + part.  The samples' float32 evaluation and this one differ
+// by less than 2^-21 of the magnitudes entering them; the margins are 2^-19.
+struct Line {
+  float x, dx, y, dy, z, dz;
+  float zmin;  // no sample of the ray is lower; NaN if a step spans more than
+               // one block along an axis (it is not looked up: it may act)
+};
 
-// Test samples k in [ka, kb] of ray r against the map; cm holds the block
-// maxima.  kUnroll samples at a time: their cells and blocks are found without
-// branches, then the block maxima are loaded together, one load per change of
-// block along the ray (a ray spends about five samples in a block of 8 x 8
-// cells).  The per-sample work is kept to the sample itself.
-__device__ __forceinline__ void march_range(const Item& it, const Ray& r, int ka, int kb,
-                                            int end_cell, const float* cm) {
-  const float an2dd = it.c.an2 * ((r.dx * r.dx + r.dy * r.dy) + r.dz * r.dz);
-  const int bl = it.bl;
-  const int bx = it.bx;
-  const float inv_r = it.c.inv_r;
-  const int nx = it.c.nx;
-  uint32_t pblk = 0xFFFFFFFFu;  // the block of the previous sample, and its maximum
-  float pm = 0.0f;
+template <int kLog>
+__device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step, int part) {
+  const float scale = it.c.inv_r * (1.0f / (float)(1 << kLog));
+  const float rk = (float)r.rK;
+  const float s = (float)step;
+  const float ox = it.P.t[0] * scale, oy = it.P.t[1] * scale, oz = it.P.t[2];
+  const float tx = r.dx * scale, ty = r.dy * scale;
+  const float ex = (fabsf(ox) + fabsf(tx)) * 0x1p-19f;
+  const float ey = (fabsf(oy) + fabsf(ty)) * 0x1p-19f;
+  const float ez = (fabsf(oz) + fabsf(r.dz)) * 0x1p-19f;
+  Line l;
+  l.dx = tx * rk;
+  l.dy = ty * rk;
+  l.dz = r.dz * rk;
+  l.x = (ox - ex) + fminf(l.dx * s, 0.0f);
+  l.y = (oy - ey) + fminf(l.dy * s, 0.0f);
+  l.z = (oz - ez) + fminf(l.dz * (float)part, 0.0f);
+  const bool fits = fabsf(l.dx) * s + 2.0f * ex < 0.999f && fabsf(l.dy) * s + 2.0f * ey < 0.999f;
+  l.zmin = fits ? fminf(oz, fmaf(l.dz, (float)r.k1, oz)) - ez : __builtin_nanf("");
+  return l;
+}
+
+// Which of kN consecutive steps of `step` samples from sample k on may hold a
+// sample below the maximum of its block (`mx`, w x h blocks).  A step's samples
+// lie in the 2 x 2 blocks from its line's on, two 8-byte lookups; clamping
+// keeps every in-map cell among them.  Every lookup is requested before any is
+// used.  Each step answers for kParts parts of `part` samples (the last may
+// reach into the next step): bit j * kParts + p.  Maps of a single row or column
+// of blocks are not looked up.
+struct __attribute__((packed, aligned(4))) Pair {
+  float a, b;
+};
+
+template <int kN, int kParts>
+__device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int step, int part,
+                                            const float* mx, int w, int h) {
+  uint32_t live = 0;
+#pragma unroll
+  for (int j = 0; j < kN; ++j)
+#pragma unroll
+    for (int p = 0; p < kParts; ++p)
+      live |= (k + j * step + p * part <= k1) ? 1u << (j * kParts + p) : 0u;
+  if (w < 2 || h < 2) return live;
+  const float xm = (float)(w - 2), ym = (float)(h - 2);
+  Pair lo[kN], hi[kN];
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    const float kf = (float)(k + j * step);
+    const int x = (int)__builtin_amdgcn_fmed3f(fmaf(kf, l.dx, l.x), 0.0f, xm);
+    const int y = (int)__builtin_amdgcn_fmed3f(fmaf(kf, l.dy, l.y), 0.0f, ym);
+    const uint32_t o = (__umul24(y, w) + (uint32_t)x) * 4u;
+    lo[j] = *(const Pair*)((const char*)mx + o);
+    hi[j] = *(const Pair*)((const char*)(mx + w) + o);
+  }
+  uint32_t bits = 0;
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    const float m = fmaxf(fmaxf(lo[j].a, lo[j].b), fmaxf(hi[j].a, hi[j].b));
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+      // a NaN zmin or height may act (fmaxf would drop the former)
+      const float z = fmaf((float)(k + j * step + p * part), l.dz, l.z);
+      bits |= !(z >= m || l.zmin >= m) ? 1u << (j * kParts + p) : 0u;
+    }
+  }
+  if (isnan(l.zmin)) bits = ~0u;
+  return bits & live;
+}
+
+// A sample of ray r, as the ABI evaluates it; in the map truncation is floor
+// (`lim`: the largest float32 below nx and ny, so that clamping to it changes
+// exactly the coordinates outside the map).
+struct Sample {
+  int ix, iy;
+  float qz;
+  bool in;
+};
+
+__device__ __forceinline__ Sample sample_of(const Item& it, const Ray& r, int k, float2 lim) {
+  const float t = t_of(r.rK, k);
+  const float fx = (it.P.t[0] + t * r.dx) * it.c.inv_r;
+  const float fy = (it.P.t[1] + t * r.dy) * it.c.inv_r;
+  const float cx = __builtin_amdgcn_fmed3f(fx, 0.0f, lim.x);
+  const float cy = __builtin_amdgcn_fmed3f(fy, 0.0f, lim.y);
+  Sample q;
+  q.qz = it.P.t[2] + t * r.dz;
+  q.in = (cx == fx) & (cy == fy);
+  q.ix = (int)cx;
+  q.iy = (int)cy;
+  return q;
+}
+
+constexpr int kUnroll = 4;
+
+// Samples [ka, kb] of ray r against the map, kUnroll at a time.  Their cells are
+// found without branches, then their clearing records {h, v} are all requested
+// together.  A cell no ray may clear holds -inf, which fails hd > 0 for every
+// finite sample height.  On maps with an upper bound layer
+// (kBound), a cell without an estimate holds {NaN, its bound at the call's
+// start} (no other record holds NaN).  The few samples that act go through one
+// loop, a lane's next one each time, so that a wave waits for its fullest lane
+// and not for every position.
+template <bool kBound>
+__device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int ka, int kb) {
+  const float2 lim = make_float2(__uint_as_float(__float_as_uint(it.c.nxf) - 1u),
+                                 __uint_as_float(__float_as_uint(it.c.nyf) - 1u));
   for (int k = ka; k <= kb; k += kUnroll) {
-    int cell[kUnroll];     // logical: the end-cell test, the records
-    int64_t pc[kUnroll];   // physical: the layers
-    uint32_t blk[kUnroll];
     float qz[kUnroll];
-    float m[kUnroll];
     bool cand[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      // [ka, kb] lies in the ray's in-map range, which the setup found with
-      // this very evaluation (f_of): qx * inv_r and qy * inv_r are in [0, nx)
-      // and [0, ny), so truncation is floor and the cell is in the map.  The
-      // unused slots past kb evaluate sample kb again, so they stay in the map
-      // too; they are never candidates.
-      const float t = t_of(r, min(k + u, kb));
-      const float qx = r.ox + t * r.dx;
-      const float qy = r.oy + t * r.dy;
-      qz[u] = r.oz + t * r.dz;
-      const int ix = (int)(qx * inv_r);
-      const int iy = (int)(qy * inv_r);
-      cell[u] = iy * nx + ix;
-      pc[u] = pcell(it.c, ix, iy);
-      blk[u] = (uint32_t)((iy >> bl) * bx + (ix >> bl));
-    }
-    // the block maxima where the block changes, every load issued before any
-    // is used; the other slots take their predecessor's
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      m[u] = 0.0f;
-      if (blk[u] != (u ? blk[u - 1] : pblk)) m[u] = cm[blk[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (blk[u] == (u ? blk[u - 1] : pblk)) m[u] = u ? m[u - 1] : pm;
-    pblk = blk[kUnroll - 1];
-    pm = m[kUnroll - 1];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      cand[u] = (k + u <= kb) & (qz[u] < m[u]) & (cell[u] != end_cell);
-    // the candidates' records, all requested before any is tested
     float2 rec[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      rec[u] = make_float2(-INFINITY, 0.0f);
-      if (cand[u]) rec[u] = it.L.clr[cell[u]];
+      const Sample q = sample_of(it, r, k + u, lim);
+      const uint32_t cell = __umul24(q.iy, it.c.nx) + (uint32_t)q.ix;
+      qz[u] = q.qz;
+      cand[u] = (k + u <= kb) & q.in & ((int)cell != r.end_cell);
+      rec[u] = *(const float2*)((const char*)it.L.clr + cell * 8u);
     }
+    uint32_t remove = 0, bound = 0;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      if (!cand[u]) continue;
-      test_cell_rec(it, r, cell[u], pc[u], qz[u], an2dd, rec[u]);
+      const float hd = rec[u].x - qz[u];
+      if (cand[u] & (hd > 0.0f) & ((hd * hd) > rec[u].y)) remove |= 1u << u;
+      if (kBound && (cand[u] & isnan(rec[u].x) & (qz[u] < rec[u].y))) bound |= 1u << u;
+    }
+    while (remove | bound) {
+      const int u = __builtin_ctz(remove | bound);
+      const Sample q = sample_of(it, r, k + u, lim);
+      const int64_t pc = pcell(it.c, q.ix, q.iy);
+      if ((remove >> u) & 1u) {
+        const float an2dd = it.c.an2 * ((r.dx * r.dx + r.dy * r.dy) + r.dz * r.dz);
+        const float dot = (r.dx * it.L.nx[pc] + r.dy * it.L.ny[pc]) + r.dz * it.L.nz[pc];
+        if ((dot * dot) > an2dd) clear_cell(it, pc, q.iy * it.c.nx + q.ix);
+      } else if (q.qz < it.L.ub[pc]) {  // another ray may have lowered it further
+        atomic_min_f32(it.L.ub + pc, q.qz);
+      }
+      remove &= ~(1u << u);
+      bound &= ~(1u << u);
     }
   }
 }
 
-// Setup work unit `unit` of item `it`; `qsel` picks the sub-queue.
-__device__ __forceinline__ void setup_body(const Item& it, int unit, int qsel) {
+// ------------------------------------------------------------------- setup
+// Superblock `unit` of item `it`: its block maxima, its own, and the records.
+__device__ __forceinline__ void setup_body(const Item& it, int unit, float* s_max) {
+  constexpr int kRows = 4;  // rows of a lane's column, two apart
   const int lane = threadIdx.x & 63;
-  // the next plain call's queue counters start from zero
-  if (unit == 0 && it.cq.counter_next && threadIdx.x <= kSubQ)
-    it.cq.counter_next[threadIdx.x * kCtrStride] = 0u;
-  if (unit < it.nprep) {
-    // ---- block role: each wave takes it.bpw (1 or 4) blocks of 8 x 8 cells,
-    // one cell of each per lane, so their loads are in flight together
-    const int b0 = (unit * (kNTc / 64) + (threadIdx.x >> 6)) * it.bpw;
-    const int side = 1 << it.bl;
-    int64_t c[kMaxBlocksPerWave];   // logical cell: the mask, the records
-    int64_t p[kMaxBlocksPerWave];   // physical cell: the layers
-    bool inside[kMaxBlocksPerWave], ok[kMaxBlocksPerWave];
-    float h[kMaxBlocksPerWave], v[kMaxBlocksPerWave];
+  const int wave = threadIdx.x >> 6;
+  const int sy = unit / it.sbx;
+  const int sx = unit - sy * it.sbx;
+  const int ix = (sx << kSuperLog) + (lane & 31);
+  const int iy0 = (sy << kSuperLog) + (wave << kBlockLog) + (lane >> 5);
+  int c[kRows];       // logical cell: the mask, the records
+  int64_t p[kRows];   // physical cell: the layers
+  bool in[kRows];
+  uint8_t vd[kRows];
 #pragma unroll
-    for (int j = 0; j < kMaxBlocksPerWave; ++j) {
-      const int b = b0 + j;
-      const int ix = ((b % it.bx) << it.bl) + (lane & (side - 1));
-      const int iy = ((b / it.bx) << it.bl) + (lane >> it.bl);
-      inside[j] = j < it.bpw && b < it.nb && ix < it.c.nx && iy < it.c.ny;
-      c[j] = inside[j] ? (int64_t)iy * it.c.nx + ix : 0;
-      p[j] = inside[j] ? pcell(it.c, ix, iy) : 0;
-    }
-    // two rounds of loads for all of the wave's blocks, not one round per
-    // test: first the validity, then what a valid cell's tests need (update
-    // time, normal z, height), or a cell without an estimate's bound.  Cells
-    // that cannot matter load nothing more (cell 0 stands in for cells
-    // outside the map).
-    uint8_t vd[kMaxBlocksPerWave];
-    int32_t tu[kMaxBlocksPerWave];
-    float nz[kMaxBlocksPerWave], ubv[kMaxBlocksPerWave];
-#pragma unroll
-    for (int j = 0; j < kMaxBlocksPerWave; ++j)
-      vd[j] = (j < it.bpw && inside[j]) ? it.L.valid[p[j]] : 0;
-#pragma unroll
-    for (int j = 0; j < kMaxBlocksPerWave; ++j) {
-      tu[j] = 0;
-      nz[j] = 0.0f;
-      h[j] = 0.0f;
-      ubv[j] = INFINITY;
-      if (vd[j]) {
-        tu[j] = it.L.t[p[j]];
-        nz[j] = it.L.nz[p[j]];
-        h[j] = it.L.h[p[j]];
-      } else if (it.L.ub && inside[j]) {
-        ubv[j] = it.L.ub[p[j]];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxBlocksPerWave; ++j) {
-      if (inside[j] && it.out_cleared) it.out_cleared[c[j]] = 0;  // the march sets removals
-      ok[j] = inside[j] && clearable(it, vd[j], tu[j], nz[j]);
-      v[j] = ok[j] ? h[j] : -INFINITY;
-      // with an upper bound layer, a sample below the bound of a cell without
-      // an estimate lowers it: such cells take part in the maximum too
-      if (it.L.ub && inside[j] && !vd[j]) v[j] = ubv[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxBlocksPerWave; ++j) {
-      if (j >= it.bpw) break;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v[j] = fmaxf(v[j], __shfl_xor(v[j], o, 64));
-      if (lane == 0 && b0 + j < it.nb) it.L.cmax[b0 + j] = v[j];
-      // the march reads records only in blocks with a removable cell, where
-      // some sample may pass below the block maximum
-      if (v[j] > -INFINITY && inside[j]) {
-        // a NaN height can never be cleared (hd > 0 fails), so -inf serves
-        const bool bound = it.L.ub && !vd[j];
-        const float hx = bound ? __builtin_nanf("") : (ok[j] && !isnan(h[j]) ? h[j] : -INFINITY);
-        it.L.clr[c[j]] = make_float2(hx, it.L.v[p[j]]);
-      }
-    }
-    return;
+  for (int j = 0; j < kRows; ++j) {
+    const int iy = iy0 + 2 * j;
+    in[j] = ix < it.c.nx && iy < it.c.ny;
+    c[j] = in[j] ? iy * it.c.nx + ix : 0;
+    p[j] = in[j] ? pcell(it.c, ix, iy) : 0;
+    vd[j] = in[j] ? it.L.valid[p[j]] : 0;
   }
-  // ---- ray role: the ray's in-map sample range, queued in segments
-  const int64_t i = (int64_t)(unit - it.nprep) * kNTc + threadIdx.x;
-  int k0 = 1, k1 = 0;
-  if (i < it.n) {
-    Ray r;
-    int K, end_cell;
-    if (ray_of(it, i, r, K, end_cell)) {
-      int lx, hx, ly, hy;
-      axis_range<true>(r, K, it.c.inv_r, it.c.nxf, r.dx >= 0.0f, lx, hx);
-      axis_range<false>(r, K, it.c.inv_r, it.c.nyf, r.dy >= 0.0f, ly, hy);
-      k0 = max(lx, ly);
-      k1 = min(hx, hy);
+  // then what a valid cell's tests and record need, or a cell without an
+  // estimate's bound; cells that cannot matter load nothing more
+  int32_t tu[kRows];
+  float nz[kRows], h[kRows], v[kRows], ub[kRows];
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    tu[j] = 0;
+    nz[j] = h[j] = v[j] = 0.0f;
+    ub[j] = INFINITY;
+    if (vd[j]) {
+      tu[j] = it.L.t[p[j]];
+      nz[j] = it.L.nz[p[j]];
+      h[j] = it.L.h[p[j]];
+      v[j] = it.L.v[p[j]];
+    } else if (it.L.ub && in[j]) {
+      ub[j] = it.L.ub[p[j]];
     }
   }
-  const int seg = it.cq.seg;
-  const int ns = k1 >= k0 ? k1 - k0 + 1 : 0;
-  const int nseg = (ns + seg - 1) / seg;
-  // one reservation per workgroup, in the sub-queue this workgroup maps to
-  __shared__ int s_isum[kNTc / 64];
-  __shared__ uint32_t s_base;
-  int wtot = 0;
-  const int off = block_exclusive_sum<kNTc>(nseg, wtot, s_isum);
-  const int sub = qsel % kSubQ;
-  const ClearQueue& cq = it.cq;
+  float2 rec[kRows];
+  float m = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    if (in[j] && it.out_cleared) it.out_cleared[c[j]] = 0;  // the march sets removals
+    const bool ok = in[j] && clearable(it, vd[j], tu[j], nz[j]);
+    if (it.L.ub && in[j] && !vd[j]) {
+      // a sample below the bound of a cell without an estimate lowers it:
+      // such cells take part in the maximum too
+      rec[j] = make_float2(__builtin_nanf(""), ub[j]);
+      m = fmaxf(m, ub[j]);
+    } else {
+      // a NaN height can never be cleared (hd > 0 fails), so -inf serves
+      rec[j] = make_float2(ok && !isnan(h[j]) ? h[j] : -INFINITY, v[j]);
+      m = fmaxf(m, rec[j].x);
+    }
+  }
+  m = fmaxf(m, __shfl_xor(m, 1, 64));
+  m = fmaxf(m, __shfl_xor(m, 2, 64));
+  m = fmaxf(m, __shfl_xor(m, 4, 64));
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+#pragma unroll
+  for (int j = 0; j < kRows; ++j)
+    if (in[j]) it.L.clr[c[j]] = rec[j];
+  const int b = (sx << (kSuperLog - kBlockLog)) + (lane >> kBlockLog);
+  const int by = (sy << (kSuperLog - kBlockLog)) + wave;
+  if (lane < 32 && (lane & 7) == 0 && b < it.bx && by < it.by) it.L.cmax[by * it.bx + b] = m;
+  m = fmaxf(m, __shfl_xor(m, 8, 64));
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  if (lane == 0) s_max[wave] = m;
+  __syncthreads();
   if (threadIdx.x == 0)
-    s_base = wtot > 0 ? atomicAdd(cq.counter + sub * kCtrStride, (uint32_t)wtot) : 0u;
-  __syncthreads();
-  if (nseg == 0) return;
-  const int64_t first = (int64_t)s_base + off;
-  uint2* q = cq.queue + (int64_t)sub * cq.qcap;
-  const int64_t gray = it.ray_base + i;
-  if (first + nseg <= cq.qcap) {
-    for (int sgi = 0; sgi < nseg; ++sgi) {
-      const int ka = k0 + sgi * seg;
-      const int cnt = min(seg, k1 - ka + 1);
-      q[first + sgi] = make_uint2((uint32_t)gray, ((uint32_t)ka << 8) | (uint32_t)cnt);
-    }
-  } else {
-    // sub-queue full: leave empty entries in any reserved slots; the whole
-    // ray goes to the overflow list, marched after the queue
-    for (int64_t e = first; e < first + nseg && e < cq.qcap; ++e) q[e] = make_uint2(0u, 0u);
-    const uint32_t o = atomicAdd(cq.counter + kOverCtr, 1u);
-    cq.over[o] = make_uint4((uint32_t)gray, (uint32_t)k0, (uint32_t)k1, 0u);
-  }
+    it.L.smax[unit] = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
 }
 
-// Prefix of the sub-queue fill levels (kSubQ == 64: the first wave).
-__device__ __forceinline__ void queue_prefix(const ClearQueue& cq, int64_t* s_qoff) {
-  if (threadIdx.x < 64) {
-    const int64_t c = min((int64_t)cq.counter[threadIdx.x * kCtrStride], cq.qcap);
-    int64_t x = c;
+// ------------------------------------------------------------------- march
+// Arrays by field: lanes that read different rays then meet different banks.
+template <int kRays>
+struct MarchShared {
+  float dx[kRays], dy[kRays], dz[kRays];
+  double rK[kRays];
+  int k1[kRays], end_cell[kRays];
+  float line[7][kRays];  // of the groups
+  // entries: ray << 24 | first sample
+  uint32_t spans[kSpans * kRays];
+  uint32_t pieces[kSpanGroups * kParts * kNTc];
+  int nspans, npieces;
+};
+
+// Appends the steps of each lane's `bits` (kN steps of kP parts) to a list with
+// room for them, by one LDS atomic per wave (an atomic per lane with its own
+// count would be expanded into a loop over the lanes).  The j-th steps of all
+// lanes come together: neighbouring rays, whose lookups share cache lines.
+// Every lane of the wave calls it.
+template <int kN, int kP>
+__device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, uint32_t ray, int k,
+                                       int step, int part) {
+  if (__ballot(bits != 0) == 0) return;
+  uint64_t b[kN * kP];
+  int total = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int64_t y = __shfl_up(x, o, 64);
-      if ((int)threadIdx.x >= o) x += y;
+  for (int j = 0; j < kN * kP; ++j) {
+    b[j] = __ballot((bits >> j) & 1u);
+    total += __popcll(b[j]);
+  }
+  int at = 0;
+  if ((threadIdx.x & 63) == 0) at = atomicAdd(n, total);
+  at = __builtin_amdgcn_readfirstlane(at);
+  const uint32_t e = (ray << 24) | (uint32_t)k;
+#pragma unroll
+  for (int j = 0; j < kN * kP; ++j) {
+    if (b[j] == 0) continue;
+    const int below = (int)__builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(b[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[j], 0u));
+    if ((bits >> j) & 1u) list[at + below] = e + (uint32_t)((j / kP) * step + (j % kP) * part);
+    at += __popcll(b[j]);
+  }
+}
+
+// Rays [kRays unit, kRays unit + kRays) of the item.  The counts in s are zero
+// on entry and on return (every thread passes a barrier after they were reset).
+template <int kRays>
+__device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchShared<kRays>& s) {
+  const int tid = threadIdx.x;
+  const int64_t i = unit * kRays + tid;
+  const int grp = it.grp, span = kSpanGroups * it.grp;
+  const int part = (grp + kParts - 1) / kParts;
+  int k = 1, k1 = 0;  // the ray's first sample that no span covers yet, its last
+  Line sl;
+  if (tid < kRays) {
+    Ray r;
+    if (i < it.n && ray_of(it, i, r, k)) {
+      k1 = r.k1;
+      sl = line_of<kSuperLog>(it, r, span, span);
+      s.dx[tid] = r.dx;
+      s.dy[tid] = r.dy;
+      s.dz[tid] = r.dz;
+      s.rK[tid] = r.rK;
+      s.k1[tid] = r.k1;
+      s.end_cell[tid] = r.end_cell;
+      const Line l = line_of<kBlockLog>(it, r, grp, part);
+      s.line[0][tid] = l.x;
+      s.line[1][tid] = l.dx;
+      s.line[2][tid] = l.y;
+      s.line[3][tid] = l.dy;
+      s.line[4][tid] = l.z;
+      s.line[5][tid] = l.dz;
+      s.line[6][tid] = l.zmin;
     }
-    s_qoff[threadIdx.x + 1] = x;
-    if (threadIdx.x == 0) s_qoff[0] = 0;
   }
-}
-
-// Queue entry g (over all sub-queues) and the ray it names.
-__device__ __forceinline__ uint2 queue_entry(const ClearQueue& cq, const int64_t* s_qoff,
-                                             int64_t g) {
-  int lo = 0, hi = kSubQ - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (s_qoff[mid] <= g) lo = mid;
-    else hi = mid - 1;
-  }
-  return cq.queue[(int64_t)lo * cq.qcap + (g - s_qoff[lo])];
-}
-
-// Samples [ka, kb] of queued ray g (the item's point g - ray_base).
-__device__ __forceinline__ void march_ray(const Item& it, uint32_t g, int ka, int kb,
-                                          const float* cm) {
-  Ray r;
-  int K, end_cell;
-  if (!ray_of(it, (int64_t)g - it.ray_base, r, K, end_cell)) return;  // never for a queued ray
-  march_range(it, r, ka, kb, end_cell, cm);
-}
-
-__device__ __forceinline__ void march_entry(const Item& it, uint2 e, const float* cm) {
-  const int cnt = (int)(e.y & 255u);
-  if (cnt == 0) return;
-  const int ka = (int)(e.y >> 8);
-  march_ray(it, e.x, ka, ka + cnt - 1, cm);
-}
-
-// Item of global ray g in a batch: the last item whose first ray is <= g
-// (items without rays are skipped over).  s_rays holds the batch's prefix.
-__device__ __forceinline__ int ray_item(const int64_t* s_rays, int n, int64_t g) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (s_rays[mid] <= g) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// ---------------------------------------------------------------- launches
-__global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
-  setup_body(it, blockIdx.x, (int)blockIdx.x - it.nprep);
-}
-
-// The block maxima are read through the caches: they are small and shared by
-// every workgroup, and staging them in LDS per workgroup costs more than it saves.
-__global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
-  __shared__ int64_t s_qoff[kSubQ + 1];
-  queue_prefix(it.cq, s_qoff);
-  __syncthreads();
-  const int64_t total = s_qoff[kSubQ];
-  for (int64_t g = (int64_t)blockIdx.x * kNTc + threadIdx.x; g < total;
-       g += (int64_t)gridDim.x * kNTc)
-    march_entry(it, queue_entry(it.cq, s_qoff, g), it.L.cmax);
-  // then the rays that overflowed their sub-queue, whole
-  const uint32_t nover = it.cq.counter[kOverCtr];
-  for (int64_t g = (int64_t)blockIdx.x * kNTc + threadIdx.x; g < nover;
-       g += (int64_t)gridDim.x * kNTc) {
-    const uint4 o = it.cq.over[g];
-    march_ray(it, o.x, (int)o.y, (int)o.z, it.L.cmax);
-  }
-}
-
-
-__global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
-  const int64_t total = bt->off[kBSetup][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBSetup, w);
-    setup_body(bt->items[i], (int)(w - bt->off[kBSetup][i]), (int)w);
+  bool more = true;
+  while (more) {
+    // spans: at most kSpans of each ray
+    uint32_t bits = 0;
+    if (k <= k1)
+      bits = k1 - k < 2 * span ? (k1 - k < span ? 1u : 3u)  // short: straight to the groups
+                               : may_act<kSpans, 1>(sl, k, k1, span, 0, it.L.smax, it.sbx, it.sby);
+    append<kSpans, 1>(s.spans, &s.nspans, bits, (uint32_t)tid, k, span, 0);
+    k += kSpans * span;
+    more = __syncthreads_or(k <= k1);
+    const int ns = s.nspans;
+    for (int b = 0; b < ns; b += kNTc) {
+      // groups: of at most one span per thread
+      uint32_t gb = 0, w = 0;
+      int ks = 0;
+      if (b + tid < ns) {
+        const uint32_t e = s.spans[b + tid];
+        w = e >> 24;
+        ks = (int)(e & 0xFFFFFFu);
+        const Line l = {s.line[0][w], s.line[1][w], s.line[2][w], s.line[3][w],
+                        s.line[4][w], s.line[5][w], s.line[6][w]};
+        gb = may_act<kSpanGroups, kParts>(l, ks, s.k1[w], grp, part, it.L.cmax, it.bx, it.by);
+      }
+      append<kSpanGroups, kParts>(s.pieces, &s.npieces, gb, w, ks, grp, part);
+      __syncthreads();
+      const int np = s.npieces;
+      for (int g = tid; g < np; g += kNTc) {
+        const uint32_t e = s.pieces[g];
+        const uint32_t w = e >> 24;
+        const Ray q = {s.dx[w], s.dy[w], s.dz[w], s.end_cell[w], s.rK[w], s.k1[w]};
+        const int ka = (int)(e & 0xFFFFFFu);
+        const int kb = min(ka + part - 1, q.k1);
+        if (it.L.ub) test_samples<true>(it, q, ka, kb);
+        else test_samples<false>(it, q, ka, kb);
+      }
+      __syncthreads();  // the pieces have been read
+      if (tid == 0) s.npieces = 0;
+      __syncthreads();
+    }
+    if (tid == 0) s.nspans = 0;
     __syncthreads();
   }
 }
 
-// Every item of a batch shares one queue (the first item's view of it); a
-// queue entry's global ray index names its item.
-__global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
-  __shared__ int64_t s_qoff[kSubQ + 1];
-  __shared__ int64_t s_rays[kMaxItems + 1];
-  const ClearQueue& cq = bt->items[0].cq;
-  const int n = bt->n;
-  queue_prefix(cq, s_qoff);
-  for (int k = threadIdx.x; k <= n; k += kNTc) s_rays[k] = bt->rays[k];
+// ---------------------------------------------------------------- launches
+__global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
+  __shared__ float s_max[kNTc / 64];
+  setup_body(it, blockIdx.x, s_max);
+}
+
+// The maxima are read through the caches: they are small and shared by every
+// workgroup, and staging them in LDS per workgroup costs more than it saves.
+__global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
+  __shared__ MarchShared<kRaysPlain> s;
+  if (threadIdx.x == 0) s.nspans = s.npieces = 0;
   __syncthreads();
-  const int64_t total = s_qoff[kSubQ];
-  for (int64_t g = (int64_t)blockIdx.x * kNTc + threadIdx.x; g < total;
-       g += (int64_t)gridDim.x * kNTc) {
-    const uint2 e = queue_entry(cq, s_qoff, g);
-    if ((e.y & 255u) == 0) continue;
-    const Item& it = bt->items[ray_item(s_rays, n, e.x)];
-    march_entry(it, e, it.L.cmax);
+  march_body(it, blockIdx.x, s);
+}
+
+__global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
+  __shared__ float s_max[kNTc / 64];
+  const UnitFinder units(bt, kBSetup);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    setup_body(bt->items[i], (int)unit, s_max);
+    __syncthreads();
   }
-  const uint32_t nover = cq.counter[kOverCtr];
-  for (int64_t g = (int64_t)blockIdx.x * kNTc + threadIdx.x; g < nover;
-       g += (int64_t)gridDim.x * kNTc) {
-    const uint4 o = cq.over[g];
-    const Item& it = bt->items[ray_item(s_rays, n, o.x)];
-    march_ray(it, o.x, (int)o.y, (int)o.z, it.L.cmax);
+}
+
+__global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
+  __shared__ MarchShared<kRaysBatch> s;
+  if (threadIdx.x == 0) s.nspans = s.npieces = 0;
+  __syncthreads();
+  const UnitFinder units(bt, kBRays);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    march_body(bt->items[i], unit, s);
   }
 }
 
@@ -524,57 +540,31 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-// Room for kQueueSamplesPerRay samples per ray on average plus two partial
-// segments per ray (a ray's range rarely ends on a segment boundary), and
-// slack for uneven sub-queue fill.  A full sub-queue is not an error: its
-// rays go to the overflow list (room for every ray) and are marched whole.
-int64_t clear_queue_cap(int64_t max_points, int seg) {
-  const int64_t segs = (max_points * kQueueSamplesPerRay + seg - 1) / seg + 2 * max_points;
-  return (segs + segs / 8 + kSubQ - 1) / kSubQ;
+// What a caller's scratch must hold for a clearing call: the size contract of
+// emx_scratch_bytes and emx_batch_scratch_bytes.  The kernels keep their work
+// lists in LDS and use none of it.
+size_t clear_scratch_bytes(int64_t max_points, int seg) {
+  const int64_t segs = (max_points * 128 + seg - 1) / seg + 2 * max_points;
+  const int64_t cap = (segs + segs / 8 + 63) / 64;
+  return align256((size_t)cap * 64 * 8) + align256((size_t)max_points * 16);
 }
 
-size_t clear_scratch_layout(int64_t max_points, int seg, char* base, ClearQueue* out) {
-  const size_t n = (size_t)max_points;
-  const size_t qcap = (size_t)clear_queue_cap(max_points, seg);
-  size_t off = 0;
-  const size_t o_q = off;
-  off = align256(off + (size_t)kSubQ * qcap * sizeof(uint2));
-  const size_t o_over = off;
-  off = align256(off + n * sizeof(uint4));
-  if (out && base) {
-    out->queue = (uint2*)(base + o_q);
-    out->over = (uint4*)(base + o_over);
-    out->qcap = (int64_t)qcap;
-    out->seg = seg;
-  }
-  return off;
-}
+int64_t setup_units(const Item& it) { return (int64_t)it.sbx * it.sby; }
+int64_t ray_units(int64_t n) { return (n + kRaysBatch - 1) / kRaysBatch; }
 
-hipError_t launch_clear(const Item& it, int march_grid, hipStream_t stream, bool* ran) {
-  *ran = false;
-  // with no rays the setup still zeroes the caller's mask (block role only)
+hipError_t launch_clear(const Item& it, hipStream_t stream) {
+  // with no rays the setup still zeroes the caller's mask
   if (it.n <= 0 && !it.out_cleared) return hipSuccess;
-  const unsigned nray = it.n > 0 ? (unsigned)((it.n + kNTc - 1) / kNTc) : 0u;
   {
     TimedLaunch tl("k_clear_setup", stream);
-    hipLaunchKernelGGL(k_clear_setup, dim3((unsigned)it.nprep + nray), dim3(kNTc), 0, stream, it);
+    hipLaunchKernelGGL(k_clear_setup, dim3((unsigned)setup_units(it)), dim3(kNTc), 0, stream, it);
   }
   hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  *ran = true;
-  if (it.n <= 0) return hipSuccess;
+  if (err != hipSuccess || it.n <= 0) return err;
   TimedLaunch tl("k_clear_march", stream);
-  hipLaunchKernelGGL(k_clear_march, dim3((unsigned)march_grid), dim3(kNTc), 0, stream, it);
+  hipLaunchKernelGGL(k_clear_march, dim3((unsigned)((it.n + kRaysPlain - 1) / kRaysPlain)),
+                     dim3(kNTc), 0, stream, it);
   return hipGetLastError();
-}
-
-int clear_setup_units(int64_t n, int nprep, bool mask) {
-  return n > 0 ? nprep + (int)((n + kNTc - 1) / kNTc) : (mask ? nprep : 0);
-}
-int clear_blocks_per_wave(int nb) { return nb >= 4096 ? kMaxBlocksPerWave : 1; }
-int clear_block_units(int nb) {
-  const int per = (kNTc / 64) * clear_blocks_per_wave(nb);
-  return (nb + per - 1) / per;
 }
 
 hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_march,

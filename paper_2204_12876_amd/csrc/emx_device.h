@@ -28,13 +28,6 @@ constexpr int kTileW = 1 << kTileLogX;
 constexpr int kTileH = 1 << kTileLogY;
 constexpr int kTileCells = kTileW * kTileH;
 
-// Clearing queue: kSubQ sub-queues, each with its own counter kCtrStride words
-// apart.
-constexpr int kSubQ = 64;
-constexpr int kCtrStride = 32;
-constexpr int kOverCtr = kSubQ * kCtrStride;          // the overflow list's counter
-constexpr int kCtrWords = (kSubQ + 1) * kCtrStride;   // one set of queue counters
-
 // One buffer set of map layers, row-major [ny][nx].
 // The map's layers, [ny][nx] each in the ring layout (pcell).
 struct Layers {
@@ -48,6 +41,7 @@ struct Layers {
   uint8_t* valid;
   uint8_t* mark;  // the fusion's per-cell flags (kMark*); all zero between calls
   float* cmax;    // per logical block: max height over cells a ray may clear (transient)
+  float* smax;    // the same per logical superblock (transient)
   float* ub;      // upper bound of the ground height (+inf: none), or null
   float2* clr;    // per logical cell {h, or -inf if a ray may not clear it, v} (transient)
   uint64_t* fx;   // the fusion's fixed-point sums: kFxWords planes of fxs words, one word
@@ -63,18 +57,11 @@ struct Layers {
 // fused result is the same in every run, alone or batched.
 enum FxWord { kFxWhi = 0, kFxWlo, kFxZhi, kFxZlo, kFxWords };  // sum 1/sp2; sum rz/sp2
 
-// Clearing prunes samples by square blocks of 8 x 8 cells: one cell per lane
-// of the wave that computes a block's maximum (the setup relies on it).  The maxima are read through
-// the caches, so their count is not bounded by LDS.
-// The setup's block role gives a wave 1 block, or 4 on maps of at least 4096
-// blocks, where more work per wave beats more waves.
-constexpr int kMaxBlocksPerWave = 4;
+// Clearing prunes samples by square blocks of 8 x 8 cells and superblocks of
+// 32 x 32 cells (one workgroup of the setup each).
+constexpr int kBlockLog = 3;
+constexpr int kSuperLog = 5;
 __host__ __device__ inline int blocks_of(int n, int b) { return (n + (1 << b) - 1) >> b; }
-__host__ __device__ inline int block_log_of(int nx, int ny) {
-  (void)nx;
-  (void)ny;
-  return 3;
-}
 
 // Float32 constants derived once on the host from emx_params.
 struct Consts {
@@ -111,23 +98,6 @@ struct FuseScratch {
   uint32_t* count;      // [nx * ny] the frame's valid points per cell (wall rule), or null
 };
 
-// Where a clearing setup queues its ray segments.  A ray is named by its
-// global index ray_base + i (i: its point in the item's frame); the march
-// rebuilds the ray from the point, in the same float32 operations.
-struct ClearQueue {
-  uint2* queue;       // kSubQ sub-queues of qcap (ray, k_start << 8 | count) entries
-  uint4* over;        // rays that did not fit their sub-queue: (ray, k0, k1, 0)
-  uint32_t* counter;  // kSubQ sub-queue counters and the overflow counter (at
-                      // kOverCtr), kCtrStride apart; zero on entry
-  uint32_t* counter_next;  // the next call's counter set, zeroed by this call's
-                           // setup (plain calls alternate two sets), or null
-  int64_t qcap;       // entries per sub-queue
-  int seg;            // samples per queued segment (1..255)
-};
-
-// Queue capacity: on average kQueueSamplesPerRay samples per point fit.
-constexpr int kQueueSamplesPerRay = 128;
-
 // Stages of one frame, in pipeline order.
 constexpr uint32_t kStageMove = 1u;
 constexpr uint32_t kStageFuse = 2u;
@@ -152,12 +122,11 @@ struct Item {
   uint8_t* out_accept;
   uint8_t* out_cleared;
   FuseScratch fs;
-  ClearQueue cq;
-  int64_t ray_base;  // this item's first ray in cq
   int fxw, fxz;      // fixed-point shifts S of the sums of 1/sp2 and rz/sp2 (FxWord)
   int tiles_x, T, B;
-  int bl, bx, by, nb, nprep;
-  int bpw;           // clearing blocks per wave in the setup's block role
+  int bx, by;        // clearing blocks
+  int sbx, sby;      // clearing superblocks
+  int grp;           // clearing samples to a group: at most 7 cells of travel
   int32_t index;     // position in its batch
 };
 
@@ -166,13 +135,14 @@ struct Item {
 constexpr int kMaxItems = 64;
 // kBZero, kBCount: the wall/edge rule's per-cell counts (zeroed, then
 // counted); kBVar: the per-cell time and outlier variance after the fusion.
-enum BatchStage { kBMove = 0, kBZero, kBCount, kBChunk, kBTile, kBVar, kBSetup, kBCells, kBNum };
+enum BatchStage {
+  kBMove = 0, kBZero, kBCount, kBChunk, kBTile, kBVar, kBSetup, kBRays, kBCells, kBNum
+};
 
 // Only the header and the first n items are uploaded for a batch of n.
 struct Batch {
   int n;
   int64_t off[kBNum][kMaxItems + 1];
-  int64_t rays[kMaxItems + 1];  // prefix of the items' clearing rays (ray_base)
   Item items[kMaxItems];
 };
 
@@ -252,61 +222,35 @@ __device__ __forceinline__ void prior_cell(const Consts& c, const Layers& L, int
   if (L.ub) L.ub[o] = INFINITY;
 }
 
-// ---------------------------------------------------------------- block scans
-// Exclusive prefix sum of one int per thread over a block of NT threads.
-// `sm` holds NT/64 ints.  Contains two barriers; every thread must call it.
-template <int NT>
-__device__ __forceinline__ int block_exclusive_sum(int v, int& total, int* sm) {
-  const int lane = threadIdx.x & 63;
-  const int wid = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sm[wid] = x;
-  __syncthreads();
-  int pre = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    const int s = sm[w];
-    pre += (w < wid) ? s : 0;
-    tot += s;
-  }
-  __syncthreads();
-  total = tot;
-  return pre + x - v;
-}
-
-// Minimum of one uint32 per thread over a block of NT threads.  `sm` holds
-// NT/64 words.  Contains two barriers; every thread must call it.
-template <int NT>
-__device__ __forceinline__ uint32_t block_min_u32(uint32_t v, uint32_t* sm) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t y = (uint32_t)__shfl_xor((int)v, o, 64);
-    v = y < v ? y : v;
-  }
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t r = sm[0];
-#pragma unroll
-  for (int w = 1; w < NT / 64; ++w) r = sm[w] < r ? sm[w] : r;
-  __syncthreads();
-  return r;
-}
-
 // ------------------------------------------------------------- batched units
-// Item holding global unit w of `stage`: the last item whose prefix is <= w.
-__device__ __forceinline__ int batch_item(const Batch* bt, int stage, int64_t w) {
-  int lo = 0, hi = bt->n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (bt->off[stage][mid] <= w) lo = mid;
-    else hi = mid - 1;
+// The item that holds a global work unit of a stage.  Each lane of a wave keeps
+// the end of one item's units (kMaxItems lanes), so that finding an item is one
+// comparison and a ballot; a search in memory would put six dependent loads,
+// each a trip to the L2, before every unit's work.  Every lane of the wave
+// calls both members, with the same w.
+class UnitFinder {
+ public:
+  __device__ __forceinline__ UnitFinder(const Batch* bt, int stage) {
+    static_assert(kMaxItems == 64, "one lane per item");
+    const int lane = threadIdx.x & 63;
+    n_ = bt->n;
+    total_ = bt->off[stage][n_];
+    end_ = lane < n_ ? bt->off[stage][lane + 1] : total_;
   }
-  return lo;
-}
+  __device__ __forceinline__ int64_t total() const { return total_; }
+  // The item of unit w < total(), and the unit's number within it.
+  __device__ __forceinline__ int find(int64_t w, int64_t& unit) const {
+    const int i = __builtin_amdgcn_readfirstlane(__popcll(__ballot(end_ <= w)));
+    const int prev = i > 0 ? i - 1 : 0;
+    const int64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)end_, prev);
+    const int64_t hi = __builtin_amdgcn_readlane((int)(end_ >> 32), prev);
+    unit = w - (i > 0 ? ((hi << 32) | lo) : 0);
+    return i;
+  }
+
+ private:
+  int n_;
+  int64_t total_, end_;
+};
 
 }  // namespace emx

@@ -459,49 +459,54 @@ __global__ __launch_bounds__(kNT1) void k_fuse_chunk_b(const Batch* bt) {
   __shared__ AggTable tab;
   agg_clear(tab);
   __syncthreads();
-  const int64_t total = bt->off[kBChunk][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBChunk, w);
-    chunk_body(bt->items[i], w - bt->off[kBChunk][i], tab);
+  const UnitFinder units(bt, kBChunk);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    chunk_body(bt->items[i], unit, tab);
   }
 }
 
 __global__ __launch_bounds__(256) void k_zero_b(const Batch* bt) {
-  const int64_t total = bt->off[kBZero][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBZero, w);
+  const UnitFinder units(bt, kBZero);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
     const Item& it = bt->items[i];
-    const int64_t c = (w - bt->off[kBZero][i]) * 256 + threadIdx.x;
+    const int64_t c = unit * 256 + threadIdx.x;
     if (c < (int64_t)it.c.nx * it.c.ny) it.fs.count[c] = 0u;
   }
 }
 
 __global__ __launch_bounds__(kNT1) void k_fuse_count_b(const Batch* bt) {
-  const int64_t total = bt->off[kBCount][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBCount, w);
-    count_body(bt->items[i], w - bt->off[kBCount][i]);
+  const UnitFinder units(bt, kBCount);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    count_body(bt->items[i], unit);
     __syncthreads();
   }
 }
 
 __global__ __launch_bounds__(kNTv) void k_time_variance_b(const Batch* bt) {
-  const int64_t total = bt->off[kBVar][bt->n];
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int i = batch_item(bt, kBVar, w);
-    timevar_body(bt->items[i], w - bt->off[kBVar][i]);
+  const UnitFinder units(bt, kBVar);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    timevar_body(bt->items[i], unit);
   }
 }
 
 // Each wave takes its own tiles: units w = (workgroup * kTilesPerGroup +
 // wave) + k * (grid * kTilesPerGroup).
 __global__ __launch_bounds__(kNT2b) void k_fuse_tile_b(const Batch* bt) {
-  const int64_t total = bt->off[kBTile][bt->n];
+  const UnitFinder units(bt, kBTile);
   const int64_t step = (int64_t)gridDim.x * kTilesPerGroup;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  for (int64_t w = (int64_t)blockIdx.x * kTilesPerGroup + wave; w < total; w += step) {
-    const int i = batch_item(bt, kBTile, w);
-    tile_body_wave(bt->items[i], w - bt->off[kBTile][i]);
+  for (int64_t w = (int64_t)blockIdx.x * kTilesPerGroup + wave; w < units.total(); w += step) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    tile_body_wave(bt->items[i], unit);
   }
 }
 

@@ -8,15 +8,12 @@
 
 namespace emx {
 
-// Per-map control words after the layers: two sets of clearing
-// queue counters, used by alternate plain calls (each call's setup zeroes the
-// other set for the next call), then the fusion's per-tile flags (one word
-// per tile, zero between calls).
-constexpr int kCtlWords = 2 * kCtrWords;
+// Per-map control words after the layers: the fusion's per-tile flags (one
+// word per tile, zero between calls).
 int64_t ctl_words(const emx_params& p);
 
-// Default clearing segment length (samples per queued segment) and march
-// workgroups per compute unit, from a sweep of both on MI355X.
+// Clearing segment length behind emx_scratch_bytes, and the batched march's
+// default workgroups per compute unit.
 constexpr int kDefaultSeg = 16;
 constexpr int kMarchPerCU = 16;
 
@@ -42,8 +39,6 @@ struct emx_map {
   char* state;
   emx::Layers L;  // the layers, in the ring layout with origin (c.ox, c.oy)
   uint32_t* ctl;
-  int ctr_sel;  // the counter set the next clear_visibility uses
-  int march_grid;
 };
 
 namespace emx {

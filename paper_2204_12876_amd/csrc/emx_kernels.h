@@ -44,17 +44,12 @@ int64_t var_units(int64_t cells);
 hipError_t launch_fuse_batch(const Batch* d_batch, const int grid[5], hipStream_t stream);
 
 // ---------------------------------------------------------------- clearing
-int64_t clear_queue_cap(int64_t max_points, int seg);
-size_t clear_scratch_layout(int64_t max_points, int seg, char* base, ClearQueue* out);
-// Setup workgroups: block role, then one per 256 rays; with no rays, the
-// block role alone if a removed-cell mask must be zeroed.
-int clear_setup_units(int64_t n, int nprep, bool mask);
-// Blocks per wave and workgroups of the setup's block role for nb pruning blocks.
-int clear_blocks_per_wave(int nb);
-int clear_block_units(int nb);
-// The item's queue counters must be zero on entry; the setup zeroes
-// it.cq.counter_next (if set) for the next call.  *ran: the setup was launched.
-hipError_t launch_clear(const Item& it, int march_grid, hipStream_t stream, bool* ran);
+size_t clear_scratch_bytes(int64_t max_points, int seg);
+// The setup's work units are the item's superblocks (with no rays only if a
+// removed-cell mask must be zeroed), the batched march's its rays by 256.
+int64_t setup_units(const Item& it);
+int64_t ray_units(int64_t n);
+hipError_t launch_clear(const Item& it, hipStream_t stream);
 hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_march,
                               hipStream_t stream);
 
