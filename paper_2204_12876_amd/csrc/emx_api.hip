@@ -368,7 +368,7 @@ static emx_status fuse_impl(emx_map* m, const emx_frame* f, bool move, double cx
   it.out_accept = d_out_accept;
   it.stages = kStageFuse;
   hipError_t e = hipSuccess;
-  if (shift) e = launch_move(it, (hipStream_t)stream);
+  if (shift && f->n == 0) e = launch_move(it, (hipStream_t)stream);
   if (e == hipSuccess && run) e = launch_fuse(it, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, move ? "move_fuse_points" : "fuse_points");
   if (shift) {

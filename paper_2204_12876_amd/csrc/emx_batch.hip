@@ -7,8 +7,8 @@
 // Then, on the caller's stream:
 //   - one copy of the table's header and its n items into the caller's
 //     scratch;
-//   - one graph of persistent launches: move, the wall rule's counts (zeroed,
-//     then counted) if a map uses it, fusion pass 1 and pass 2, the per-cell
+//   - one graph of persistent launches: the wall rule's counts (zeroed, then
+//     counted) if a map uses it, fusion pass 1 with the moves, pass 2, the per-cell
 //     variances if a map uses time or outlier variance, clearing setup and
 //     march, then normals + traversability.
 // Every launch finds its work in the table, so a graph depends only on the
@@ -64,8 +64,8 @@ bool json_int(const char* js, const char* key, int* out) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// grid: move, zero, count, chunk, tile, variance, setup, march, cells
-constexpr int kGrids = 9;
+// grid: zero, count, chunk (with the moves), tile, variance, setup, march, cells
+constexpr int kGrids = 8;
 
 struct GraphKey {
   void* scratch;
@@ -342,7 +342,7 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
     tab->off[kBMove][i + 1] = tab->off[kBMove][i] + (moved ? move_units(it) : 0);
     tab->off[kBZero][i + 1] = tab->off[kBZero][i] + (wall ? zero_units(cells) : 0);
     tab->off[kBCount][i + 1] = tab->off[kBCount][i] + (wall ? it.B : 0);
-    tab->off[kBChunk][i + 1] = tab->off[kBChunk][i] + (fuse ? it.B : 0);
+    tab->off[kBChunk][i + 1] = tab->off[kBChunk][i] + (fuse ? chunk_units(it.n) : 0);
     tab->off[kBTile][i + 1] = tab->off[kBTile][i] + (fuse ? it.T : 0);
     tab->off[kBVar][i + 1] = tab->off[kBVar][i] + (var ? var_units(cells) : 0);
     tab->off[kBSetup][i + 1] =
@@ -362,15 +362,14 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   auto cap_opt = [&](int tuned, int64_t units) { return units < 1 ? 0 : cap(tuned, units); };
   GraphKey key;
   key.scratch = d_scratch;
-  key.grid[0] = cap(t.grid_move, tab->off[kBMove][n]);
-  key.grid[1] = cap_opt(t.grid_cells, tab->off[kBZero][n]);
-  key.grid[2] = cap_opt(t.grid_chunk, tab->off[kBCount][n]);
-  key.grid[3] = cap(t.grid_chunk, tab->off[kBChunk][n]);
-  key.grid[4] = cap(t.grid_tile, tab->off[kBTile][n]);
-  key.grid[5] = cap_opt(t.grid_cells, tab->off[kBVar][n]);
-  key.grid[6] = cap(t.grid_setup, tab->off[kBSetup][n]);
-  key.grid[7] = cap(t.grid_march, tab->off[kBRays][n]);
-  key.grid[8] = cap(t.grid_cells, tab->off[kBCells][n]);
+  key.grid[0] = cap_opt(t.grid_cells, tab->off[kBZero][n]);
+  key.grid[1] = cap_opt(t.grid_chunk, tab->off[kBCount][n]);
+  key.grid[2] = cap(t.grid_chunk, tab->off[kBMove][n] + tab->off[kBChunk][n]);
+  key.grid[3] = cap(t.grid_tile, tab->off[kBTile][n]);
+  key.grid[4] = cap_opt(t.grid_cells, tab->off[kBVar][n]);
+  key.grid[5] = cap(t.grid_setup, tab->off[kBSetup][n]);
+  key.grid[6] = cap(t.grid_march, tab->off[kBRays][n]);
+  key.grid[7] = cap(t.grid_cells, tab->off[kBCells][n]);
 
   // ---- enqueue: the table upload, then a cached graph or the same launches
   hipStream_t st = (hipStream_t)stream;
@@ -378,10 +377,9 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   e = hipMemcpyAsync(d_tab, tab, upload, hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return hip_fail(e, "pipeline_batch: table upload");
   auto enqueue = [&](hipStream_t q) -> hipError_t {
-    hipError_t r = launch_move_batch(d_tab, key.grid[0], q);
-    if (r == hipSuccess) r = launch_fuse_batch(d_tab, key.grid + 1, q);
-    if (r == hipSuccess) r = launch_clear_batch(d_tab, key.grid[6], key.grid[7], q);
-    if (r == hipSuccess) r = launch_cells_batch(d_tab, key.grid[8], q);
+    hipError_t r = launch_fuse_batch(d_tab, key.grid, q);
+    if (r == hipSuccess) r = launch_clear_batch(d_tab, key.grid[5], key.grid[6], q);
+    if (r == hipSuccess) r = launch_cells_batch(d_tab, key.grid[7], q);
     return r;
   };
   if (t.graph) {

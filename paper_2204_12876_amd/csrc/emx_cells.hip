@@ -1,4 +1,5 @@
-// Per-cell passes: prior fill, robot-centric move, 3x3 normals, conv traversability.
+// Per-cell passes: prior fill, robot-centric move (alone; before a fusion it
+// runs in that launch), 3x3 normals, conv traversability.
 //
 // The stencils (normals, traversability) stage a 66 x 18 halo tile of heights
 // and validity in LDS.  Each 256-thread workgroup then produces a 64 x 16
@@ -70,52 +71,6 @@ __global__ __launch_bounds__(kNTf) void k_fill_prior(FillArgs a) {
   a.L.mark[i] = 0;
   if (a.L.ub) a.L.ub[i] = INFINITY;
   for (int k = 0; k < kFxWords; ++k) a.L.fx[k * a.L.fxs + i] = 0u;
-}
-
-// ------------------------------------------------------------------------ move
-// The ring has already turned (it.c holds the new origin); the cells that
-// enter the map go back to the prior.  With a shift (sx, sy) they are the
-// logical columns [nx - sx, nx) (sx > 0) or [0, -sx) (sx < 0) in every row,
-// and the logical rows [ny - sy, ny) or [0, -sy) in every column; a shift of a
-// whole side resets every cell.  One thread per cell: the column strip, then
-// the row strip (their corner twice, with the same values).
-struct Strips {
-  int ncol, nrow;   // entering columns and rows
-  bool all;         // every cell enters
-  int64_t cells;    // threads needed
-};
-
-__host__ __device__ __forceinline__ Strips strips_of(const Item& it) {
-  Strips s;
-  const int ax = it.sx < 0 ? -it.sx : it.sx;
-  const int ay = it.sy < 0 ? -it.sy : it.sy;
-  s.ncol = ax < it.c.nx ? ax : it.c.nx;
-  s.nrow = ay < it.c.ny ? ay : it.c.ny;
-  s.all = s.ncol == it.c.nx || s.nrow == it.c.ny;
-  s.cells = s.all ? (int64_t)it.c.nx * it.c.ny
-                  : (int64_t)s.ncol * it.c.ny + (int64_t)s.nrow * it.c.nx;
-  return s;
-}
-
-__device__ __forceinline__ void move_body(const Item& it, int64_t unit) {
-  const Strips st = strips_of(it);
-  const int64_t q = unit * kNTf + threadIdx.x;
-  if (q >= st.cells) return;
-  int ix, iy;
-  if (st.all) {
-    iy = (int)(q / it.c.nx);
-    ix = (int)(q - (int64_t)iy * it.c.nx);
-  } else if (q < (int64_t)st.ncol * it.c.ny) {
-    iy = (int)(q / st.ncol);
-    const int k = (int)(q - (int64_t)iy * st.ncol);
-    ix = it.sx > 0 ? it.c.nx - st.ncol + k : k;
-  } else {
-    const int64_t q2 = q - (int64_t)st.ncol * it.c.ny;
-    const int k = (int)(q2 / it.c.nx);
-    ix = (int)(q2 - (int64_t)k * it.c.nx);
-    iy = it.sy > 0 ? it.c.ny - st.nrow + k : k;
-  }
-  prior_cell(it.c, it.L, pcell(it.c, ix, iy));
 }
 
 // ------------------------------------------------------------ overlap clearance
@@ -272,7 +227,9 @@ __device__ __forceinline__ void cells_body(const Item& it, int64_t unit, bool do
 }
 
 // ---------------------------------------------------------------- launches
-__global__ __launch_bounds__(kNTf) void k_move(Item it) { move_body(it, blockIdx.x); }
+__global__ __launch_bounds__(kNTf) void k_move(Item it) {
+  move_body<kNTf>(it, blockIdx.x);
+}
 // One workgroup per output tile, each XCD taking a contiguous range of tiles.
 __global__ __launch_bounds__(kNTf) void k_normals(Item it) {
   cells_body(it, xcd_unit(blockIdx.x, gridDim.x), true, false);
@@ -283,15 +240,6 @@ __global__ __launch_bounds__(kNTf) void k_trav(Item it) {
 // Both from one staged tile: the heights are read once.
 __global__ __launch_bounds__(kNTf) void k_normals_trav(Item it) {
   cells_body(it, xcd_unit(blockIdx.x, gridDim.x), true, true);
-}
-
-__global__ __launch_bounds__(kNTf) void k_move_b(const Batch* bt) {
-  const UnitFinder units(bt, kBMove);
-  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
-    int64_t unit;
-    const int i = units.find(w, unit);
-    move_body(bt->items[i], unit);
-  }
 }
 
 // Each XCD takes a contiguous range of the batch's tiles (xcd_unit_k).
@@ -311,7 +259,6 @@ __global__ __launch_bounds__(kNTf) void k_cells_b(const Batch* bt) {
 
 }  // namespace
 
-int64_t move_units(const Item& it) { return (strips_of(it).cells + kNTf - 1) / kNTf; }
 int64_t cells_units(int nx, int ny) {
   return (int64_t)blocks_of(nx, kSWLog) * blocks_of(ny, kSHLog);
 }
@@ -339,7 +286,7 @@ hipError_t launch_overlap(const OverlapArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_move(const Item& it, hipStream_t stream) {
-  const int64_t units = move_units(it);
+  const int64_t units = (strips_of(it).cells + kNTf - 1) / kNTf;
   if (units == 0) return hipSuccess;
   TimedLaunch tl("k_move", stream);
   hipLaunchKernelGGL(k_move, dim3((unsigned)units), dim3(kNTf), 0, stream, it);
@@ -364,14 +311,6 @@ hipError_t launch_normals_trav(const Item& it, hipStream_t stream) {
   TimedLaunch tl("k_normals_trav", stream);
   hipLaunchKernelGGL(k_normals_trav, dim3((unsigned)cells_units(it.c.nx, it.c.ny)), dim3(kNTf), 0,
                      stream, it);
-  return hipGetLastError();
-}
-
-hipError_t launch_move_batch(const Batch* d_batch, int grid, hipStream_t stream) {
-  {
-    TimedLaunch tl("k_move_b", stream);
-    hipLaunchKernelGGL(k_move_b, dim3(grid), dim3(kNTf), 0, stream, d_batch);
-  }
   return hipGetLastError();
 }
 

@@ -222,6 +222,62 @@ __device__ __forceinline__ void prior_cell(const Consts& c, const Layers& L, int
   if (L.ub) L.ub[o] = INFINITY;
 }
 
+// ------------------------------------------------------------------------ move
+// The ring has already turned (it.c holds the new origin); the cells that
+// enter the map go back to the prior.  With a shift (sx, sy) they are the
+// logical columns [nx - sx, nx) (sx > 0) or [0, -sx) (sx < 0) in every row,
+// and the logical rows [ny - sy, ny) or [0, -sy) in every column; a shift of a
+// whole side resets every cell.  One thread per cell: the column strip, then
+// the row strip (their corner twice, with the same values).  Where the move is
+// followed by a fusion, its pass 1 resets the cells in the same launch and
+// takes the prior for entering cells itself (entering).
+struct Strips {
+  int ncol, nrow;   // entering columns and rows
+  bool all;         // every cell enters
+  int64_t cells;    // threads needed
+};
+
+__host__ __device__ __forceinline__ Strips strips_of(const Item& it) {
+  Strips s;
+  const int ax = it.sx < 0 ? -it.sx : it.sx;
+  const int ay = it.sy < 0 ? -it.sy : it.sy;
+  s.ncol = ax < it.c.nx ? ax : it.c.nx;
+  s.nrow = ay < it.c.ny ? ay : it.c.ny;
+  s.all = s.ncol == it.c.nx || s.nrow == it.c.ny;
+  s.cells = s.all ? (int64_t)it.c.nx * it.c.ny
+                  : (int64_t)s.ncol * it.c.ny + (int64_t)s.nrow * it.c.nx;
+  return s;
+}
+
+// Whether logical cell (ix, iy) has entered the map with the item's move.
+__device__ __forceinline__ bool entering(const Item& it, int ix, int iy) {
+  return (it.sx > 0 && ix >= it.c.nx - it.sx) || (it.sx < 0 && ix < -it.sx) ||
+         (it.sy > 0 && iy >= it.c.ny - it.sy) || (it.sy < 0 && iy < -it.sy);
+}
+
+// Unit `unit` of kT of the entering cells, one per thread.
+template <int kT>
+__device__ __forceinline__ void move_body(const Item& it, int64_t unit) {
+  const Strips st = strips_of(it);
+  const int64_t q = unit * kT + threadIdx.x;
+  if (q >= st.cells) return;
+  int ix, iy;
+  if (st.all) {
+    iy = (int)(q / it.c.nx);
+    ix = (int)(q - (int64_t)iy * it.c.nx);
+  } else if (q < (int64_t)st.ncol * it.c.ny) {
+    iy = (int)(q / st.ncol);
+    const int k = (int)(q - (int64_t)iy * st.ncol);
+    ix = it.sx > 0 ? it.c.nx - st.ncol + k : k;
+  } else {
+    const int64_t q2 = q - (int64_t)st.ncol * it.c.ny;
+    const int k = (int)(q2 / it.c.nx);
+    ix = (int)(q2 - (int64_t)k * it.c.nx);
+    iy = it.sy > 0 ? it.c.ny - st.nrow + k : k;
+  }
+  prior_cell(it.c, it.L, pcell(it.c, ix, iy));
+}
+
 // ------------------------------------------------------------- batched units
 // The item that holds a global work unit of a stage.  Each lane of a wave keeps
 // the end of one item's units (kMaxItems lanes), so that finding an item is one

@@ -9,18 +9,26 @@
 // order the additions land in: results are bitwise identical from run to run,
 // alone or batched, whatever the grid shape.
 //
-// Pass 1, chunk body: one workgroup per chunk of kChunk points, kPerThread
-// points per thread, consecutive points in consecutive lanes.
+// Pass 1, chunk body: one workgroup per chunk of consecutive points, consecutive
+// points in consecutive lanes.
 //   - Takes the per-point decisions: transform, range, bin, exclusion area,
 //     wall/edge rule, and the Mahalanobis gate against the frame-start prior.
 //   - Converts an accepted point's 1/sp2 and rz/sp2 to fixed point (rz: the
 //     rotated point's height, zm = rz + tz; tz * sum 1/sp2 is added back in
 //     pass 2, which keeps the terms independent of the sensor's height).
-//   - Sums each run of consecutive lanes in one cell within the wave
-//     (sensors emit points in scan order, so most runs span several points),
-//     then each cell's runs in an LDS table for the chunk, and adds the
-//     chunk's sums to the cell's words (FxWord planes) with integer atomics;
-//     the cell's tile is flagged.
+//   - Sums the chunk's points per cell in an LDS table: the first lane of each
+//     run of one cell finds the run's slot (sensors emit points in scan order,
+//     so most runs span several points), then every lane adds its own words
+//     with LDS integer atomics.  Words that are zero, as the low words of most
+//     terms are at these scales, are not added.  A segmented scan of the four
+//     words over the wave in front of the table cost 54 cross-lane moves per
+//     wave and four such scans in a row per thread: 15 against 9 us for a 300k
+//     frame, 144 against 80 us for a batch of 16 maps.
+//   - Adds the chunk's sums to the cells' words (FxWord planes) with integer
+//     atomics; the cells' tiles are flagged.
+//   - Where the call moves the map first, further workgroups of the same launch
+//     reset the entering cells, and points in them take the prior (a launch of
+//     its own took 3 us of every frame).
 // Pass 2, tile body: per 32 x 16-cell tile of the physical layout, a
 // workgroup with one thread per cell (plain calls) or one wave with eight
 // cells per lane (batches).  An unflagged tile returns after one load;
@@ -35,40 +43,17 @@ namespace emx {
 
 namespace {
 
-constexpr int kNT1 = 256;                   // pass-1 threads
-constexpr int kPerThread = kChunk / kNT1;   // points per thread
+constexpr int kNT1 = 256;                   // threads of the wall rule's counts
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;   // lanes without an accepted point
 
-// The integer X = round(x * 2^S) of a finite float32 x (ties to even), as
-// X = hi * 2^32 + lo with 0 <= lo < 2^32.  Exact for |x| * 2^S < 2^94, which
-// the choice of S guarantees: x = m * 2^(e - 150) with the 24-bit significand
-// m, so X is m shifted by e - 150 + S bits, in two words.
+// The integer X = round(x * 2^S) (ties to even) of a finite float32 x, as
+// X = hi * 2^32 + lo with 0 <= lo < 2^32.  Every step is exact in float64: x has
+// 24 significant bits and the choice of S keeps |X| < 2^94.
 __device__ __forceinline__ void fx_split(float x, int S, int64_t& hi, uint64_t& lo) {
-  const uint32_t b = __float_as_uint(x);
-  const uint32_t ex = (b >> 23) & 255u;
-  const uint64_t m = (uint64_t)((b & 0x7FFFFFu) | (ex ? 0x800000u : 0u));
-  const int sh = (int)(ex ? ex : 1u) - 150 + S;
-  uint64_t h = 0, l = 0;
-  if (sh >= 32) {
-    h = m << (sh - 32);  // X < 2^94: h < 2^62
-  } else if (sh >= 0) {
-    const uint64_t v = m << sh;  // < 2^56
-    h = v >> 32;
-    l = v & 0xFFFFFFFFull;
-  } else if (sh >= -24) {
-    const int r = -sh;
-    const uint64_t q = m >> r;
-    const uint64_t rem = m & ((1ull << r) - 1ull);
-    const uint64_t half = 1ull << (r - 1);
-    l = q + ((rem > half || (rem == half && (q & 1ull))) ? 1ull : 0ull);
-  }  // else |x| * 2^S < 2^-1: rounds to zero
-  if (b >> 31) {  // -(h * 2^32 + l) with the low word kept non-negative
-    hi = -(int64_t)h - (l != 0 ? 1 : 0);
-    lo = (0x100000000ull - l) & 0xFFFFFFFFull;
-  } else {
-    hi = (int64_t)h;
-    lo = l;
-  }
+  const double d = rint(ldexp((double)x, S));
+  const double h = floor(d * 0x1p-32);
+  hi = (int64_t)h;
+  lo = (uint64_t)(uint32_t)fma(h, -0x1p32, d);
 }
 
 // (hi * 2^32 + lo) * 2^-S in float64.
@@ -77,39 +62,26 @@ __device__ __forceinline__ double fx_value(int64_t hi, uint64_t lo, int S) {
 }
 
 // ------------------------------------------------------------------ pass 1
-// Inclusive sums over each run of equal keys in the wave, in place: after the
-// call a lane holds the sum of its run's lanes up to and including itself.
-// Combining (flag, value) pairs: earlier (+) later = later.flag ? later :
-// earlier + later, where a flag marks a run's first lane.
-__device__ __forceinline__ void run_sums(uint32_t key, int64_t& whi, uint64_t& wlo,
-                                         int64_t& zhi, uint64_t& zlo) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t prev = (uint32_t)__shfl_up((int)key, 1, 64);
-  int f = (lane == 0 || prev != key) ? 1 : 0;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int pf = __shfl_up(f, o, 64);
-    const int64_t a = __shfl_up(whi, o, 64);
-    const uint64_t b = __shfl_up(wlo, o, 64);
-    const int64_t c = __shfl_up(zhi, o, 64);
-    const uint64_t d = __shfl_up(zlo, o, 64);
-    if (lane >= o) {
-      if (!f) {
-        whi += a;
-        wlo += b;
-        zhi += c;
-        zlo += d;
-      }
-      f |= pf;
-    }
-  }
-}
-
 // A chunk's sums are gathered per cell in an LDS table before they go to the
 // map: kAggSlots slots of (cell + 1, four words), open addressing with at most
 // kAggProbes probes.  A run that finds no slot adds to the map directly.
-constexpr int kAggSlots = 512;
+constexpr int kAggLog = 9;
+constexpr int kAggSlots = 1 << kAggLog;
 constexpr int kAggProbes = 8;
+constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
+
+// Chunks.  A frame alone takes one point per thread: its few workgroups wait for
+// each step of their chain, and four points per thread put four of each step in
+// a row.  Up to one 256-point chunk for each compute unit (20k points on 128 x
+// 128 cells: 4.2 against 5.9 us with 1024; 43k on 250 x 250: 4.5 against 6.7);
+// above, 1024-point chunks, whose table joins more of a cell's runs before the
+// map's atomics (300k on 400 x 400: 9.1 against 13.2 us with 256).  A batch has
+// workgroups to spare, and 256 threads with four points each leave more of them
+// in flight (16 maps, 4.6M points: 80 against 91 us).
+constexpr int64_t kSmallFrame = 65536;
+constexpr int kThreadsLarge = 1024;
+constexpr int kThreadsBatch = 256;
+constexpr int kPointsBatch = 4;
 
 struct AggTable {
   uint32_t key[kAggSlots];                   // physical cell + 1; 0 = free
@@ -129,52 +101,53 @@ __device__ __forceinline__ uint32_t tile_of_cell(const Item& it, uint32_t cell) 
 }
 
 // Zeroes the table (every thread of the block; the caller synchronises).
+template <int kT>
 __device__ __forceinline__ void agg_clear(AggTable& t) {
-  for (int s = threadIdx.x; s < kAggSlots; s += kNT1) {
+  for (int s = threadIdx.x; s < kAggSlots; s += kT) {
     t.key[s] = 0u;
 #pragma unroll
     for (int k = 0; k < kFxWords; ++k) t.v[k][s] = 0ull;
   }
 }
 
-// One chunk of kChunk points: point chunk * kChunk + j * kNT1 + thread of
-// step j.  Every lane runs the wave's run sums, also past the frame's end.
-// On entry the table is zero; it is zero again on return.
+// One chunk of kT * kP points; a thread takes kP of them, kT apart, so that
+// consecutive points lie in consecutive lanes.  On entry the table is zero; it
+// is zero again on return.
+template <int kT, int kP>
 __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTable& tab) {
   const int lane = threadIdx.x & 63;
-  // the thread's kPerThread points, every load issued before any is used:
-  // first the coordinates, then the prior of each point's cell
-  PointEval e[kPerThread];
-  int64_t pc[kPerThread];
-  int cell[kPerThread];
-  bool in[kPerThread], gated[kPerThread];
-  float h0[kPerThread], v0[kPerThread];
-  uint32_t cnt[kPerThread];
-  uint8_t vd[kPerThread];
-  {
-    float xs[kPerThread], ys[kPerThread], zs[kPerThread];
+  float x[kP], y[kP], z[kP];
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-      const int64_t i = chunk * kChunk + j * kNT1 + threadIdx.x;
-      in[j] = i < it.n;
-      xs[j] = in[j] ? it.x[i] : 0.0f;
-      ys[j] = in[j] ? it.y[i] : 0.0f;
-      zs[j] = in[j] ? it.z[i] : 0.0f;
-    }
+  for (int j = 0; j < kP; ++j) {
+    const int64_t i = (chunk * kP + j) * kT + threadIdx.x;
+    const bool in = i < it.n;  // past the end: a point at the sensor, never valid
+    x[j] = in ? it.x[i] : 0.0f;
+    y[j] = in ? it.y[i] : 0.0f;
+    z[j] = in ? it.z[i] : 0.0f;
+  }
+  // the priors of the thread's points, every load issued before any is used
+  PointEval e[kP];
+  uint32_t pc[kP], cnt[kP];
+  int cell[kP];
+  float h0[kP], v0[kP];
+  uint8_t vd[kP];
+  bool gated[kP];
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-      e[j] = eval_point(it.P, it.c, xs[j], ys[j], zs[j]);
-      int ix = 0, iy = 0;
-      const bool inmap = in[j] && e[j].valid && bin_xy(e[j].xm, e[j].ym, it.c, ix, iy);
-      cell[j] = inmap ? iy * it.c.nx + ix : -1;
-      pc[j] = inmap ? pcell(it.c, ix, iy) : 0;
-      // points of the exclusion area are ignored
-      gated[j] = inmap && (!it.c.excl_on || !excluded_point(it.P, it.c, e[j]));
-      h0[j] = 0.0f;
-      v0[j] = 0.0f;
-      cnt[j] = 0u;
-      vd[j] = 0;
-      if (gated[j]) {
+  for (int j = 0; j < kP; ++j) {
+    e[j] = eval_point(it.P, it.c, x[j], y[j], z[j]);
+    int ix = 0, iy = 0;
+    const bool inmap = e[j].valid && bin_xy(e[j].xm, e[j].ym, it.c, ix, iy);
+    cell[j] = inmap ? iy * it.c.nx + ix : -1;
+    // points of the exclusion area are ignored
+    gated[j] = inmap && (!it.c.excl_on || !excluded_point(it.P, it.c, e[j]));
+    pc[j] = 0;
+    h0[j] = it.c.h_init;
+    v0[j] = it.c.v_init;
+    cnt[j] = 0u;
+    vd[j] = 0;
+    if (gated[j]) {
+      pc[j] = (uint32_t)pcell(it.c, ix, iy);
+      if (!entering(it, ix, iy)) {  // else the prior, which this launch is storing
         h0[j] = it.L.h[pc[j]];
         v0[j] = it.L.v[pc[j]];
         if (it.fs.count) cnt[j] = it.fs.count[pc[j]];
@@ -183,10 +156,10 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
     }
   }
 #pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
-    const int64_t i = chunk * kChunk + j * kNT1 + threadIdx.x;
+  for (int j = 0; j < kP; ++j) {
+    const int64_t i = (chunk * kP + j) * kT + threadIdx.x;
     uint32_t key = kNoCell;  // the accepted point's physical cell
-    float w = 0.0f, u = 0.0f;
+    uint64_t v[kFxWords] = {0, 0, 0, 0};
     bool acc = false;
     if (gated[j]) {
       const float d = e[j].zm - h0[j];
@@ -200,42 +173,46 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
       // the outlier variance (a plain store: every writer stores 2)
       if (it.c.var_o != 0.0f && !inside && !walled && vd[j]) it.L.mark[pc[j]] = kMarkOutlier;
       if (acc) {
-        key = (uint32_t)pc[j];
-        w = 1.0f / e[j].sp2;
-        u = w * e[j].rz;
+        key = pc[j];
+        const float w = 1.0f / e[j].sp2;
+        int64_t hi;
+        fx_split(w, it.fxw, hi, v[kFxWlo]);
+        v[kFxWhi] = (uint64_t)hi;
+        if (hi == 0 && v[kFxWlo] == 0) v[kFxWlo] = 1;  // an accepted point adds at least one unit
+        fx_split(w * e[j].rz, it.fxz, hi, v[kFxZlo]);
+        v[kFxZhi] = (uint64_t)hi;
       }
     }
-    if (in[j]) {
+    if (i < it.n) {
       if (it.out_cell) it.out_cell[i] = cell[j];
       if (it.out_accept) it.out_accept[i] = acc ? 1 : 0;
     }
-    int64_t whi = 0, zhi = 0;
-    uint64_t wlo = 0, zlo = 0;
-    if (key != kNoCell) {
-      fx_split(w, it.fxw, whi, wlo);
-      if (whi == 0 && wlo == 0) wlo = 1;  // an accepted point adds at least one unit
-      fx_split(u, it.fxz, zhi, zlo);
-    }
-    run_sums(key, whi, wlo, zhi, zlo);
-    const uint32_t next = (uint32_t)__shfl_down((int)key, 1, 64);
-    if (key != kNoCell && (lane == 63 || next != key)) {
-      // the run's sums into the chunk's table, or straight to the map
-      const uint64_t v[4] = {(uint64_t)whi, wlo, (uint64_t)zhi, zlo};
-      uint32_t h = (key * 2654435761u) >> (32 - 9);
-      static_assert(kAggSlots == 1 << 9, "the hash yields 9 bits");
-      bool placed = false;
+    // the first lane of each run of one cell finds the run's slot ...
+    const uint32_t prev = (uint32_t)__shfl_up((int)key, 1, 64);
+    const bool head = key != kNoCell && (lane == 0 || prev != key);
+    const uint64_t heads = __ballot(head);
+    if (heads == 0) continue;
+    uint32_t slot = kNoSlot;
+    if (head) {
+      uint32_t h = (key * 2654435761u) >> (32 - kAggLog);
       for (int p = 0; p < kAggProbes; ++p) {
-        const uint32_t prev = atomicCAS(&tab.key[h], 0u, key + 1u);
-        if (prev == 0u || prev == key + 1u) {
-#pragma unroll
-          for (int k = 0; k < kFxWords; ++k)
-            if (v[k]) atomicAdd(&tab.v[k][h], (unsigned long long)v[k]);
-          placed = true;
+        const uint32_t was = atomicCAS(&tab.key[h], 0u, key + 1u);
+        if (was == 0u || was == key + 1u) {
+          slot = h;
           break;
         }
         h = (h + 1u) & (kAggSlots - 1);
       }
-      if (!placed) {
+    }
+    // ... and its lanes add to it, or straight to the map
+    const uint64_t upto = heads & (~0ull >> (63 - lane));
+    slot = (uint32_t)__shfl((int)slot, upto ? 63 - __builtin_clzll(upto) : 0, 64);
+    if (key != kNoCell) {
+      if (slot != kNoSlot) {
+#pragma unroll
+        for (int k = 0; k < kFxWords; ++k)
+          if (v[k]) atomicAdd(&tab.v[k][slot], (unsigned long long)v[k]);
+      } else {
         add_to_map(it, key, v);
         it.fs.tcnt[tile_of_cell(it, key)] = 1u;
       }
@@ -243,13 +220,13 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
   }
   __syncthreads();
   // the table's cells to the map; the table back to zero
-  for (int s = threadIdx.x; s < kAggSlots; s += kNT1) {
+  for (int s = threadIdx.x; s < kAggSlots; s += kT) {
     const uint32_t k1 = tab.key[s];
     if (k1 == 0u) continue;
-    const uint32_t cell = k1 - 1u;
-    const uint64_t v[4] = {tab.v[0][s], tab.v[1][s], tab.v[2][s], tab.v[3][s]};
-    add_to_map(it, cell, v);
-    it.fs.tcnt[tile_of_cell(it, cell)] = 1u;
+    const uint32_t c = k1 - 1u;
+    const uint64_t t[4] = {tab.v[0][s], tab.v[1][s], tab.v[2][s], tab.v[3][s]};
+    add_to_map(it, c, t);
+    it.fs.tcnt[tile_of_cell(it, c)] = 1u;
     tab.key[s] = 0u;
 #pragma unroll
     for (int k = 0; k < kFxWords; ++k) tab.v[k][s] = 0ull;
@@ -446,24 +423,35 @@ __global__ __launch_bounds__(256) void k_zero_u32(uint32_t* p, int64_t n) {
 }
 
 // ---------------------------------------------------------------- launches
-__global__ __launch_bounds__(kNT1) void k_fuse_chunk(Item it) {
+// The first `chunks` workgroups take points, the others the cells of the move.
+template <int kT>
+__global__ __launch_bounds__(kT) void k_fuse_chunk(Item it, uint32_t chunks) {
   __shared__ AggTable tab;
-  agg_clear(tab);
+  if (blockIdx.x >= chunks) {
+    move_body<kT>(it, blockIdx.x - chunks);
+    return;
+  }
+  agg_clear<kT>(tab);
   __syncthreads();
-  chunk_body(it, blockIdx.x, tab);
+  chunk_body<kT, 1>(it, blockIdx.x, tab);
 }
 
 __global__ __launch_bounds__(kNT2) void k_fuse_tile(Item it) { tile_body_group(it, blockIdx.x); }
 
-__global__ __launch_bounds__(kNT1) void k_fuse_chunk_b(const Batch* bt) {
+__global__ __launch_bounds__(kThreadsBatch) void k_fuse_chunk_b(const Batch* bt) {
   __shared__ AggTable tab;
-  agg_clear(tab);
+  agg_clear<kThreadsBatch>(tab);
   __syncthreads();
-  const UnitFinder units(bt, kBChunk);
-  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+  const UnitFinder units(bt, kBChunk), moves(bt, kBMove);
+  for (int64_t w = blockIdx.x; w < moves.total() + units.total(); w += gridDim.x) {
     int64_t unit;
-    const int i = units.find(w, unit);
-    chunk_body(bt->items[i], unit, tab);
+    if (w < moves.total()) {
+      const int i = moves.find(w, unit);
+      move_body<kThreadsBatch>(bt->items[i], unit);
+    } else {
+      const int i = units.find(w - moves.total(), unit);
+      chunk_body<kThreadsBatch, kPointsBatch>(bt->items[i], unit, tab);
+    }
   }
 }
 
@@ -578,7 +566,15 @@ hipError_t launch_fuse(const Item& it, hipStream_t stream) {
     }
     {
       TimedLaunch tl("k_fuse_chunk", stream);
-      hipLaunchKernelGGL(k_fuse_chunk, dim3(it.B), dim3(kNT1), 0, stream, it);
+      const int64_t entering = strips_of(it).cells;
+      const auto go = [&](auto kernel, int threads) {
+        const int64_t chunks = (it.n + threads - 1) / threads;
+        const int64_t moves = (entering + threads - 1) / threads;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(chunks + moves)), dim3((unsigned)threads), 0,
+                           stream, it, (uint32_t)chunks);
+      };
+      if (it.n <= kSmallFrame) go(k_fuse_chunk<256>, 256);
+      else go(k_fuse_chunk<kThreadsLarge>, kThreadsLarge);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
     {
@@ -597,6 +593,12 @@ hipError_t launch_fuse(const Item& it, hipStream_t stream) {
   return err;
 }
 
+int64_t move_units(const Item& it) {
+  return (strips_of(it).cells + kThreadsBatch - 1) / kThreadsBatch;
+}
+int64_t chunk_units(int64_t n) {
+  return (n + kThreadsBatch * kPointsBatch - 1) / (kThreadsBatch * kPointsBatch);
+}
 int64_t zero_units(int64_t cells) { return (cells + 255) / 256; }
 int64_t var_units(int64_t cells) { return (cells + kNTv - 1) / kNTv; }
 
@@ -614,7 +616,7 @@ hipError_t launch_fuse_batch(const Batch* d_batch, const int grid[5], hipStream_
   }
   {
     TimedLaunch tl("k_fuse_chunk_b", stream);
-    hipLaunchKernelGGL(k_fuse_chunk_b, dim3(grid_chunk), dim3(kNT1), 0, stream, d_batch);
+    hipLaunchKernelGGL(k_fuse_chunk_b, dim3(grid_chunk), dim3(kThreadsBatch), 0, stream, d_batch);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;

@@ -35,12 +35,17 @@ void fuse_fixed_shifts(const Consts& c, const Pose32& P, int64_t n, int* fxw, in
 // count_cells: cells of the per-cell point counts of the wall/edge rule (0:
 // none); the fusion's only scratch.  Sets out->count.
 size_t fuse_scratch_layout(int64_t count_cells, char* base, FuseScratch* out);
-// Runs the time variance pass even when it.n == 0.
+// Runs the time variance pass even when it.n == 0.  With points, also resets the
+// cells of the item's move (it.sx, it.sy).
 hipError_t launch_fuse(const Item& it, hipStream_t stream);
-// Work units of the batched count zeroing and per-cell variance stages.
+// Work units of the batched stages: entering cells of a move and points of pass
+// 1 (one launch takes both), count zeroing, per-cell variances.
+int64_t move_units(const Item& it);
+int64_t chunk_units(int64_t n);
 int64_t zero_units(int64_t cells);
 int64_t var_units(int64_t cells);
-// grid: zero, count, chunk, tile, variance; a zero grid skips its stage.
+// grid: zero, count, chunk (with the moves), tile, variance; a zero grid skips
+// its stage.
 hipError_t launch_fuse_batch(const Batch* d_batch, const int grid[5], hipStream_t stream);
 
 // ---------------------------------------------------------------- clearing
@@ -54,8 +59,6 @@ hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_mar
                               hipStream_t stream);
 
 // --------------------------------------------------------------- per cell
-// Threads' worth of work of the move: the cells that enter the map.
-int64_t move_units(const Item& it);
 int64_t cells_units(int nx, int ny);
 // Fills L with the prior and zeroes ctl[0..nctl).
 hipError_t launch_fill_prior(const Consts& c, const Layers& L, uint32_t* ctl, int nctl,
@@ -77,7 +80,6 @@ hipError_t launch_overlap(const OverlapArgs& a, hipStream_t stream);
 hipError_t launch_normals(const Item& it, hipStream_t stream);
 hipError_t launch_trav(const Item& it, hipStream_t stream);
 hipError_t launch_normals_trav(const Item& it, hipStream_t stream);
-hipError_t launch_move_batch(const Batch* d_batch, int grid, hipStream_t stream);
 hipError_t launch_cells_batch(const Batch* d_batch, int grid, hipStream_t stream);
 
 // ---------------------------------------------------------------- filters
