@@ -142,16 +142,6 @@ int tiles_of(const emx_params& p) { return tiles_x_of(p.nx) * tiles_y_of(p.ny); 
 
 int64_t ctl_words(const emx_params& p) { return tiles_of(p); }
 
-// A persistent grid of per_cu workgroups per compute unit of the current device.
-int persistent_grid(int per_cu) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0)
-    cus = 256;
-  return per_cu * cus;
-}
-
 bool center_cell(double c, double r, int64_t* out) {
   const double q = floor(c / r);
   if (!isfinite(q) || fabs(q) > 1073741824.0) return false;

@@ -12,10 +12,8 @@ namespace emx {
 // word per tile, zero between calls).
 int64_t ctl_words(const emx_params& p);
 
-// Clearing segment length behind emx_scratch_bytes, and the batched march's
-// default workgroups per compute unit.
+// Clearing segment length behind emx_scratch_bytes.
 constexpr int kDefaultSeg = 16;
-constexpr int kMarchPerCU = 16;
 
 emx_status fail(emx_status code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 emx_status hip_fail(hipError_t e, const char* what);
@@ -26,7 +24,6 @@ Consts make_consts(const emx_params& p);
 size_t set_layout(const emx_params& p, char* base, Layers* L);
 size_t clr_bytes(const emx_params& p);  // the per-map clearing record array
 int tiles_of(const emx_params& p);
-int persistent_grid(int per_cu);
 bool center_cell(double c, double r, int64_t* out);
 
 }  // namespace emx
