@@ -1,12 +1,9 @@
 // Per-cell passes: prior fill, robot-centric move (alone; before a fusion it
 // runs in that launch), 3x3 normals, conv traversability.
 //
-// The stencils (normals, traversability) stage a 66 x 18 halo tile of heights
-// and validity in LDS.  Each 256-thread workgroup then produces a 64 x 16
-// output tile, four cells per thread (a 400 x 400 map: 7 x 25 = 175 tiles).
-// The halo makes each height read about 1.16 times, the repeats mostly from
-// the L2 that the neighbouring tile shares (see the unit order below).
-// The batched launch computes normals and traversability from one staged tile.
+// The stencils (normals, traversability) work in registers: a wave holds a strip
+// of rows, one column per lane (see "stencil tile").  The batched launch computes
+// both from one set of loads.
 #include "emx_kernels.h"
 
 namespace emx {
@@ -96,76 +93,52 @@ __global__ __launch_bounds__(kNTf) void k_overlap(OverlapArgs a) {
 }
 
 // ---------------------------------------------------------------- stencil tile
-// Output tiles of 64 x 16 cells, four per thread.  Each row of the halo tile is
-// read by one wave: lane l takes column x0 + l (one 256-byte load of heights
-// and one 64-byte load of validity per row), two lanes take the halo columns.
-constexpr int kSW = 64;            // output tile width (one wave per row)
-constexpr int kSH = 16;            // output tile height
-constexpr int kHW = kSW + 2;       // halo tile
-constexpr int kHH = kSH + 2;
-constexpr int kSWLog = 6;
-constexpr int kSHLog = 4;
+// A wave takes kRows rows of 62 cells: its lanes are the columns x0 - 1 .. x0 +
+// 62, so the neighbours of lanes 1..62 lie in the lanes beside them (one DPP
+// move each) and nothing is staged in LDS.  Every load of the kRows + 2 rows of
+// heights and validity is issued at once, a cell's window is valid where three
+// rows' validity masks and their shifts by a lane agree (a few scalar
+// instructions a row), and the filter's weights are scalar operands.  The four
+// waves of a workgroup lie below each other, so a halo row is in the first-level
+// cache of its other user.
+// What bounds it: the bytes on large maps (1533 x 1277 cells: 13.7 -> 9.9 us, 4.2
+// TB/s of its 21 bytes a cell), the one round trip on small ones (400 x 400: 8.6 ->
+// 4.4 us), in a batch both (16 maps, 6.2M cells: 55 -> 38 us).  Before, a 66 x 18
+// tile in LDS took five dependent rounds of loads per wave and 89 LDS reads of
+// weights per cell.
+constexpr int kSW = 62;            // columns of a tile
+// Rows of a wave.  A map alone: two, for more waves in flight (128 x 128: 4.2
+// against 5.1 us with four; 1533 x 1277: 9.9 against 10.6; 2000 x 2000: 14.8
+// against 15.3).  A batch: four, which halve the fixed part of a unit (16 maps:
+// 38 against 48 us).
+constexpr int kRowsPlain = 2;
+constexpr int kRowsBatch = 4;
 
-struct HaloTile {
-  float h[kHH][kHW + 1];
-  uint8_t ok[kHH][kHW + 2];
+constexpr int tile_rows(int rows) { return rows * (kNTf / 64); }  // of a workgroup
+
+// The value of the lane below (left column) or above (right column).
+__device__ __forceinline__ float from_left(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138 /* wave_shr:1 */, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float from_right(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130 /* wave_shl:1 */, 0xf, 0xf, false));
+}
+
+// A row of heights: the lane's column and its neighbours.
+struct Row {
+  float l, m, r;
 };
 
-__device__ __forceinline__ void load_halo(HaloTile& s, const Consts& c, const Layers& L, int x0,
-                                          int y0) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int ly = wave; ly < kHH; ly += kNTf / 64) {
-    const int gy = y0 - 1 + ly;
-    const bool row = gy >= 0 && gy < c.ny;
-    {  // body column lx = lane + 1
-      const int gx = x0 + lane;
-      float hv = 0.0f;
-      uint8_t ok = 0;
-      if (row && gx < c.nx) {
-        const int64_t o = pcell(c, gx, gy);
-        ok = L.valid[o];
-        hv = L.h[o];
-      }
-      s.h[ly][lane + 1] = hv;
-      s.ok[ly][lane + 1] = ok;
-    }
-    if (lane < 2) {  // halo columns lx = 0 and lx = kSW + 1
-      const int lx = lane == 0 ? 0 : kSW + 1;
-      const int gx = x0 - 1 + lx;
-      float hv = 0.0f;
-      uint8_t ok = 0;
-      if (row && gx >= 0 && gx < c.nx) {
-        const int64_t o = pcell(c, gx, gy);
-        ok = L.valid[o];
-        hv = L.h[o];
-      }
-      s.h[ly][lx] = hv;
-      s.ok[ly][lx] = ok;
-    }
-  }
-}
-
-// the cell at halo position (lx, ly) is interior and its 3x3 window is valid
-__device__ __forceinline__ bool window_ok(const HaloTile& s, const Consts& c, int gx, int gy,
-                                          int lx, int ly) {
-  if (gx < 1 || gy < 1 || gx > c.nx - 2 || gy > c.ny - 2) return false;
-  bool ok = true;
-#pragma unroll
-  for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-    for (int dx = -1; dx <= 1; ++dx) ok = ok && (s.ok[ly + dy][lx + dx] != 0);
-  return ok;
-}
-
-__device__ __forceinline__ void normal_at(const HaloTile& s, int lx, int ly, float inv6r,
+__device__ __forceinline__ void normal_at(const Row& a, const Row& b, const Row& c, float inv6r,
                                           float& nx, float& ny, float& nz) {
-  const float dxm = s.h[ly - 1][lx + 1] - s.h[ly - 1][lx - 1];
-  const float dx0 = s.h[ly][lx + 1] - s.h[ly][lx - 1];
-  const float dxp = s.h[ly + 1][lx + 1] - s.h[ly + 1][lx - 1];
-  const float dym = s.h[ly + 1][lx - 1] - s.h[ly - 1][lx - 1];
-  const float dy0 = s.h[ly + 1][lx] - s.h[ly - 1][lx];
-  const float dyp = s.h[ly + 1][lx + 1] - s.h[ly - 1][lx + 1];
+  const float dxm = a.r - a.l;
+  const float dx0 = b.r - b.l;
+  const float dxp = c.r - c.l;
+  const float dym = c.l - a.l;
+  const float dy0 = c.m - a.m;
+  const float dyp = c.r - a.r;
   const float gxv = ((dxm + dx0) + dxp) * inv6r;
   const float gyv = ((dym + dy0) + dyp) * inv6r;
   const float q = (gxv * gxv + gyv * gyv) + 1.0f;
@@ -175,54 +148,93 @@ __device__ __forceinline__ void normal_at(const HaloTile& s, int lx, int ly, flo
   nz = inv;
 }
 
-__device__ __forceinline__ float trav_at(const HaloTile& s, int lx, int ly, const float* sw) {
-  float win[9];
-#pragma unroll
-  for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx) win[dy * 3 + dx] = s.h[ly - 1 + dy][lx - 1 + dx];
-  float T = sw[88];
-#pragma unroll
-  for (int ch = 0; ch < 8; ++ch) {
-    float acc = sw[72 + ch];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc = fmaf(sw[ch * 9 + k], win[k], acc);
-    T = fmaf(sw[80 + ch], fmaxf(acc, 0.0f), T);
-  }
-  return T;
-}
+// The weights through the scalar cache: uniform, and written by no kernel of
+// this launch.
+typedef const __attribute__((address_space(4))) float* Weights;
 
 // Normals and/or traversability of one output tile.
+template <int kRows>
 __device__ __forceinline__ void cells_body(const Item& it, int64_t unit, bool do_n, bool do_t) {
-  __shared__ HaloTile s;
-  __shared__ float sw[89];
-  const int ux = blocks_of(it.c.nx, kSWLog);
-  const int x0 = (int)(unit % ux) * kSW;
-  const int y0 = (int)(unit / ux) * kSH;
-  if (do_t && threadIdx.x < 89) sw[threadIdx.x] = it.w[threadIdx.x];
-  load_halo(s, it.c, it.L, x0, y0);
-  __syncthreads();
-  const int tx = threadIdx.x & (kSW - 1);
-  const int ty0 = threadIdx.x / kSW;
-  const float qnan = __builtin_nanf("");
+  const Consts& c = it.c;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ux = (c.nx + kSW - 1) / kSW;
+  const int uy = (int)(unit / ux);
+  const int gx = (int)(unit - (int64_t)uy * ux) * kSW - 1 + lane;
+  const int y0 = uy * tile_rows(kRows) + wave * kRows;
+  if (y0 >= c.ny) return;
+  const bool col = gx >= 0 && gx < c.nx;
+  int px = gx + c.ox;
+  px = col ? px - (px >= c.nx ? c.nx : 0) : 0;
+  // physical cells of rows y0 - 1 .. y0 + kRows; a row outside the map reads row 0
+  uint32_t o[kRows + 2];
+  float h[kRows + 2];
+  uint8_t ok[kRows + 2];
 #pragma unroll
-  for (int j = 0; j < kSH / (kNTf / kSW); ++j) {
-    const int ty = ty0 + j * (kNTf / kSW);
-    const int gx = x0 + tx;
-    const int gy = y0 + ty;
-    if (gx >= it.c.nx || gy >= it.c.ny) continue;
-    const int lx = tx + 1;
-    const int ly = ty + 1;
-    const bool ok = window_ok(s, it.c, gx, gy, lx, ly);
-    const int64_t o = pcell(it.c, gx, gy);
-    if (do_n) {
+  for (int r = 0; r < kRows + 2; ++r) {
+    const int gy = y0 - 1 + r;
+    int py = gy + c.oy;
+    py = gy >= 0 && gy < c.ny ? py - (py >= c.ny ? c.ny : 0) : 0;
+    o[r] = (uint32_t)py * (uint32_t)c.nx + (uint32_t)px;
+    h[r] = it.L.h[o[r]];
+    ok[r] = it.L.valid[o[r]];
+  }
+  uint64_t m[kRows + 2];  // the row's valid cells whose neighbours in the row are valid
+#pragma unroll
+  for (int r = 0; r < kRows + 2; ++r) {
+    const int gy = y0 - 1 + r;
+    const uint64_t v = gy >= 0 && gy < c.ny ? __ballot(col && ok[r] != 0) : 0ull;
+    m[r] = v & (v << 1) & (v >> 1);
+  }
+  Row row[kRows + 2];
+#pragma unroll
+  for (int r = 0; r < kRows + 2; ++r) row[r] = Row{from_left(h[r]), h[r], from_right(h[r])};
+  const bool out = col && lane >= 1 && lane <= kSW;
+  const float qnan = __builtin_nanf("");
+  bool win[kRows];
+  uint64_t any = 0;
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    const uint64_t w = m[j] & m[j + 1] & m[j + 2];
+    any |= w;
+    win[j] = (w >> lane) & 1u;
+  }
+  if (do_n) {
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
       float nx = qnan, ny = qnan, nz = qnan;
-      if (ok) normal_at(s, lx, ly, it.c.inv6r, nx, ny, nz);
-      it.L.nx[o] = nx;
-      it.L.ny[o] = ny;
-      it.L.nz[o] = nz;
+      if (win[j]) normal_at(row[j], row[j + 1], row[j + 2], c.inv6r, nx, ny, nz);
+      if (out && y0 + j < c.ny) {
+        it.L.nx[o[j + 1]] = nx;
+        it.L.ny[o[j + 1]] = ny;
+        it.L.nz[o[j + 1]] = nz;
+      }
     }
-    if (do_t) it.L.trav[o] = ok ? trav_at(s, lx, ly, sw) : qnan;
+  }
+  if (do_t) {
+    const Weights w = (Weights)(uintptr_t)it.w;
+    float T[kRows];
+    if (any) {  // some window of the wave is valid
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) T[j] = w[88];
+#pragma unroll
+      for (int ch = 0; ch < 8; ++ch) {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) {
+          float acc = w[72 + ch];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            acc = fmaf(w[ch * 9 + 3 * k], row[j + k].l, acc);
+            acc = fmaf(w[ch * 9 + 3 * k + 1], row[j + k].m, acc);
+            acc = fmaf(w[ch * 9 + 3 * k + 2], row[j + k].r, acc);
+          }
+          T[j] = fmaf(w[80 + ch], fmaxf(acc, 0.0f), T[j]);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j)
+      if (out && y0 + j < c.ny) it.L.trav[o[j + 1]] = win[j] ? T[j] : qnan;
   }
 }
 
@@ -231,15 +243,8 @@ __global__ __launch_bounds__(kNTf) void k_move(Item it) {
   move_body<kNTf>(it, blockIdx.x);
 }
 // One workgroup per output tile, each XCD taking a contiguous range of tiles.
-__global__ __launch_bounds__(kNTf) void k_normals(Item it) {
-  cells_body(it, xcd_unit(blockIdx.x, gridDim.x), true, false);
-}
-__global__ __launch_bounds__(kNTf) void k_trav(Item it) {
-  cells_body(it, xcd_unit(blockIdx.x, gridDim.x), false, true);
-}
-// Both from one staged tile: the heights are read once.
-__global__ __launch_bounds__(kNTf) void k_normals_trav(Item it) {
-  cells_body(it, xcd_unit(blockIdx.x, gridDim.x), true, true);
+__global__ __launch_bounds__(kNTf) void k_cells(Item it, bool do_n, bool do_t) {
+  cells_body<kRowsPlain>(it, xcd_unit(blockIdx.x, gridDim.x), do_n, do_t);
 }
 
 // Each XCD takes a contiguous range of the batch's tiles (xcd_unit_k).
@@ -251,17 +256,17 @@ __global__ __launch_bounds__(kNTf) void k_cells_b(const Batch* bt) {
     int64_t unit;
     const int i = units.find(w, unit);
     const Item& it = bt->items[i];
-    cells_body(it, unit, (it.stages & kStageNormals) != 0,
-               (it.stages & kStageTrav) != 0);
-    __syncthreads();
+    cells_body<kRowsBatch>(it, unit, (it.stages & kStageNormals) != 0,
+                          (it.stages & kStageTrav) != 0);
   }
 }
 
 }  // namespace
 
-int64_t cells_units(int nx, int ny) {
-  return (int64_t)blocks_of(nx, kSWLog) * blocks_of(ny, kSHLog);
+static int64_t cells_tiles(int nx, int ny, int rows) {
+  return (int64_t)((nx + kSW - 1) / kSW) * ((ny + tile_rows(rows) - 1) / tile_rows(rows));
 }
+int64_t cells_units(int nx, int ny) { return cells_tiles(nx, ny, kRowsBatch); }
 
 hipError_t launch_fill_prior(const Consts& c, const Layers& L, uint32_t* ctl, int nctl,
                              hipStream_t stream) {
@@ -293,25 +298,25 @@ hipError_t launch_move(const Item& it, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_normals(const Item& it, hipStream_t stream) {
-  TimedLaunch tl("k_normals", stream);
-  hipLaunchKernelGGL(k_normals, dim3((unsigned)cells_units(it.c.nx, it.c.ny)), dim3(kNTf), 0,
-                     stream, it);
+static hipError_t launch_cells(const Item& it, const char* name, bool do_n, bool do_t,
+                               hipStream_t stream) {
+  TimedLaunch tl(name, stream);
+  const int nx = it.c.nx, ny = it.c.ny;
+  hipLaunchKernelGGL(k_cells, dim3((unsigned)cells_tiles(nx, ny, kRowsPlain)), dim3(kNTf), 0,
+                     stream, it, do_n, do_t);
   return hipGetLastError();
+}
+
+hipError_t launch_normals(const Item& it, hipStream_t stream) {
+  return launch_cells(it, "k_normals", true, false, stream);
 }
 
 hipError_t launch_trav(const Item& it, hipStream_t stream) {
-  TimedLaunch tl("k_trav", stream);
-  hipLaunchKernelGGL(k_trav, dim3((unsigned)cells_units(it.c.nx, it.c.ny)), dim3(kNTf), 0, stream,
-                     it);
-  return hipGetLastError();
+  return launch_cells(it, "k_trav", false, true, stream);
 }
 
 hipError_t launch_normals_trav(const Item& it, hipStream_t stream) {
-  TimedLaunch tl("k_normals_trav", stream);
-  hipLaunchKernelGGL(k_normals_trav, dim3((unsigned)cells_units(it.c.nx, it.c.ny)), dim3(kNTf), 0,
-                     stream, it);
-  return hipGetLastError();
+  return launch_cells(it, "k_normals_trav", true, true, stream);
 }
 
 hipError_t launch_cells_batch(const Batch* d_batch, int grid, hipStream_t stream) {
