@@ -37,7 +37,10 @@ def aligned_empty(nbytes: int, device, align: int = 256) -> torch.Tensor:
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # the current stream's handle, without a Stream object around it
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(
+        torch.cuda.current_device() if index is None else index)
 
 
 def _f32(t: torch.Tensor, device) -> torch.Tensor:
@@ -61,6 +64,7 @@ class ElevationMap:
         self._state = aligned_empty(nbytes, self.device)
         self._scratch = None
         self._scratch_bytes = 0
+        self._scratch_points = -1      # frames of up to this many points fit it
         self.handle = _emx.init_map(self.p, float(cx), float(cy), int(t0_ms),
                                     self._state.data_ptr(), nbytes, _stream(self.device))
 
@@ -84,10 +88,14 @@ class ElevationMap:
         return _emx.make_frame(x.data_ptr(), y.data_ptr(), z.data_ptr(), n, pose, t_ms), n
 
     def scratch(self, n: int) -> torch.Tensor:
+        if n <= self._scratch_points:
+            return self._scratch
         need = max(_emx.scratch_bytes(self.p, n), _emx.drift_scratch_bytes(n))
         if self._scratch is None or self._scratch_bytes < need:
             self._scratch = aligned_empty(need, self.device)
             self._scratch_bytes = need
+        if need > 0:                   # the sizes grow with n
+            self._scratch_points = n
         return self._scratch
 
     def move_map(self, cx: float, cy: float):

@@ -50,6 +50,10 @@ class Frame(Structure):
                 ("pose", c_double * 12), ("t_ms", c_int64)]
 
 
+_FRAME_HEAD, _FRAME_TAIL = bytes(Frame.pose.offset), bytes(ctypes.sizeof(Frame)
+                                                           - Frame.pose.offset - 96)
+
+
 class BatchItem(Structure):
     _fields_ = [("map", c_void_p), ("frame", Frame), ("cx", c_double), ("cy", c_double),
                 ("d_weights", c_void_p), ("d_out_cell", c_void_p), ("d_out_accept", c_void_p),
@@ -171,12 +175,11 @@ def make_params(d: dict) -> Params:
 
 
 def make_frame(x_ptr: int, y_ptr: int, z_ptr: int, n: int, pose, t_ms: int) -> Frame:
-    f = Frame()
-    f.x, f.y, f.z = c_void_p(x_ptr), c_void_p(y_ptr), c_void_p(z_ptr)
-    f.n = int(n)
-    P = np.ascontiguousarray(np.asarray(pose, dtype=np.float64).reshape(12))
-    for k in range(12):
-        f.pose[k] = float(P[k])
+    # the pose as one copy of its bytes: twelve element stores took half the call
+    f = Frame.from_buffer_copy(
+        _FRAME_HEAD + np.asarray(pose, dtype=np.float64).reshape(12).tobytes() + _FRAME_TAIL)
+    f.x, f.y, f.z = x_ptr, y_ptr, z_ptr
+    f.n = n
     f.t_ms = int(t_ms)
     return f
 
@@ -216,9 +219,8 @@ def move_map(h: int, cx: float, cy: float, stream: int):
 
 def fuse_points(h: int, f: Frame, d_scratch: int, nbytes: int, d_out_cell: int,
                 d_out_accept: int, stream: int):
-    check(lib().emx_fuse_points(c_void_p(h), byref(f), c_void_p(d_scratch), nbytes,
-                                c_void_p(d_out_cell or None), c_void_p(d_out_accept or None),
-                                c_void_p(stream)))
+    check(lib().emx_fuse_points(h, byref(f), d_scratch, nbytes, d_out_cell or None,
+                                d_out_accept or None, stream))
 
 
 def noalloc_scratch_limit() -> int:
@@ -269,15 +271,14 @@ def compensate_drift(h: int, f: Frame, trav_min: float, d_scratch: int, nbytes: 
 
 def move_fuse_points(h: int, cx: float, cy: float, f: Frame, d_scratch: int, nbytes: int,
                      d_out_cell: int, d_out_accept: int, stream: int):
-    check(lib().emx_move_fuse_points(c_void_p(h), float(cx), float(cy), byref(f),
-                                     c_void_p(d_scratch), nbytes, c_void_p(d_out_cell or None),
-                                     c_void_p(d_out_accept or None), c_void_p(stream)))
+    check(lib().emx_move_fuse_points(h, float(cx), float(cy), byref(f), d_scratch, nbytes,
+                                     d_out_cell or None, d_out_accept or None, stream))
 
 
 def clear_visibility(h: int, f: Frame, d_scratch: int, nbytes: int, d_out_cleared: int,
                      stream: int):
-    check(lib().emx_clear_visibility(c_void_p(h), byref(f), c_void_p(d_scratch or None), nbytes,
-                                     c_void_p(d_out_cleared or None), c_void_p(stream)))
+    check(lib().emx_clear_visibility(h, byref(f), d_scratch or None, nbytes,
+                                     d_out_cleared or None, stream))
 
 
 def compute_normals(h: int, stream: int):
@@ -289,7 +290,7 @@ def traversability(h: int, d_weights: int, stream: int):
 
 
 def normals_traversability(h: int, d_weights: int, stream: int):
-    check(lib().emx_normals_traversability(c_void_p(h), c_void_p(d_weights), c_void_p(stream)))
+    check(lib().emx_normals_traversability(h, d_weights, stream))
 
 
 def layer(h: int, layer_id: int) -> int:
