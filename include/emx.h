@@ -139,9 +139,8 @@ emx_status emx_params_check(const emx_params* params);
 /* Device bytes of one map's state: one set of layers stored as a ring (see
  * emx_layer; with upper_bound = 1 it also holds the upper bound layer), the
  * fusion's fixed-point sums (32 bytes per cell, zero between calls), 8 bytes
- * of clearing scratch per cell and a small control block (the clearing queue
- * counters and one word per 32x16-cell fusion tile).  Returns 0 for invalid
- * parameters. */
+ * of clearing records per cell, the clearing's block maxima and one word per
+ * 32x8-cell fusion tile.  Returns 0 for invalid parameters. */
 size_t emx_state_bytes(const emx_params* params);
 
 /* Device scratch bytes emx_fuse_points and emx_clear_visibility need for

@@ -20,10 +20,10 @@ namespace emx {
 // Points per fusion work unit (one workgroup of pass 1, the wall counts and
 // the drift partials).
 constexpr int kChunk = 1024;
-// Map tiles of 32 x 16 cells: pass 2 of the fusion visits only the tiles the
-// frame touched (a 400 x 400 map has 13 x 25 = 325 tiles).
+// Map tiles of 32 x 8 cells: pass 2 of the fusion visits only the tiles the
+// frame touched (a 400 x 400 map has 13 x 50 = 650 tiles).
 constexpr int kTileLogX = 5;
-constexpr int kTileLogY = 4;
+constexpr int kTileLogY = 3;
 constexpr int kTileW = 1 << kTileLogX;
 constexpr int kTileH = 1 << kTileLogY;
 constexpr int kTileCells = kTileW * kTileH;

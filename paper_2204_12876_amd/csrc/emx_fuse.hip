@@ -29,9 +29,9 @@
 //   - Where the call moves the map first, further workgroups of the same launch
 //     reset the entering cells, and points in them take the prior (a launch of
 //     its own took 3 us of every frame).
-// Pass 2, tile body: per 32 x 16-cell tile of the physical layout, a
-// workgroup with one thread per cell (plain calls) or one wave with eight
-// cells per lane (batches).  An unflagged tile returns after one load;
+// Pass 2, tile body: per 32 x 8-cell tile of the physical layout, a workgroup
+// with one thread per cell (plain calls) or one wave with four cells per lane
+// (batches).  An unflagged tile returns after one load;
 // otherwise the flag is reset, and each cell with a nonzero sum converts its
 // sums back to floating point, applies the information-form update once and
 // resets its words to zero for the next call.
@@ -238,8 +238,7 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
 constexpr int kNT2 = kTileCells;               // plain pass 2: one thread per cell of the tile
 constexpr int kNT2b = 256;                     // batched pass 2: one wave per tile
 constexpr int kTilesPerGroup = kNT2b / 64;
-constexpr int kCellsPerLane = kTileCells / 64;  // 8: lane l owns cells l, l + 64, ...
-constexpr int kHalf = kCellsPerLane / 2;
+constexpr int kCellsPerLane = kTileCells / 64;  // 4: lane l owns cells l, l + 64, ...
 
 // Information-form update of physical cell `cell` from its sums (Σw's words
 // whi, wlo given, not both zero); the sums are reset to zero.
@@ -289,10 +288,12 @@ __device__ __forceinline__ void tile_body_group(const Item& it, int64_t t) {
 }
 
 // Tile t, by one wave: lane l takes cells l + 64 i of the tile (two rows of 32
-// per step), in two halves of kHalf cells, each half's loads issued together.
-// The batched form: a batch holds tens of thousands of tiles, many untouched,
-// so a workgroup's waves take one tile each and an untouched tile costs one
-// wave one load.  The same update_cell as the plain form: the same bits.
+// per step), their loads issued together.  The batched form: a batch holds tens
+// of thousands of tiles, many untouched, so a workgroup's waves take one tile
+// each and an untouched tile costs one wave one load.  The same update_cell as
+// the plain form: the same bits.  (Tiles of 32 x 16 cells took a wave two rounds
+// of loads: 17.7 against 13.9 us for a server's batch of 8 maps, 24.1 against 21.8 us
+// for 16 maps.)
 __device__ __forceinline__ void tile_body_wave(const Item& it, int64_t t) {
   const int lane = threadIdx.x & 63;
   if (it.fs.tcnt[t] == 0u) return;  // wave-uniform: the frame added to no cell of the tile
@@ -301,51 +302,48 @@ __device__ __forceinline__ void tile_body_wave(const Item& it, int64_t t) {
   const int tx = (int)(t % it.tiles_x);
   const int ty = (int)(t / it.tiles_x);
   const int64_t fs = it.L.fxs;
+  int64_t cell[kCellsPerLane];
+  bool in[kCellsPerLane];
+  int64_t whi[kCellsPerLane];
+  uint64_t wlo[kCellsPerLane];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    int64_t cell[kHalf];
-    bool in[kHalf];
-    int64_t whi[kHalf];
-    uint64_t wlo[kHalf];
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-      const int c = lane + 64 * (half * kHalf + i);
-      // the cell, physical (tiles cover the ring layout as stored)
-      const int px = (tx << kTileLogX) + (c & (kTileW - 1));
-      const int py = (ty << kTileLogY) + (c >> kTileLogX);
-      in[i] = px < it.c.nx && py < it.c.ny;
-      cell[i] = in[i] ? (int64_t)py * it.c.nx + px : 0;
-      whi[i] = 0;
-      wlo[i] = 0;
-      if (in[i]) {
-        whi[i] = (int64_t)it.L.fx[kFxWhi * fs + cell[i]];
-        wlo[i] = it.L.fx[kFxWlo * fs + cell[i]];
-      }
+  for (int i = 0; i < kCellsPerLane; ++i) {
+    const int c = lane + 64 * i;
+    // the cell, physical (tiles cover the ring layout as stored)
+    const int px = (tx << kTileLogX) + (c & (kTileW - 1));
+    const int py = (ty << kTileLogY) + (c >> kTileLogX);
+    in[i] = px < it.c.nx && py < it.c.ny;
+    cell[i] = in[i] ? (int64_t)py * it.c.nx + px : 0;
+    whi[i] = 0;
+    wlo[i] = 0;
+    if (in[i]) {
+      whi[i] = (int64_t)it.L.fx[kFxWhi * fs + cell[i]];
+      wlo[i] = it.L.fx[kFxWlo * fs + cell[i]];
     }
-    // cells with an accepted point (every term is positive): the rest of
-    // their sums and their prior, all loads issued before any is used
-    bool hit[kHalf];
-    int64_t zhi[kHalf];
-    uint64_t zlo[kHalf];
-    float h0[kHalf], v0[kHalf];
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-      hit[i] = in[i] && (whi[i] != 0 || wlo[i] != 0);
-      zhi[i] = 0;
-      zlo[i] = 0;
-      h0[i] = 0.0f;
-      v0[i] = 1.0f;
-      if (hit[i]) {
-        zhi[i] = (int64_t)it.L.fx[kFxZhi * fs + cell[i]];
-        zlo[i] = it.L.fx[kFxZlo * fs + cell[i]];
-        h0[i] = it.L.h[cell[i]];
-        v0[i] = it.L.v[cell[i]];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i)
-      if (hit[i]) update_cell(it, cell[i], whi[i], wlo[i], zhi[i], zlo[i], h0[i], v0[i]);
   }
+  // cells with an accepted point (every term is positive): the rest of
+  // their sums and their prior, all loads issued before any is used
+  bool hit[kCellsPerLane];
+  int64_t zhi[kCellsPerLane];
+  uint64_t zlo[kCellsPerLane];
+  float h0[kCellsPerLane], v0[kCellsPerLane];
+#pragma unroll
+  for (int i = 0; i < kCellsPerLane; ++i) {
+    hit[i] = in[i] && (whi[i] != 0 || wlo[i] != 0);
+    zhi[i] = 0;
+    zlo[i] = 0;
+    h0[i] = 0.0f;
+    v0[i] = 1.0f;
+    if (hit[i]) {
+      zhi[i] = (int64_t)it.L.fx[kFxZhi * fs + cell[i]];
+      zlo[i] = it.L.fx[kFxZlo * fs + cell[i]];
+      h0[i] = it.L.h[cell[i]];
+      v0[i] = it.L.v[cell[i]];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kCellsPerLane; ++i)
+    if (hit[i]) update_cell(it, cell[i], whi[i], wlo[i], zhi[i], zlo[i], h0[i], v0[i]);
 }
 
 // ------------------------------------------------------- wall rule: counts
