@@ -5,23 +5,30 @@
 // A union-find over the grid labels the regions.  Links only ever point from
 // a larger cell index to a smaller one (an integer atomic minimum), so there
 // are no cycles and each region ends with its smallest cell as the root,
-// whatever the order of the unions.  Four per-cell launches:
+// whatever the order of the unions.  Four launches, all but the first on the
+// scratch arrays alone, in logical cell order:
 //   1. local: per 32 x 32 tile, in LDS, the union of the tile's invalid cells
 //      and, per tile-local region, the minimum border height offered from
-//      inside the tile.  Writes each invalid cell's parent (its local root)
-//      and the local minimum at each local root;
-//   2. merge: invalid cells on a tile edge unite with their invalid
-//      neighbours across it, in the global parent array;
-//   3. border: local roots pass their minimum to their final root, and valid
-//      cells on a tile edge offer their height across it;
+//      inside the tile.  Writes each invalid cell's parent (its local root; -1
+//      marks a valid cell), the local minimum at each local root, and the valid
+//      cells' output;
+//   2. seams, one thread per pair of cells across a tile edge: invalid pairs
+//      unite in the global parent array, a valid cell offers its height to the
+//      local region across the edge (any cell on its chain of parents is a
+//      local root, which the next launch collects);
+//   3. collect: local roots pass their minimum to their final root;
 //   4. fill: invalid cells read their final root's minimum (NaN if none).
 // Minima are integer atomics over an order-preserving key of the float, so
 // the output is deterministic.
+// What bounds it: the four launches' chains of dependent loads.  Measured on a
+// 400 x 400 map, before and after: local 21.3 -> 9.9 us (a wave's offers were
+// reduced region by region), seams 10.1 -> 10.4 us with the offers across the
+// edges in them, collect 12.1 -> 4.7 us (it made those offers, and followed every
+// chain through the atomics path), fill 3.9 us.
 //
-// Smoothing (box, Gaussian, median) works on 16 x 16 output tiles.  A
-// workgroup stages the tile and its mirrored halo in LDS; box and Gaussian
-// then run a pass along x into LDS and a pass along y to the output, the
-// median selects from the staged window.
+// Smoothing.  Box and Gaussian work on 16 x 16 output tiles: a workgroup stages
+// the tile and its mirrored halo in LDS and runs a pass along x into LDS and a
+// pass along y to the output.  The median works in registers, a column per lane.
 #include "emx_kernels.h"
 
 namespace emx {
@@ -44,7 +51,7 @@ constexpr uint32_t kNoKey = 0xffffffffu;
 struct InpaintArgs {
   Consts c;
   Layers L;
-  int32_t* parent;  // [cells] parent chain of invalid cells (global indices)
+  int32_t* parent;  // [cells] parent chain of invalid cells (global indices); -1: valid
   uint32_t* best;   // [cells] at local roots: key of the smallest border height
   float* out;       // [cells]
   int tiles_x;
@@ -53,44 +60,55 @@ struct InpaintArgs {
 constexpr int kIT = 32;                // inpainting tile side
 constexpr int kNTl = kIT * kIT;        // one thread per tile cell
 
+// Root of cell x once no union runs any more.
 __device__ __forceinline__ int32_t find_root(const int32_t* parent, int32_t x) {
-  // parents change under concurrent unions: read them through the atomics path
-  int32_t p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
+  int32_t p = parent[x];
   while (p != x) {
     x = p;
-    p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
+    p = parent[x];
   }
   return x;
 }
 
-// find_root that also halves the path: each visited cell is pointed at its
-// grandparent.  The write is an atomic minimum, so it can never undo a link
-// made meanwhile (parents only decrease, and stay ancestors).
-__device__ __forceinline__ int32_t find_halve(int32_t* parent, int32_t x) {
-  int32_t p = __atomic_load_n(parent + x, __ATOMIC_RELAXED);
-  while (p != x) {
-    const int32_t g = __atomic_load_n(parent + p, __ATOMIC_RELAXED);
-    if (g != p) atomicMin(parent + x, g);
-    x = p;
-    p = g;
-  }
-  return x;
+// A parent while unions run: past the L2, which is not shared by all the chip.
+__device__ __forceinline__ int32_t load_parent(const int32_t* parent, int32_t x) {
+  return __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Unites the regions of cells a and b.  Both chains of parents are followed at
+// the same time, one step of each to a round trip, and halved on the way: each
+// visited cell is pointed at its grandparent.  The write is an atomic minimum,
+// so it can never undo a link made meanwhile (parents only decrease, and stay
+// ancestors).
 __device__ __forceinline__ void unite(int32_t* parent, int32_t a, int32_t b) {
-  while (true) {
-    a = find_halve(parent, a);
-    b = find_halve(parent, b);
-    if (a == b) return;
-    if (a < b) {
-      const int32_t t = a;
-      a = b;
-      b = t;
+  int32_t pa = load_parent(parent, a), pb = load_parent(parent, b);
+  while (a != b) {
+    const bool ra = pa == a, rb = pb == b;
+    if (ra && rb) {
+      if (a < b) {
+        const int32_t t = a;
+        a = b;
+        b = t;
+      }
+      // link root a below b; if a is no longer a root, follow its new parent
+      const int32_t old = atomicMin(parent + a, b);
+      if (old == a) return;
+      a = old;
+      pa = load_parent(parent, a);
+      pb = load_parent(parent, b);
+      continue;
     }
-    // link root a below b; if a is no longer a root, follow its new parent
-    const int32_t old = atomicMin(parent + a, b);
-    if (old == a) return;
-    a = old;
+    const int32_t ga = load_parent(parent, pa), gb = load_parent(parent, pb);
+    if (!ra) {
+      if (ga != pa) atomicMin(parent + a, ga);
+      a = pa;
+    }
+    if (!rb) {
+      if (gb != pb) atomicMin(parent + b, gb);
+      b = pb;
+    }
+    pa = ga;
+    pb = gb;
   }
 }
 
@@ -121,14 +139,6 @@ __device__ __forceinline__ void lds_unite(int* par, int a, int b) {
   }
 }
 
-// Physical cell of logical cell i (the map's ring layout).  The union-find
-// works on logical cells; only the map's layers are read through the ring.
-__device__ __forceinline__ int64_t lphys(const Consts& c, int64_t i) {
-  const int iy = (int)(i / c.nx);
-  const int ix = (int)(i - (int64_t)iy * c.nx);
-  return pcell(c, ix, iy);
-}
-
 __global__ __launch_bounds__(kNTl) void k_inp_local(InpaintArgs a) {
   __shared__ int s_par[kNTl];
   __shared__ uint32_t s_best[kNTl];
@@ -142,8 +152,9 @@ __global__ __launch_bounds__(kNTl) void k_inp_local(InpaintArgs a) {
   const int gx = x0 + lx;
   const int gy = y0 + ly;
   const bool in = gx < nx && gy < ny;
-  const int64_t i = (int64_t)gy * nx + gx;
-  const bool ok = in && a.L.valid[lphys(a.c, i)];
+  const int64_t pc = in ? pcell(a.c, gx, gy) : 0;
+  const bool ok = in && a.L.valid[pc];
+  const float height = in ? a.L.h[pc] : 0.0f;
   const bool hole = in && !ok;
   // Rows first, without atomics: a hole's parent is the first cell of its
   // run of holes along the row (a tile row is half a wave: one ballot).
@@ -158,89 +169,80 @@ __global__ __launch_bounds__(kNTl) void k_inp_local(InpaintArgs a) {
   if (hole && ly > 0 && s_par[tid - kIT] >= 0 && (lx == start || s_par[tid - kIT - 1] < 0))
     lds_unite(s_par, ly * kIT + start, tid - kIT);
   __syncthreads();
-  // offers from valid cells to holes of the same tile: per direction, the
-  // lanes of a wave that offer to one region are reduced first, so that each
-  // region takes one LDS atomic per wave
-  {
-    volatile int* vp = s_par;
-    const uint32_t k = ok ? f32_key(a.L.h[lphys(a.c, i)]) : kNoKey;
-    const int nb[4] = {lx > 0 ? tid - 1 : -1, lx + 1 < kIT && gx + 1 < nx ? tid + 1 : -1,
-                       ly > 0 ? tid - kIT : -1, ly + 1 < kIT && gy + 1 < ny ? tid + kIT : -1};
+  // the roots, then each hole's own root in place of its parent
+  const int root = hole ? lds_find(s_par, tid) : -1;
+  __syncthreads();
+  s_par[tid] = root;
+  __syncthreads();
+  // valid cells offer their height to the holes beside them, each by an LDS
+  // atomic of its own (reducing a wave's offers region by region first cost
+  // seven cross-lane steps for every region that the wave met)
+  if (ok) {
+    const uint32_t k = f32_key(height);
+    const int nb[4] = {lx > 0 ? s_par[tid - 1] : -1, lx + 1 < kIT ? s_par[tid + 1] : -1,
+                       ly > 0 ? s_par[tid - kIT] : -1, ly + 1 < kIT ? s_par[tid + kIT] : -1};
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      int r = (ok && nb[d] >= 0 && vp[nb[d]] >= 0) ? lds_find(vp, nb[d]) : -1;
-      uint64_t pend = __ballot(r >= 0);
-      while (pend) {
-        const int leader = __builtin_ctzll(pend);
-        const int R = __shfl(r, leader, 64);
-        uint32_t m = r == R ? k : kNoKey;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o, 64));
-        if ((threadIdx.x & 63) == leader) atomicMin(s_best + R, m);
-        if (r == R) r = -1;
-        pend = __ballot(r >= 0);
-      }
-    }
+    for (int d = 0; d < 4; ++d)
+      if (nb[d] >= 0) atomicMin(s_best + nb[d], k);
   }
   __syncthreads();
-  if (hole) {
-    const int r = lds_find(s_par, tid);
-    a.parent[i] = (int32_t)((int64_t)(y0 + r / kIT) * nx + x0 + r % kIT);
-    a.best[i] = r == tid ? s_best[tid] : kNoKey;
-  }
+  if (!in) return;
+  const int64_t i = (int64_t)gy * nx + gx;
+  a.parent[i] = hole ? (int32_t)((int64_t)(y0 + root / kIT) * nx + x0 + root % kIT) : -1;
+  a.best[i] = root == tid ? s_best[tid] : kNoKey;
+  if (ok) a.out[i] = height;
 }
 
-__global__ __launch_bounds__(kNTi) void k_inp_merge(InpaintArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * kNTi + threadIdx.x;
-  const int nx = a.c.nx;
-  if (i >= (int64_t)nx * a.c.ny) return;
-  const int iy = (int)(i / nx);
-  const int ix = (int)(i - (int64_t)iy * nx);
-  const bool right = (ix % kIT) == kIT - 1 && ix + 1 < nx;
-  const bool down = (iy % kIT) == kIT - 1 && iy + 1 < a.c.ny;
-  if (!(right || down) || a.L.valid[lphys(a.c, i)]) return;
-  // Along an edge, hole pairs next to each other are already joined on both
-  // sides: only the first pair of each run of pairs unites.
-  if (right && !a.L.valid[lphys(a.c, i + 1)] &&
-      (iy % kIT == 0 || a.L.valid[lphys(a.c, i - nx)] || a.L.valid[lphys(a.c, i - nx + 1)]))
-    unite(a.parent, (int32_t)i, (int32_t)(i + 1));
-  if (down && !a.L.valid[lphys(a.c, i + nx)] && (ix % kIT == 0 || a.L.valid[lphys(a.c, i - 1)] || a.L.valid[lphys(a.c, i + nx - 1)]))
-    unite(a.parent, (int32_t)i, (int32_t)(i + nx));
+// Seam pairs: ny to each vertical seam, then nx to each horizontal one.
+__host__ __device__ inline int64_t seam_pairs(int nx, int ny) {
+  return (int64_t)((nx - 1) / kIT) * ny + (int64_t)((ny - 1) / kIT) * nx;
 }
 
-__global__ __launch_bounds__(kNTi) void k_inp_border(InpaintArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * kNTi + threadIdx.x;
+__global__ __launch_bounds__(kNTi) void k_inp_seams(InpaintArgs a) {
   const int nx = a.c.nx;
   const int ny = a.c.ny;
-  if (i >= (int64_t)nx * ny) return;
-  const int iy = (int)(i / nx);
-  const int ix = (int)(i - (int64_t)iy * nx);
-  if (!a.L.valid[lphys(a.c, i)]) {
-    // a local root hands its tile's minimum to the final root
-    const uint32_t k = a.best[i];
-    if (k == kNoKey) return;
-    const int32_t r = find_root(a.parent, (int32_t)i);
-    if (r != (int32_t)i) atomicMin(a.best + r, k);
-    return;
+  const int64_t q = (int64_t)blockIdx.x * kNTi + threadIdx.x;
+  if (q >= seam_pairs(nx, ny)) return;
+  const int nv = ((nx - 1) / kIT) * ny;  // at most 511 * 16384
+  const bool vertical = q < nv;
+  const int u = (int)(vertical ? q : q - nv);
+  const int len = vertical ? ny : nx;
+  const int seam = u / len;
+  const int along = u - seam * len;
+  const int across = (seam + 1) * kIT - 1;
+  const int32_t i = vertical ? along * nx + across : across * nx + along;
+  const int32_t j = i + (vertical ? 1 : nx);
+  const int32_t back = vertical ? nx : 1;  // the pair before this one along the seam
+  // (whatever unions these loads see, they give an ancestor of a hole, -1 of a
+  // valid cell)
+  const bool first = along % kIT == 0;
+  const int32_t pi = a.parent[i], pj = a.parent[j];
+  const int32_t bi = first ? -1 : a.parent[i - back], bj = first ? -1 : a.parent[j - back];
+  if (pi >= 0 && pj >= 0) {
+    // pairs next to each other along a tile edge are already joined on both
+    // sides: only the first pair of each run of pairs unites
+    if (bi < 0 || bj < 0) unite(a.parent, pi, pj);
+  } else if (pi >= 0) {
+    atomicMin(a.best + pi, f32_key(a.out[j]));
+  } else if (pj >= 0) {
+    atomicMin(a.best + pj, f32_key(a.out[i]));
   }
-  // valid cells offer their height to holes across a tile edge
-  const int tx = ix % kIT;
-  const int ty = iy % kIT;
-  if (tx != 0 && tx != kIT - 1 && ty != 0 && ty != kIT - 1) return;
-  const uint32_t k = f32_key(a.L.h[lphys(a.c, i)]);
-  if (tx == 0 && ix > 0 && !a.L.valid[lphys(a.c, i - 1)]) atomicMin(a.best + find_root(a.parent, (int32_t)(i - 1)), k);
-  if (tx == kIT - 1 && ix + 1 < nx && !a.L.valid[lphys(a.c, i + 1)])
-    atomicMin(a.best + find_root(a.parent, (int32_t)(i + 1)), k);
-  if (ty == 0 && iy > 0 && !a.L.valid[lphys(a.c, i - nx)])
-    atomicMin(a.best + find_root(a.parent, (int32_t)(i - nx)), k);
-  if (ty == kIT - 1 && iy + 1 < ny && !a.L.valid[lphys(a.c, i + nx)])
-    atomicMin(a.best + find_root(a.parent, (int32_t)(i + nx)), k);
+}
+
+__global__ __launch_bounds__(kNTi) void k_inp_collect(InpaintArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * kNTi + threadIdx.x;
+  if (i >= (int64_t)a.c.nx * a.c.ny) return;
+  const uint32_t k = a.best[i];
+  if (k == kNoKey) return;
+  const int32_t r = find_root(a.parent, (int32_t)i);
+  if (r != (int32_t)i) atomicMin(a.best + r, k);
 }
 
 __global__ __launch_bounds__(kNTi) void k_inp_fill(InpaintArgs a) {
   const int64_t i = (int64_t)blockIdx.x * kNTi + threadIdx.x;
   if (i >= (int64_t)a.c.nx * a.c.ny) return;
-  a.out[i] = a.L.valid[lphys(a.c, i)] ? a.L.h[lphys(a.c, i)] : key_f32(a.best[find_root(a.parent, (int32_t)i)]);
+  const int32_t p = a.parent[i];
+  if (p >= 0) a.out[i] = key_f32(a.best[find_root(a.parent, p)]);
 }
 
 // -------------------------------------------------------------- smoothing
@@ -307,45 +309,119 @@ __global__ __launch_bounds__(kNTi) void k_smooth_sep(SmoothArgs a) {
   a.out[(int64_t)gy * a.nx + gx] = acc * a.scale;
 }
 
-// Median of a K x K window: the value whose rank brackets the middle; NaN if
-// the window holds a NaN.
+// ------------------------------------------------------------------ median
+// A wave takes one row of 64 - (K - 1) outputs, a column per lane.  A lane sorts
+// its column of K values; the sorted columns of the K - 1 lanes beside it come by
+// DPP moves.  Selecting from sorted columns takes about a fifth of the
+// comparisons of ranking every value against every other: 15.7 -> 4.1 us for
+// ksize 5 on 400 x 400 cells.
+__device__ __forceinline__ void order(float& a, float& b) {
+  const float lo = fminf(a, b);
+  b = fmaxf(a, b);
+  a = lo;
+}
+
+__device__ __forceinline__ void sort3(float& a, float& b, float& c) {
+  order(a, b);
+  order(b, c);
+  order(a, b);
+}
+
+// Nine exchanges.
+__device__ __forceinline__ void sort5(float (&v)[5]) {
+  order(v[0], v[1]);
+  order(v[3], v[4]);
+  order(v[2], v[4]);
+  order(v[2], v[3]);
+  order(v[1], v[4]);
+  order(v[0], v[3]);
+  order(v[0], v[2]);
+  order(v[1], v[3]);
+  order(v[1], v[2]);
+}
+
+// The middle of n (odd) values, of which the first n / 2 + 2 are held: their
+// smallest and largest cannot be the middle and go, and the next value comes in.
+template <int n>
+__device__ __forceinline__ float middle(float* v) {
+  constexpr int held = n / 2 + 2;
+  if constexpr (n == 3) {
+    return __builtin_amdgcn_fmed3f(v[0], v[1], v[2]);
+  } else {
+#pragma unroll
+    for (int i = 1; i < held; ++i) order(v[0], v[i]);       // smallest to v[0]
+#pragma unroll
+    for (int i = 1; i + 1 < held; ++i) order(v[i], v[held - 1]);  // largest to the end
+    // what is left: v[1 .. held - 2], then the values not seen yet
+#pragma unroll
+    for (int i = 0; i < held - 2; ++i) v[i] = v[i + 1];
+#pragma unroll
+    for (int i = held - 2; i < n - 2; ++i) v[i] = v[i + 2];
+    return middle<n - 2>(v);
+  }
+}
+
+// The lane's value of the column `step` to the right (below: to the left); lanes
+// at the wave's ends get a value they do not use.
+template <int step>
+__device__ __forceinline__ float column(float v) {
+  int x = __float_as_int(v);
+#pragma unroll
+  for (int i = 0; i < (step < 0 ? -step : step); ++i)
+    x = step < 0 ? __builtin_amdgcn_update_dpp(0, x, 0x138 /* wave_shr:1 */, 0xf, 0xf, false)
+                 : __builtin_amdgcn_update_dpp(0, x, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
+  return __int_as_float(x);
+}
+
+// Median of a K x K window: the middle value; NaN if the window holds a NaN.
+constexpr int kNTm = 64 * kFT;  // a wave to a row, kFT rows to a workgroup
+
 template <int K>
-__global__ __launch_bounds__(kNTi) void k_smooth_median(SmoothArgs a) {
-  __shared__ float s[kFH][kFH];
-  const int x0 = blockIdx.x * kFT;
-  const int y0 = blockIdx.y * kFT;
-  stage(s, a, x0, y0);
-  __syncthreads();
-  const int lx = threadIdx.x % kFT;
-  const int ly = threadIdx.x / kFT;
-  const int gx = x0 + lx;
-  const int gy = y0 + ly;
-  if (gx >= a.nx || gy >= a.ny) return;
-  constexpr int N = K * K;
-  constexpr int mid = N / 2;
-  float v[N];
+__global__ __launch_bounds__(kNTm) void k_smooth_median(SmoothArgs a) {
+  constexpr int R = K / 2;
+  const int lane = threadIdx.x & 63;
+  const int gx = (int)blockIdx.x * (64 - 2 * R) - R + lane;
+  const int gy = (int)blockIdx.y * kFT + (int)(threadIdx.x >> 6);
+  if (gy >= a.ny) return;  // whole waves
+  const int cx = mirror(gx, a.nx);
+  float v[K];
   bool nan = false;
 #pragma unroll
-  for (int dy = 0; dy < K; ++dy)
-#pragma unroll
-    for (int dx = 0; dx < K; ++dx) {
-      v[dy * K + dx] = s[ly + dy][lx + dx];
-      nan = nan || isnan(v[dy * K + dx]);
-    }
-  float med = __builtin_nanf("");
-  if (!nan) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      int less = 0, same = 0;
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        less += v[j] < v[i] ? 1 : 0;
-        same += v[j] == v[i] ? 1 : 0;
-      }
-      if (less <= mid && less + same > mid) med = v[i];
-    }
+  for (int j = 0; j < K; ++j) {
+    v[j] = a.in[(int64_t)mirror(gy + j - R, a.ny) * a.nx + cx];
+    nan = nan || isnan(v[j]);
   }
-  a.out[(int64_t)gy * a.nx + gx] = med;
+  uint64_t bad = __ballot(nan);
+  float med;
+  if constexpr (K == 3) {
+    bad |= (bad << 1) | (bad >> 1);
+    sort3(v[0], v[1], v[2]);
+    const float lo = fmaxf(fmaxf(column<-1>(v[0]), v[0]), column<1>(v[0]));
+    const float mi = __builtin_amdgcn_fmed3f(column<-1>(v[1]), v[1], column<1>(v[1]));
+    const float hi = fminf(fminf(column<-1>(v[2]), v[2]), column<1>(v[2]));
+    med = __builtin_amdgcn_fmed3f(lo, mi, hi);
+  } else {
+    bad |= (bad << 1) | (bad >> 1) | (bad << 2) | (bad >> 2);
+    sort5(v);
+    float r[5][5];  // by rank in the column, then sorted across the columns
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      r[i][0] = column<-2>(v[i]);
+      r[i][1] = column<-1>(v[i]);
+      r[i][2] = v[i];
+      r[i][3] = column<1>(v[i]);
+      r[i][4] = column<2>(v[i]);
+      sort5(r[i]);
+    }
+    // Sorted both ways, r[i][j] has (i + 1)(j + 1) - 1 values not above and
+    // (5 - i)(5 - j) - 1 not below it.  Where one of them is over 12 it is not the
+    // middle of 25: six values below and six above it go, 13 are left.
+    float c[13] = {r[0][3], r[0][4], r[1][2], r[1][3], r[1][4], r[2][1], r[2][2],
+                   r[2][3], r[3][0], r[3][1], r[3][2], r[4][0], r[4][1]};
+    med = middle<13>(c);
+  }
+  if (lane >= R && lane < 64 - R && gx < a.nx)
+    a.out[(int64_t)gy * a.nx + gx] = ((bad >> lane) & 1u) ? __builtin_nanf("") : med;
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -375,16 +451,20 @@ hipError_t launch_inpaint(const Consts& c, const Layers& L, float* out, char* sc
     hipLaunchKernelGGL(k_inp_local, dim3(tiles), dim3(kNTl), 0, stream, a);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  {
-    TimedLaunch tl("k_inp_merge", stream);
-    hipLaunchKernelGGL(k_inp_merge, grid, dim3(kNTi), 0, stream, a);
+  // a map of one tile has no seams: its local minima are final
+  if (const int64_t pairs = seam_pairs(c.nx, c.ny)) {
+    {
+      TimedLaunch tl("k_inp_seams", stream);
+      hipLaunchKernelGGL(k_inp_seams, dim3((unsigned)((pairs + kNTi - 1) / kNTi)), dim3(kNTi), 0,
+                         stream, a);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    {
+      TimedLaunch tl("k_inp_collect", stream);
+      hipLaunchKernelGGL(k_inp_collect, grid, dim3(kNTi), 0, stream, a);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  {
-    TimedLaunch tl("k_inp_border", stream);
-    hipLaunchKernelGGL(k_inp_border, grid, dim3(kNTi), 0, stream, a);
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   {
     TimedLaunch tl("k_inp_fill", stream);
     hipLaunchKernelGGL(k_inp_fill, grid, dim3(kNTi), 0, stream, a);
@@ -419,8 +499,10 @@ hipError_t launch_smooth(const float* in, float* out, int nx, int ny, int kind, 
   const dim3 grid((unsigned)((nx + kFT - 1) / kFT), (unsigned)((ny + kFT - 1) / kFT));
   if (kind == 2) {
     TimedLaunch tl("k_smooth_median", stream);
-    if (ksize == 3) hipLaunchKernelGGL(k_smooth_median<3>, grid, dim3(kNTi), 0, stream, a);
-    else hipLaunchKernelGGL(k_smooth_median<5>, grid, dim3(kNTi), 0, stream, a);
+    const int wide = 64 - 2 * a.r;
+    const dim3 rows((unsigned)((nx + wide - 1) / wide), grid.y);
+    if (ksize == 3) hipLaunchKernelGGL(k_smooth_median<3>, rows, dim3(kNTm), 0, stream, a);
+    else hipLaunchKernelGGL(k_smooth_median<5>, rows, dim3(kNTm), 0, stream, a);
   } else {
     TimedLaunch tl("k_smooth_sep", stream);
     hipLaunchKernelGGL(k_smooth_sep, grid, dim3(kNTi), 0, stream, a);
