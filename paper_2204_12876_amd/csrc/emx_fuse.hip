@@ -43,7 +43,6 @@ namespace emx {
 
 namespace {
 
-constexpr int kNT1 = 256;                   // threads of the wall rule's counts
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;   // lanes without an accepted point
 
 // The integer X = round(x * 2^S) (ties to even) of a finite float32 x, as
@@ -353,21 +352,24 @@ __device__ __forceinline__ void tile_body_wave(const Item& it, int64_t t) {
 // twice as many slots as points: a free slot always exists) and then adds one
 // count per distinct cell.  Integer sums do not depend on their order.  The
 // counts are zeroed by the launch before.
+// As in pass 1, a frame alone takes one point per thread, a batch four (300k
+// points on 400 x 400 cells: 7.4 -> 5.7 us).
 constexpr int kCountSlotsLog = 11;
 constexpr int kCountSlots = 1 << kCountSlotsLog;
 static_assert(kCountSlots >= 2 * kChunk, "the table must keep a free slot");
 
+template <int kT>
 __device__ __forceinline__ void count_body(const Item& it, int64_t chunk) {
   __shared__ uint32_t s_key[kCountSlots];  // cell + 1, 0 = empty
   __shared__ uint32_t s_cnt[kCountSlots];
-  for (int j = threadIdx.x; j < kCountSlots; j += kNT1) {
+  for (int j = threadIdx.x; j < kCountSlots; j += kT) {
     s_key[j] = 0u;
     s_cnt[j] = 0u;
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kChunk / kNT1; ++j) {
-    const int64_t i = chunk * kChunk + j * kNT1 + threadIdx.x;
+  for (int j = 0; j < kChunk / kT; ++j) {
+    const int64_t i = chunk * kChunk + j * kT + threadIdx.x;
     if (i >= it.n) continue;
     const PointEval e = eval_point(it.P, it.c, it.x[i], it.y[i], it.z[i]);
     int ix, iy;
@@ -385,7 +387,7 @@ __device__ __forceinline__ void count_body(const Item& it, int64_t chunk) {
     }
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < kCountSlots; j += kNT1) {
+  for (int j = threadIdx.x; j < kCountSlots; j += kT) {
     const uint32_t key = s_key[j];
     if (key) atomicAdd(it.fs.count + (key - 1u), s_cnt[j]);
   }
@@ -411,7 +413,9 @@ __device__ __forceinline__ void timevar_body(const Item& it, int64_t unit) {
   it.L.v[i] = v;
 }
 
-__global__ __launch_bounds__(kNT1) void k_fuse_count(Item it) { count_body(it, blockIdx.x); }
+__global__ __launch_bounds__(kChunk) void k_fuse_count(Item it) {
+  count_body<kChunk>(it, blockIdx.x);
+}
 
 __global__ __launch_bounds__(kNTv) void k_time_variance(Item it) { timevar_body(it, blockIdx.x); }
 
@@ -464,12 +468,12 @@ __global__ __launch_bounds__(256) void k_zero_b(const Batch* bt) {
   }
 }
 
-__global__ __launch_bounds__(kNT1) void k_fuse_count_b(const Batch* bt) {
+__global__ __launch_bounds__(kThreadsBatch) void k_fuse_count_b(const Batch* bt) {
   const UnitFinder units(bt, kBCount);
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
     int64_t unit;
     const int i = units.find(w, unit);
-    count_body(bt->items[i], unit);
+    count_body<kThreadsBatch>(bt->items[i], unit);
     __syncthreads();
   }
 }
@@ -558,7 +562,7 @@ hipError_t launch_fuse(const Item& it, hipStream_t stream) {
       if ((err = hipGetLastError()) != hipSuccess) return err;
       {
         TimedLaunch tl("k_fuse_count", stream);
-        hipLaunchKernelGGL(k_fuse_count, dim3(it.B), dim3(kNT1), 0, stream, it);
+        hipLaunchKernelGGL(k_fuse_count, dim3(it.B), dim3(kChunk), 0, stream, it);
       }
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
@@ -610,7 +614,7 @@ hipError_t launch_fuse_batch(const Batch* d_batch, const int grid[5], hipStream_
   }
   if (grid[1] > 0) {
     TimedLaunch tl("k_fuse_count_b", stream);
-    hipLaunchKernelGGL(k_fuse_count_b, dim3(grid[1]), dim3(kNT1), 0, stream, d_batch);
+    hipLaunchKernelGGL(k_fuse_count_b, dim3(grid[1]), dim3(kThreadsBatch), 0, stream, d_batch);
   }
   {
     TimedLaunch tl("k_fuse_chunk_b", stream);
