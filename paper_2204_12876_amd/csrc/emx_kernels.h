@@ -92,7 +92,6 @@ hipError_t launch_smooth(const float* in, float* out, int nx, int ny, int kind, 
 
 // ------------------------------------------------------------------ drift
 struct DriftScratch {
-  void* res;            // the mean (double) and count (int64) of the last call
   double* part_sum;     // [chunks] float64 partial sums of the errors
   uint32_t* part_cnt;   // [chunks] contributing points per chunk
 };
