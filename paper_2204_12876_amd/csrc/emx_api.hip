@@ -276,7 +276,7 @@ emx_status emx_init_map(const emx_params* params, double cx, double cy, int64_t 
   m->t0 = t0_ms;
   m->state = (char*)d_state;
   const size_t set_bytes = set_layout(*params, m->state, &m->L);
-  m->L.clr = (float2*)(m->state + set_bytes);
+  m->L.clr = (float*)(m->state + set_bytes);
   m->ctl = (uint32_t*)(m->state + set_bytes + clr_bytes(*params));
   hipError_t e =
       launch_fill_prior(m->c, m->L, m->ctl, (int)ctl_words(*params), (hipStream_t)stream);

@@ -12,10 +12,13 @@
 //   - Per 8 x 8 block (cmax) and per 32 x 32 superblock (smax): the largest
 //     height of a cell that a ray could still remove: valid, older than the
 //     minimum age, with a normal.  It is -inf if there is none.
-//   - Each cell's 8-byte clearing record {h, or -inf if no ray may remove it,
-//     v}, so that the march's height test takes one load.
-//   - Loads come in two rounds: validity, then the update time, normal z,
-//     height and variance of valid cells (or the upper bound of invalid ones).
+//   - Each cell's clearing record: h, or -inf if no ray may remove it, so that
+//     the march's height test takes one load.  A map alone keeps {that, v}, which
+//     stops most of what passes the test of the height alone (4M rays: the march
+//     271 against 285 us); a batch keeps 4 bytes, which is what bounds its setup
+//     (16 maps: 39 -> 30 us, the march the same).
+//   - Loads come in two rounds: validity, then the update time, normal z, height
+//     and variance of valid cells (or the upper bound of invalid ones).
 //   - The caller's removed-cell mask is zeroed here.
 // march: one workgroup per 128 rays (256 in a batch).
 //   - The ray is cut into groups of Item::grp consecutive samples, at most 7
@@ -33,13 +36,15 @@
 //     1.5 times slower on 400 x 400 maps: the longest ray's chain of lookups, a
 //     microsecond each, set the time.
 //   - Every sample of a surviving half group is evaluated exactly and compared
-//     with its cell's record; the few below it read the cell's normal.
+//     with its cell's record; the few below it read the cell's variance and
+//     normal.
 //   - A sample that removes its cell resets the cell to the prior on the spot
-//     (and flags it in the caller's mask).  The march reads only the setup's
-//     records and the normals, never the heights, variances or validity it
-//     resets, so every ray still sees the state as it was when the call
-//     started.  Resets are idempotent stores of the same values, so their
-//     order never shows in the result.
+//     (and flags it in the caller's mask).  Of what it resets the march reads
+//     only the variance, of a cell that it may be about to remove: a ray that
+//     sees it reset finds a cell that is removed already.  All else are the
+//     setup's records and the normals, so every ray tests the state as it was
+//     when the call started, and resets are idempotent stores of the same
+//     values: their order never shows in the result.
 // Measured on MI355X, setup + march, against a queue of 16-sample segments whose
 // every sample was evaluated: 4M LiDAR rays on 2000 x 2000 cells 1197 -> 288 us,
 // 300k rays on 400 x 400 cells 25.4 -> 22.9 us, 16 maps with 4.6M rays in a batch
@@ -264,44 +269,59 @@ __device__ __forceinline__ Sample sample_of(const Item& it, const Ray& r, int k,
 constexpr int kUnroll = 4;
 
 // Samples [ka, kb] of ray r against the map, kUnroll at a time.  Their cells are
-// found without branches, then their clearing records {h, v} are all requested
-// together.  A cell no ray may clear holds -inf, which fails hd > 0 for every
-// finite sample height.  On maps with an upper bound layer
-// (kBound), a cell without an estimate holds {NaN, its bound at the call's
-// start} (no other record holds NaN).  The few samples that act go through one
-// loop, a lane's next one each time, so that a wave waits for its fullest lane
-// and not for every position.
-template <bool kBound>
+// found without branches, then their clearing records are all requested
+// together: the height, or -inf for a cell no ray may clear, which fails hd > 0
+// for every finite sample height.  With kPair the record also holds the
+// variance; on maps with an upper bound layer (kBound, always pairs) a cell
+// without an estimate holds {NaN, its bound at the call's start} (no other
+// record holds NaN).  The few samples that pass go through one loop, a lane's
+// next one each time, so that a wave waits for its fullest lane and not for
+// every position.  Without pairs that loop reads the variance from the layer:
+// another ray may have removed the cell meanwhile, but then it is removed
+// whatever this ray finds.
+template <bool kBound, bool kPair>
 __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int ka, int kb) {
   const float2 lim = make_float2(__uint_as_float(__float_as_uint(it.c.nxf) - 1u),
                                  __uint_as_float(__float_as_uint(it.c.nyf) - 1u));
   for (int k = ka; k <= kb; k += kUnroll) {
     float qz[kUnroll];
     bool cand[kUnroll];
-    float2 rec[kUnroll];
+    float rec[kUnroll], v[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const Sample q = sample_of(it, r, k + u, lim);
       const uint32_t cell = __umul24(q.iy, it.c.nx) + (uint32_t)q.ix;
       qz[u] = q.qz;
       cand[u] = (k + u <= kb) & q.in & ((int)cell != r.end_cell);
-      rec[u] = *(const float2*)((const char*)it.L.clr + cell * 8u);
+      v[u] = -INFINITY;
+      if (kPair) {
+        const float2 p = *(const float2*)((const char*)it.L.clr + cell * 8u);
+        rec[u] = p.x;
+        v[u] = p.y;
+      } else {
+        rec[u] = *(const float*)((const char*)it.L.clr + cell * 4u);
+      }
     }
     uint32_t remove = 0, bound = 0;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      const float hd = rec[u].x - qz[u];
-      if (cand[u] & (hd > 0.0f) & ((hd * hd) > rec[u].y)) remove |= 1u << u;
-      if (kBound && (cand[u] & isnan(rec[u].x) & (qz[u] < rec[u].y))) bound |= 1u << u;
+      const float hd = rec[u] - qz[u];
+      if (cand[u] & (hd > 0.0f) & (!kPair || (hd * hd) > v[u])) remove |= 1u << u;
+      if (kBound && (cand[u] & isnan(rec[u]) & (qz[u] < v[u]))) bound |= 1u << u;
     }
     while (remove | bound) {
       const int u = __builtin_ctz(remove | bound);
       const Sample q = sample_of(it, r, k + u, lim);
       const int64_t pc = pcell(it.c, q.ix, q.iy);
       if ((remove >> u) & 1u) {
+        bool below = true;
+        if (!kPair) {
+          const float hd = it.L.clr[__umul24(q.iy, it.c.nx) + (uint32_t)q.ix] - q.qz;
+          below = (hd * hd) > it.L.v[pc];
+        }
         const float an2dd = it.c.an2 * ((r.dx * r.dx + r.dy * r.dy) + r.dz * r.dz);
         const float dot = (r.dx * it.L.nx[pc] + r.dy * it.L.ny[pc]) + r.dz * it.L.nz[pc];
-        if ((dot * dot) > an2dd) clear_cell(it, pc, q.iy * it.c.nx + q.ix);
+        if (below && (dot * dot) > an2dd) clear_cell(it, pc, q.iy * it.c.nx + q.ix);
       } else if (q.qz < it.L.ub[pc]) {  // another ray may have lowered it further
         atomic_min_f32(it.L.ub + pc, q.qz);
       }
@@ -314,7 +334,8 @@ __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int k
 // ------------------------------------------------------------------- setup
 // Superblock `unit` of item `it`: its block maxima, its own, and the records.
 // kAll: every cell's fields are loaded along with its validity.
-template <bool kAll>
+// kPair: the records are pairs.
+template <bool kAll, bool kBound, bool kPair>
 __device__ __forceinline__ void setup_body(const Item& it, int unit, float* s_max) {
   constexpr int kRows = 4;  // rows of a lane's column, two apart
   const int lane = threadIdx.x & 63;
@@ -348,25 +369,25 @@ __device__ __forceinline__ void setup_body(const Item& it, int unit, float* s_ma
       tu[j] = it.L.t[p[j]];
       nz[j] = it.L.nz[p[j]];
       h[j] = it.L.h[p[j]];
-      v[j] = it.L.v[p[j]];
+      if (kPair) v[j] = it.L.v[p[j]];
     }
-    if (it.L.ub && in[j] && (kAll || !vd[j])) ub[j] = it.L.ub[p[j]];
+    if (kBound && in[j] && (kAll || !vd[j])) ub[j] = it.L.ub[p[j]];
   }
-  float2 rec[kRows];
+  float rec[kRows];
   float m = -INFINITY;
 #pragma unroll
   for (int j = 0; j < kRows; ++j) {
     if (in[j] && it.out_cleared) it.out_cleared[c[j]] = 0;  // the march sets removals
     const bool ok = in[j] && clearable(it, vd[j], tu[j], nz[j]);
-    if (it.L.ub && in[j] && !vd[j]) {
+    // a NaN height can never be cleared (hd > 0 fails), so -inf serves
+    rec[j] = ok && !isnan(h[j]) ? h[j] : -INFINITY;
+    m = fmaxf(m, rec[j]);
+    if (kBound && in[j] && !vd[j]) {
       // a sample below the bound of a cell without an estimate lowers it:
       // such cells take part in the maximum too
-      rec[j] = make_float2(__builtin_nanf(""), ub[j]);
+      rec[j] = __builtin_nanf("");
+      v[j] = ub[j];
       m = fmaxf(m, ub[j]);
-    } else {
-      // a NaN height can never be cleared (hd > 0 fails), so -inf serves
-      rec[j] = make_float2(ok && !isnan(h[j]) ? h[j] : -INFINITY, v[j]);
-      m = fmaxf(m, rec[j].x);
     }
   }
   m = fmaxf(m, __shfl_xor(m, 1, 64));
@@ -375,7 +396,10 @@ __device__ __forceinline__ void setup_body(const Item& it, int unit, float* s_ma
   m = fmaxf(m, __shfl_xor(m, 32, 64));
 #pragma unroll
   for (int j = 0; j < kRows; ++j)
-    if (in[j]) it.L.clr[c[j]] = rec[j];
+    if (in[j]) {
+      if (kPair) ((float2*)it.L.clr)[c[j]] = make_float2(rec[j], v[j]);
+      else it.L.clr[c[j]] = rec[j];
+    }
   const int b = (sx << (kSuperLog - kBlockLog)) + (lane >> kBlockLog);
   const int by = (sy << (kSuperLog - kBlockLog)) + wave;
   if (lane < 32 && (lane & 7) == 0 && b < it.bx && by < it.by) it.L.cmax[by * it.bx + b] = m;
@@ -433,7 +457,7 @@ __device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, ui
 
 // Rays [kRays unit, kRays unit + kRays) of the item.  The counts in s are zero
 // on entry and on return (every thread passes a barrier after they were reset).
-template <int kRays>
+template <int kRays, bool kPair>
 __device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchShared<kRays>& s) {
   const int tid = threadIdx.x;
   const int64_t i = unit * kRays + tid;
@@ -494,8 +518,8 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchSh
         const Ray q = {s.dx[w], s.dy[w], s.dz[w], s.end_cell[w], s.rK[w], s.k1[w]};
         const int ka = (int)(e & 0xFFFFFFu);
         const int kb = min(ka + part - 1, q.k1);
-        if (it.L.ub) test_samples<true>(it, q, ka, kb);
-        else test_samples<false>(it, q, ka, kb);
+        if (it.L.ub) test_samples<true, true>(it, q, ka, kb);
+        else test_samples<false, kPair>(it, q, ka, kb);
       }
       __syncthreads();  // the pieces have been read
       if (tid == 0) s.npieces = 0;
@@ -510,7 +534,8 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchSh
 template <bool kAll>
 __global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
   __shared__ float s_max[kNTc / 64];
-  setup_body<kAll>(it, blockIdx.x, s_max);
+  if (it.L.ub) setup_body<kAll, true, true>(it, blockIdx.x, s_max);
+  else setup_body<kAll, false, true>(it, blockIdx.x, s_max);
 }
 
 // The maxima are read through the caches: they are small and shared by every
@@ -520,7 +545,7 @@ __global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
   __shared__ MarchShared<kRays> s;
   if (threadIdx.x == 0) s.nspans = s.npieces = 0;
   __syncthreads();
-  march_body(it, blockIdx.x, s);
+  march_body<kRays, true>(it, blockIdx.x, s);
 }
 
 __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
@@ -529,7 +554,9 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
     int64_t unit;
     const int i = units.find(w, unit);
-    setup_body<false>(bt->items[i], (int)unit, s_max);
+    const Item& it = bt->items[i];
+    if (it.L.ub) setup_body<false, true, true>(it, (int)unit, s_max);
+    else setup_body<false, false, false>(it, (int)unit, s_max);
     __syncthreads();
   }
 }
@@ -542,7 +569,7 @@ __global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
     int64_t unit;
     const int i = units.find(w, unit);
-    march_body(bt->items[i], unit, s);
+    march_body<kRaysBatch, false>(bt->items[i], unit, s);
   }
 }
 

@@ -43,7 +43,8 @@ struct Layers {
   float* cmax;    // per logical block: max height over cells a ray may clear (transient)
   float* smax;    // the same per logical superblock (transient)
   float* ub;      // upper bound of the ground height (+inf: none), or null
-  float2* clr;    // per logical cell {h, or -inf if a ray may not clear it, v} (transient)
+  float* clr;     // per logical cell: h, or -inf if a ray may not clear it; or pairs of that
+                  // and v (with the bound layer {NaN, bound} without an estimate) (transient)
   uint64_t* fx;   // the fusion's fixed-point sums: kFxWords planes of fxs words, one word
                   // per physical cell each; all zero between calls
   int64_t fxs;    // plane stride in words
