@@ -16,11 +16,11 @@
 //     the march's height test takes one load.  A map alone keeps {that, v}, which
 //     stops most of what passes the test of the height alone (4M rays: the march
 //     271 against 285 us); a batch keeps 4 bytes, which is what bounds its setup
-//     (16 maps: 39 -> 30 us, the march the same).
+//     (16 maps: 39 -> 28 us, the march the same).
 //   - Loads come in two rounds: validity, then the update time, normal z, height
 //     and variance of valid cells (or the upper bound of invalid ones).
 //   - The caller's removed-cell mask is zeroed here.
-// march: one workgroup per 128 rays (256 in a batch).
+// march: one workgroup per 64, 128 or (in a batch) 256 rays.
 //   - The ray is cut into groups of Item::grp consecutive samples, at most 7
 //     cells of travel, and spans of four groups.  Lower bounds of a group's
 //     cells and height come from the ray's line, widened by more than the
@@ -31,13 +31,14 @@
 //     never skips a sample that could act, and costs no sample evaluation.
 //   - Three phases hand lists in LDS to each other, so that every phase has an
 //     equal share for each thread whatever the rays' lengths: spans (one ray
-//     per thread), groups (one surviving span per thread), samples (half a
-//     surviving group per thread).  One thread per ray through all phases was
-//     1.5 times slower on 400 x 400 maps: the longest ray's chain of lookups, a
-//     microsecond each, set the time.
-//   - Every sample of a surviving half group is evaluated exactly and compared
-//     with its cell's record; the few below it read the cell's variance and
-//     normal.
+//     per thread), groups (one surviving span per thread; rays of one span take
+//     theirs in the first phase), samples (one surviving group per thread).  One
+//     thread per ray through all phases was 1.5 times slower on 400 x 400 maps:
+//     the longest ray's chain of lookups, a microsecond each, set the time.
+//   - Every sample of a surviving group is evaluated exactly and compared
+//     with its cell's record, eight samples' records requested together (4M
+//     rays: 260 against 273 us for half groups of four); the few below it read
+//     the cell's variance and normal.
 //   - A sample that removes its cell resets the cell to the prior on the spot
 //     (and flags it in the caller's mask).  Of what it resets the march reads
 //     only the variance, of a cell that it may be about to remove: a ray that
@@ -46,9 +47,9 @@
 //     when the call started, and resets are idempotent stores of the same
 //     values: their order never shows in the result.
 // Measured on MI355X, setup + march, against a queue of 16-sample segments whose
-// every sample was evaluated: 4M LiDAR rays on 2000 x 2000 cells 1197 -> 288 us,
+// every sample was evaluated: 4M LiDAR rays on 2000 x 2000 cells 1197 -> 276 us,
 // 300k rays on 400 x 400 cells 25.4 -> 22.9 us, 16 maps with 4.6M rays in a batch
-// 302 -> 180 us.  The march is bound by VALU issue on the large frames (0.83 of
+// 302 -> 148 us.  The march is bound by VALU issue on the large frames (0.83 of
 // the SIMDs' issue slots) and by its chain of lookups on the small ones.
 // There is no separate pass to apply the removals.
 //
@@ -64,22 +65,24 @@ namespace emx {
 namespace {
 
 constexpr int kNTc = 256;
-// Rays of a march workgroup.  A single frame's few workgroups are balanced
-// better by 128 (400 x 400: 17.0 against 19.4 us; 128 x 128: 6.3 against 10.0);
-// a batch has enough of them, and 256 halve the work's fixed part (16 maps:
-// 137 against 167 us).  4M rays alone: the same.  With an upper bound layer most
-// samples over unseen ground act, and 64 keep the longest rays' workgroups short
-// (400 x 400: 22 against 27 us; without the layer 18.5 against 17).
+// Rays of a march workgroup.  A single frame's workgroups are balanced better by
+// 128 than by 256 (400 x 400: 17.0 against 19.4 us); a batch has enough of them,
+// and 256 halve the work's fixed part (16 maps: 137 against 167 us).  4M rays
+// alone: the same.  64 keep the longest rays' workgroups short, which pays while
+// 128 would leave fewer than 4 workgroups to a CU (a whole call, 60k rays on
+// 200 x 200: 12.0 against 14.6 us; 100k on 2000 x 2000: 34.6 against 38.9; 200k:
+// the same; 300k on 400 x 400: 18.5 against 17) and with an upper bound layer,
+// where most samples over unseen ground act (400 x 400: 22 against 27 us).
 constexpr int kRaysPlain = 128;
-constexpr int kRaysBound = 64;
+constexpr int kRaysShort = 64;
 constexpr int kRaysBatch = 256;
+constexpr int64_t kShortRays = 1 << 17;  // the line: 4 x 256 workgroups of 128
 // Maps up to this size load a cell's fields without waiting for its validity: the
 // 16 bytes that most cells then load for nothing cost less than the round trip
 // (128 x 128: 6.1 -> 5.1 us, 400 x 400 with the bound: 6.6 -> 5.5 us).
 constexpr int64_t kAllCells = 1 << 18;
 constexpr int kSpanGroups = 4;  // groups in a span
 constexpr int kSpans = 8;       // spans of a ray looked up together
-constexpr int kParts = 2;       // parts of a group, looked up together
 
 // A ray: direction from the sensor origin (Pose32::t), 1/K correctly rounded
 // in double, the last sample that can lie in the map, and the end point's cell.
@@ -164,10 +167,10 @@ __device__ __forceinline__ bool ray_of(const Item& it, int64_t i, Ray& r, int& k
   return true;
 }
 
-// Lower bounds of the samples of a step: x and y, in blocks of 2^kLog cells,
-// bound the exact samples k .. k + step of the ray at line(k), z the height of
-// samples k .. k + part.  The samples' float32 evaluation and this one differ
-// by less than 2^-21 of the magnitudes entering them; the margins are 2^-19.
+// Lower bounds of the samples of a step: x and y, in blocks of 2^kLog cells, and
+// the height z of the exact samples k .. k + step of the ray are at least
+// line(k).  The samples' float32 evaluation and this one differ by less than
+// 2^-21 of the magnitudes entering them; the margins are 2^-19.
 struct Line {
   float x, dx, y, dy, z, dz;
   float zmin;  // no sample of the ray is lower; NaN if a step spans more than
@@ -175,7 +178,7 @@ struct Line {
 };
 
 template <int kLog>
-__device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step, int part) {
+__device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step) {
   const float scale = it.c.inv_r * (1.0f / (float)(1 << kLog));
   const float rk = (float)r.rK;
   const float s = (float)step;
@@ -190,40 +193,37 @@ __device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step, 
   l.dz = r.dz * rk;
   l.x = (ox - ex) + fminf(l.dx * s, 0.0f);
   l.y = (oy - ey) + fminf(l.dy * s, 0.0f);
-  l.z = (oz - ez) + fminf(l.dz * (float)part, 0.0f);
+  l.z = (oz - ez) + fminf(l.dz * s, 0.0f);
   const bool fits = fabsf(l.dx) * s + 2.0f * ex < 0.999f && fabsf(l.dy) * s + 2.0f * ey < 0.999f;
   l.zmin = fits ? fminf(oz, fmaf(l.dz, (float)r.k1, oz)) - ez : __builtin_nanf("");
   return l;
 }
 
-// Which of kN consecutive steps of `step` samples from sample k on may hold a
-// sample below the maximum of its block (`mx`, w x h blocks).  A step's samples
-// lie in the 2 x 2 blocks from its line's on, two 8-byte lookups; clamping
-// keeps every in-map cell among them.  Every lookup is requested before any is
-// used.  Each step answers for kParts parts of `part` samples (the last may
-// reach into the next step): bit j * kParts + p.  Maps of a single row or column
-// of blocks are not looked up.
+// Which of kN consecutive steps of `step` samples from sample k on (bit j: the
+// j-th) may hold a sample below the maximum of its block (`mx`, w x h blocks).  A
+// step's samples lie in the 2 x 2 blocks from its line's on, two 8-byte lookups;
+// clamping keeps every in-map cell among them.  Every lookup is requested before
+// any is used.  Maps of a single row or column of blocks are not looked up.
 struct __attribute__((packed, aligned(4))) Pair {
   float a, b;
 };
 
-template <int kN, int kParts>
-__device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int step, int part,
+template <int kN>
+__device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int step,
                                             const float* mx, int w, int h) {
   uint32_t live = 0;
 #pragma unroll
-  for (int j = 0; j < kN; ++j)
-#pragma unroll
-    for (int p = 0; p < kParts; ++p)
-      live |= (k + j * step + p * part <= k1) ? 1u << (j * kParts + p) : 0u;
+  for (int j = 0; j < kN; ++j) live |= (k + j * step <= k1) ? 1u << j : 0u;
   if (w < 2 || h < 2) return live;
   const float xm = (float)(w - 2), ym = (float)(h - 2);
   Pair lo[kN], hi[kN];
+  float z[kN];
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
     const float kf = (float)(k + j * step);
     const int x = (int)__builtin_amdgcn_fmed3f(fmaf(kf, l.dx, l.x), 0.0f, xm);
     const int y = (int)__builtin_amdgcn_fmed3f(fmaf(kf, l.dy, l.y), 0.0f, ym);
+    z[j] = fmaf(kf, l.dz, l.z);
     const uint32_t o = (__umul24(y, w) + (uint32_t)x) * 4u;
     lo[j] = *(const Pair*)((const char*)mx + o);
     hi[j] = *(const Pair*)((const char*)(mx + w) + o);
@@ -232,12 +232,8 @@ __device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int st
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
     const float m = fmaxf(fmaxf(lo[j].a, lo[j].b), fmaxf(hi[j].a, hi[j].b));
-#pragma unroll
-    for (int p = 0; p < kParts; ++p) {
-      // a NaN zmin or height may act (fmaxf would drop the former)
-      const float z = fmaf((float)(k + j * step + p * part), l.dz, l.z);
-      bits |= !(z >= m || l.zmin >= m) ? 1u << (j * kParts + p) : 0u;
-    }
+    // a NaN height may act (fmaxf would drop zmin's)
+    bits |= !(z[j] >= m || l.zmin >= m) ? 1u << j : 0u;
   }
   if (isnan(l.zmin)) bits = ~0u;
   return bits & live;
@@ -266,7 +262,7 @@ __device__ __forceinline__ Sample sample_of(const Item& it, const Ray& r, int k,
   return q;
 }
 
-constexpr int kUnroll = 4;
+constexpr int kUnroll = 8;
 
 // Samples [ka, kb] of ray r against the map, kUnroll at a time.  Their cells are
 // found without branches, then their clearing records are all requested
@@ -418,26 +414,26 @@ struct MarchShared {
   float dx[kRays], dy[kRays], dz[kRays];
   double rK[kRays];
   int k1[kRays], end_cell[kRays];
-  float line[7][kRays];  // of the groups
+  float line[7][kRays];  // of the groups, for rays of more than one span
   // entries: ray << 24 | first sample
   uint32_t spans[kSpans * kRays];
-  uint32_t pieces[kSpanGroups * kParts * kNTc];
-  int nspans, npieces;
+  uint32_t groups[kSpanGroups * (kRays + kNTc)];
+  int nspans, ngroups;
 };
 
-// Appends the steps of each lane's `bits` (kN steps of kP parts) to a list with
-// room for them, by one LDS atomic per wave (an atomic per lane with its own
-// count would be expanded into a loop over the lanes).  The j-th steps of all
-// lanes come together: neighbouring rays, whose lookups share cache lines.
-// Every lane of the wave calls it.
-template <int kN, int kP>
+// Appends the steps of each lane's `bits` (kN of them) to a list with room for
+// them, by one LDS atomic per wave (an atomic per lane with its own count would
+// be expanded into a loop over the lanes).  The j-th steps of all lanes come
+// together: neighbouring rays, whose lookups share cache lines.  Every lane of
+// the wave calls it.
+template <int kN>
 __device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, uint32_t ray, int k,
-                                       int step, int part) {
+                                       int step) {
   if (__ballot(bits != 0) == 0) return;
-  uint64_t b[kN * kP];
+  uint64_t b[kN];
   int total = 0;
 #pragma unroll
-  for (int j = 0; j < kN * kP; ++j) {
+  for (int j = 0; j < kN; ++j) {
     b[j] = __ballot((bits >> j) & 1u);
     total += __popcll(b[j]);
   }
@@ -446,11 +442,11 @@ __device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, ui
   at = __builtin_amdgcn_readfirstlane(at);
   const uint32_t e = (ray << 24) | (uint32_t)k;
 #pragma unroll
-  for (int j = 0; j < kN * kP; ++j) {
+  for (int j = 0; j < kN; ++j) {
     if (b[j] == 0) continue;
     const int below = (int)__builtin_amdgcn_mbcnt_hi(
         (uint32_t)(b[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[j], 0u));
-    if ((bits >> j) & 1u) list[at + below] = e + (uint32_t)((j / kP) * step + (j % kP) * part);
+    if ((bits >> j) & 1u) list[at + below] = e + (uint32_t)(j * step);
     at += __popcll(b[j]);
   }
 }
@@ -462,69 +458,80 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchSh
   const int tid = threadIdx.x;
   const int64_t i = unit * kRays + tid;
   const int grp = it.grp, span = kSpanGroups * it.grp;
-  const int part = (grp + kParts - 1) / kParts;
+  Ray r;
   int k = 1, k1 = 0;  // the ray's first sample that no span covers yet, its last
-  Line sl;
   if (tid < kRays) {
-    Ray r;
-    if (i < it.n && ray_of(it, i, r, k)) {
-      k1 = r.k1;
-      sl = line_of<kSuperLog>(it, r, span, span);
+    uint32_t gb = 0;
+    int first = 1;
+    if (i < it.n && ray_of(it, i, r, first)) {
       s.dx[tid] = r.dx;
       s.dy[tid] = r.dy;
       s.dz[tid] = r.dz;
       s.rK[tid] = r.rK;
       s.k1[tid] = r.k1;
       s.end_cell[tid] = r.end_cell;
-      const Line l = line_of<kBlockLog>(it, r, grp, part);
-      s.line[0][tid] = l.x;
-      s.line[1][tid] = l.dx;
-      s.line[2][tid] = l.y;
-      s.line[3][tid] = l.dy;
-      s.line[4][tid] = l.z;
-      s.line[5][tid] = l.dz;
-      s.line[6][tid] = l.zmin;
+      const Line l = line_of<kBlockLog>(it, r, grp);
+      if (r.k1 - first < span) {
+        // one span, as most rays: its groups at once
+        gb = may_act<kSpanGroups>(l, first, r.k1, grp, it.L.cmax, it.bx, it.by);
+      } else {
+        s.line[0][tid] = l.x;
+        s.line[1][tid] = l.dx;
+        s.line[2][tid] = l.y;
+        s.line[3][tid] = l.dy;
+        s.line[4][tid] = l.z;
+        s.line[5][tid] = l.dz;
+        s.line[6][tid] = l.zmin;
+        k = first;
+        k1 = r.k1;
+      }
     }
+    append<kSpanGroups>(s.groups, &s.ngroups, gb, (uint32_t)tid, first, grp);
   }
   bool more = true;
   while (more) {
-    // spans: at most kSpans of each ray
+    // spans: at most kSpans of each long ray
     uint32_t bits = 0;
     if (k <= k1)
-      bits = k1 - k < 2 * span ? (k1 - k < span ? 1u : 3u)  // short: straight to the groups
-                               : may_act<kSpans, 1>(sl, k, k1, span, 0, it.L.smax, it.sbx, it.sby);
-    append<kSpans, 1>(s.spans, &s.nspans, bits, (uint32_t)tid, k, span, 0);
+      bits = k1 - k < 2 * span ? (k1 - k < span ? 1u : 3u)  // straight to the groups
+                               : may_act<kSpans>(line_of<kSuperLog>(it, r, span), k, k1, span,
+                                                 it.L.smax, it.sbx, it.sby);
+    append<kSpans>(s.spans, &s.nspans, bits, (uint32_t)tid, k, span);
     k += kSpans * span;
     more = __syncthreads_or(k <= k1);
     const int ns = s.nspans;
-    for (int b = 0; b < ns; b += kNTc) {
-      // groups: of at most one span per thread
-      uint32_t gb = 0, w = 0;
-      int ks = 0;
-      if (b + tid < ns) {
-        const uint32_t e = s.spans[b + tid];
-        w = e >> 24;
-        ks = (int)(e & 0xFFFFFFu);
-        const Line l = {s.line[0][w], s.line[1][w], s.line[2][w], s.line[3][w],
-                        s.line[4][w], s.line[5][w], s.line[6][w]};
-        gb = may_act<kSpanGroups, kParts>(l, ks, s.k1[w], grp, part, it.L.cmax, it.bx, it.by);
+    int b = 0;
+    do {
+      if (b < ns) {
+        // groups: of at most one span per thread
+        uint32_t gb = 0, w = 0;
+        int ks = 0;
+        if (b + tid < ns) {
+          const uint32_t e = s.spans[b + tid];
+          w = e >> 24;
+          ks = (int)(e & 0xFFFFFFu);
+          const Line l = {s.line[0][w], s.line[1][w], s.line[2][w], s.line[3][w],
+                          s.line[4][w], s.line[5][w], s.line[6][w]};
+          gb = may_act<kSpanGroups>(l, ks, s.k1[w], grp, it.L.cmax, it.bx, it.by);
+        }
+        append<kSpanGroups>(s.groups, &s.ngroups, gb, w, ks, grp);
+        __syncthreads();
       }
-      append<kSpanGroups, kParts>(s.pieces, &s.npieces, gb, w, ks, grp, part);
-      __syncthreads();
-      const int np = s.npieces;
-      for (int g = tid; g < np; g += kNTc) {
-        const uint32_t e = s.pieces[g];
+      const int ng = s.ngroups;
+      for (int g = tid; g < ng; g += kNTc) {
+        const uint32_t e = s.groups[g];
         const uint32_t w = e >> 24;
         const Ray q = {s.dx[w], s.dy[w], s.dz[w], s.end_cell[w], s.rK[w], s.k1[w]};
         const int ka = (int)(e & 0xFFFFFFu);
-        const int kb = min(ka + part - 1, q.k1);
+        const int kb = min(ka + grp - 1, q.k1);
         if (it.L.ub) test_samples<true, true>(it, q, ka, kb);
         else test_samples<false, kPair>(it, q, ka, kb);
       }
-      __syncthreads();  // the pieces have been read
-      if (tid == 0) s.npieces = 0;
+      __syncthreads();  // the groups have been read
+      if (tid == 0) s.ngroups = 0;
       __syncthreads();
-    }
+      b += kNTc;
+    } while (b < ns);
     if (tid == 0) s.nspans = 0;
     __syncthreads();
   }
@@ -543,7 +550,7 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
 template <int kRays>
 __global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
   __shared__ MarchShared<kRays> s;
-  if (threadIdx.x == 0) s.nspans = s.npieces = 0;
+  if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
   march_body<kRays, true>(it, blockIdx.x, s);
 }
@@ -563,7 +570,7 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
 
 __global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
   __shared__ MarchShared<kRaysBatch> s;
-  if (threadIdx.x == 0) s.nspans = s.npieces = 0;
+  if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
   const UnitFinder units(bt, kBRays);
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
@@ -601,8 +608,9 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || it.n <= 0) return err;
   TimedLaunch tl("k_clear_march", stream);
-  const int rays = it.L.ub ? kRaysBound : kRaysPlain;
-  hipLaunchKernelGGL(it.L.ub ? k_clear_march<kRaysBound> : k_clear_march<kRaysPlain>,
+  const bool few = it.L.ub || it.n <= kShortRays;
+  const int rays = few ? kRaysShort : kRaysPlain;
+  hipLaunchKernelGGL(few ? k_clear_march<kRaysShort> : k_clear_march<kRaysPlain>,
                      dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream, it);
   return hipGetLastError();
 }
