@@ -108,7 +108,7 @@ Consts make_consts(const emx_params& p) {
 
 // One buffer set: seven 4-byte layers, two byte layers, the clearing maxima per
 // block and superblock, the upper bound layer if the map keeps one, then
-// the fusion's four planes of fixed-point sums (8 bytes per cell each); each
+// the fusion's fixed-point sums (four words of 8 bytes per cell); each
 // 256-aligned.
 size_t set_layout(const emx_params& p, char* base, Layers* L) {
   const size_t C = (size_t)p.nx * (size_t)p.ny;
@@ -131,7 +131,6 @@ size_t set_layout(const emx_params& p, char* base, Layers* L) {
     L->smax = (float*)(base + 7 * l4 + 2 * l1 + align256(nb * 4));
     L->ub = p.upper_bound ? (float*)(base + 7 * l4 + 2 * l1 + lb) : nullptr;
     L->fx = (uint64_t*)(base + 7 * l4 + 2 * l1 + lb + (p.upper_bound ? l4 : 0));
-    L->fxs = (int64_t)(align256(C * 8) / 8);
   }
   return 7 * l4 + 2 * l1 + lb + (p.upper_bound ? l4 : 0) + kFxWords * align256(C * 8);
 }

@@ -45,12 +45,11 @@ struct Layers {
   float* ub;      // upper bound of the ground height (+inf: none), or null
   float* clr;     // per logical cell: h, or -inf if a ray may not clear it; or pairs of that
                   // and v (with the bound layer {NaN, bound} without an estimate) (transient)
-  uint64_t* fx;   // the fusion's fixed-point sums: kFxWords planes of fxs words, one word
-                  // per physical cell each; all zero between calls
-  int64_t fxs;    // plane stride in words
+  uint64_t* fx;   // the fusion's fixed-point sums: kFxWords words per physical cell; all
+                  // zero between calls
 };
 
-// Fixed-point sums of a cell, one word in each plane.  A value x enters as the
+// Fixed-point sums of a cell, its words side by side.  A value x enters as the
 // integer X = round(x * 2^S) (S: the item's shift for that sum), split as
 // X = hi * 2^32 + lo with 0 <= lo < 2^32; the hi and lo parts are summed in
 // separate words (hi as two's complement).  Integer addition is associative,

@@ -23,9 +23,14 @@
 //     terms are at these scales, are not added.  A segmented scan of the four
 //     words over the wave in front of the table cost 54 cross-lane moves per
 //     wave and four such scans in a row per thread: 15 against 9 us for a 300k
-//     frame, 144 against 80 us for a batch of 16 maps.
-//   - Adds the chunk's sums to the cells' words (FxWord planes) with integer
-//     atomics; the cells' tiles are flagged.
+//     frame, 144 against 80 us for a batch of 16 maps, each at the time.
+//   - Adds the chunk's sums to the cells' words (FxWord) with integer atomics,
+//     from a list of the slots taken, four neighbouring lanes to a cell: its
+//     words lie side by side, so a cell's atomics are one request, and the pass
+//     has no idle lanes.  With a plane for each word and a scan of all slots the
+//     atomics were a fourth to a third of the pass (300k points: 9.6 -> 6.9 us,
+//     4M: 42 -> 41, 16 maps: 80 -> 75; pass 2, which takes a cell's words in two
+//     loads, 21 -> 18 us for 16 maps).  The cells' tiles are flagged.
 //   - Where the call moves the map first, further workgroups of the same launch
 //     reset the entering cells, and points in them take the prior (a launch of
 //     its own took 3 us of every frame).
@@ -72,11 +77,13 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 // Chunks.  A frame alone takes one point per thread: its few workgroups wait for
 // each step of their chain, and four points per thread put four of each step in
 // a row.  Up to one 256-point chunk for each compute unit (20k points on 128 x
-// 128 cells: 4.2 against 5.9 us with 1024; 43k on 250 x 250: 4.5 against 6.7);
+// 128 cells: 4.6 against 5.9 us with 1024; 43k on 250 x 250: 4.9 against 6.7);
 // above, 1024-point chunks, whose table joins more of a cell's runs before the
 // map's atomics (300k on 400 x 400: 9.1 against 13.2 us with 256).  A batch has
 // workgroups to spare, and 256 threads with four points each leave more of them
-// in flight (16 maps, 4.6M points: 80 against 91 us).
+// in flight (16 maps, 4.6M points: 80 against 91 us; 512 threads with four points
+// 72 against 75, but 38 against 36 for a server's batch of 8 maps).  They take 128
+// registers, four waves to a SIMD; a bound of five spills (75 -> 108 us).
 constexpr int64_t kSmallFrame = 65536;
 constexpr int kThreadsLarge = 1024;
 constexpr int kThreadsBatch = 256;
@@ -84,13 +91,16 @@ constexpr int kPointsBatch = 4;
 
 struct AggTable {
   uint32_t key[kAggSlots];                   // physical cell + 1; 0 = free
-  unsigned long long v[kFxWords][kAggSlots];  // the words, as in the map's planes
+  // the words, a plane each; the stride keeps eight slots' words in distinct banks
+  unsigned long long v[kFxWords][kAggSlots + 8];
+  uint32_t used[kAggSlots];                   // the slots taken
+  int n;                                      // how many, over all chunks of the workgroup
 };
 
 __device__ __forceinline__ void add_to_map(const Item& it, uint32_t cell, const uint64_t (&v)[4]) {
 #pragma unroll
   for (int k = 0; k < kFxWords; ++k)
-    if (v[k]) atomicAdd((unsigned long long*)(it.L.fx + k * it.L.fxs + cell), v[k]);
+    if (v[k]) atomicAdd((unsigned long long*)(it.L.fx + kFxWords * (int64_t)cell + k), v[k]);
 }
 
 __device__ __forceinline__ uint32_t tile_of_cell(const Item& it, uint32_t cell) {
@@ -102,6 +112,7 @@ __device__ __forceinline__ uint32_t tile_of_cell(const Item& it, uint32_t cell) 
 // Zeroes the table (every thread of the block; the caller synchronises).
 template <int kT>
 __device__ __forceinline__ void agg_clear(AggTable& t) {
+  if (threadIdx.x == 0) t.n = 0;
   for (int s = threadIdx.x; s < kAggSlots; s += kT) {
     t.key[s] = 0u;
 #pragma unroll
@@ -110,10 +121,12 @@ __device__ __forceinline__ void agg_clear(AggTable& t) {
 }
 
 // One chunk of kT * kP points; a thread takes kP of them, kT apart, so that
-// consecutive points lie in consecutive lanes.  On entry the table is zero; it
-// is zero again on return.
+// consecutive points lie in consecutive lanes.  On entry the table is zero but
+// for n, which is n0; so it is again on return, with the next n0 (a count that
+// goes on needs no reset, and so no barrier between the flush and the next chunk's
+// first slot).
 template <int kT, int kP>
-__device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTable& tab) {
+__device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTable& tab, int& n0) {
   const int lane = threadIdx.x & 63;
   float x[kP], y[kP], z[kP];
 #pragma unroll
@@ -192,16 +205,28 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
     const uint64_t heads = __ballot(head);
     if (heads == 0) continue;
     uint32_t slot = kNoSlot;
+    bool fresh = false;
     if (head) {
       uint32_t h = (key * 2654435761u) >> (32 - kAggLog);
       for (int p = 0; p < kAggProbes; ++p) {
         const uint32_t was = atomicCAS(&tab.key[h], 0u, key + 1u);
         if (was == 0u || was == key + 1u) {
           slot = h;
+          fresh = was == 0u;
           break;
         }
         h = (h + 1u) & (kAggSlots - 1);
       }
+    }
+    const uint64_t fr = __ballot(fresh);
+    if (fr != 0) {  // slots taken: one atomic per wave
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&tab.n, __popcll(fr));
+      at = __builtin_amdgcn_readfirstlane(at) - n0;
+      if (fresh)
+        tab.used[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(fr >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)fr, 0u))] =
+            slot;
     }
     // ... and its lanes add to it, or straight to the map
     const uint64_t upto = heads & (~0ull >> (63 - lane));
@@ -218,17 +243,24 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
     }
   }
   __syncthreads();
-  // the table's cells to the map; the table back to zero
-  for (int s = threadIdx.x; s < kAggSlots; s += kT) {
-    const uint32_t k1 = tab.key[s];
-    if (k1 == 0u) continue;
-    const uint32_t c = k1 - 1u;
-    const uint64_t t[4] = {tab.v[0][s], tab.v[1][s], tab.v[2][s], tab.v[3][s]};
-    add_to_map(it, c, t);
-    it.fs.tcnt[tile_of_cell(it, c)] = 1u;
-    tab.key[s] = 0u;
-#pragma unroll
-    for (int k = 0; k < kFxWords; ++k) tab.v[k][s] = 0ull;
+  // the table's cells to the map, the table back to zero (the lanes that read a key
+  // are in the wave that resets it, and read it first)
+  const int n1 = tab.n;
+  const int items = (n1 - n0) * kFxWords;
+  n0 = n1;
+  for (int f = threadIdx.x; f < items; f += kT) {
+    const uint32_t s = tab.used[f / kFxWords];
+    const int k = f % kFxWords;
+    const uint32_t c = tab.key[s] - 1u;
+    const unsigned long long t = tab.v[k][s];
+    if (t) {
+      atomicAdd((unsigned long long*)(it.L.fx + kFxWords * (int64_t)c + k), t);
+      tab.v[k][s] = 0ull;
+    }
+    if (k == 0) {
+      it.fs.tcnt[tile_of_cell(it, c)] = 1u;
+      tab.key[s] = 0u;
+    }
   }
   __syncthreads();
 }
@@ -244,10 +276,8 @@ constexpr int kCellsPerLane = kTileCells / 64;  // 4: lane l owns cells l, l + 6
 __device__ __forceinline__ void update_cell(const Item& it, int64_t cell, int64_t whi,
                                             uint64_t wlo, int64_t zhi, uint64_t zlo, float h0,
                                             float v0) {
-  uint64_t* f = it.L.fx + cell;
-  const int64_t fs = it.L.fxs;
-#pragma unroll
-  for (int k = 0; k < kFxWords; ++k) f[k * fs] = 0u;
+  ulonglong2* f = reinterpret_cast<ulonglong2*>(it.L.fx + kFxWords * cell);
+  f[0] = f[1] = make_ulonglong2(0u, 0u);
   const double sw = fx_value(whi, wlo, it.fxw);
   const double srz = fx_value(zhi, zlo, it.fxz);
   const float acc_w = (float)sw;
@@ -278,12 +308,10 @@ __device__ __forceinline__ void tile_body_group(const Item& it, int64_t t) {
   const int py = (ty << kTileLogY) + (l >> kTileLogX);
   if (px >= it.c.nx || py >= it.c.ny) return;
   const int64_t cell = (int64_t)py * it.c.nx + px;
-  const int64_t fs = it.L.fxs;
-  const int64_t whi = (int64_t)it.L.fx[kFxWhi * fs + cell];
-  const uint64_t wlo = it.L.fx[kFxWlo * fs + cell];
-  if (whi == 0 && wlo == 0) return;  // no accepted point: every term is positive
-  update_cell(it, cell, whi, wlo, (int64_t)it.L.fx[kFxZhi * fs + cell],
-              it.L.fx[kFxZlo * fs + cell], it.L.h[cell], it.L.v[cell]);
+  const ulonglong2* f = reinterpret_cast<const ulonglong2*>(it.L.fx + kFxWords * cell);
+  const ulonglong2 w = f[0], z = f[1];
+  if (w.x == 0 && w.y == 0) return;  // no accepted point: every term is positive
+  update_cell(it, cell, (int64_t)w.x, w.y, (int64_t)z.x, z.y, it.L.h[cell], it.L.v[cell]);
 }
 
 // Tile t, by one wave: lane l takes cells l + 64 i of the tile (two rows of 32
@@ -300,49 +328,40 @@ __device__ __forceinline__ void tile_body_wave(const Item& it, int64_t t) {
   if (lane == 0) it.fs.tcnt[t] = 0u;  // zero again for the next call
   const int tx = (int)(t % it.tiles_x);
   const int ty = (int)(t / it.tiles_x);
-  const int64_t fs = it.L.fxs;
   int64_t cell[kCellsPerLane];
-  bool in[kCellsPerLane];
-  int64_t whi[kCellsPerLane];
-  uint64_t wlo[kCellsPerLane];
+  ulonglong2 w[kCellsPerLane];
 #pragma unroll
   for (int i = 0; i < kCellsPerLane; ++i) {
     const int c = lane + 64 * i;
     // the cell, physical (tiles cover the ring layout as stored)
     const int px = (tx << kTileLogX) + (c & (kTileW - 1));
     const int py = (ty << kTileLogY) + (c >> kTileLogX);
-    in[i] = px < it.c.nx && py < it.c.ny;
-    cell[i] = in[i] ? (int64_t)py * it.c.nx + px : 0;
-    whi[i] = 0;
-    wlo[i] = 0;
-    if (in[i]) {
-      whi[i] = (int64_t)it.L.fx[kFxWhi * fs + cell[i]];
-      wlo[i] = it.L.fx[kFxWlo * fs + cell[i]];
-    }
+    cell[i] = (int64_t)py * it.c.nx + px;
+    w[i] = make_ulonglong2(0u, 0u);
+    if (px < it.c.nx && py < it.c.ny)
+      w[i] = reinterpret_cast<const ulonglong2*>(it.L.fx + kFxWords * cell[i])[0];
   }
   // cells with an accepted point (every term is positive): the rest of
   // their sums and their prior, all loads issued before any is used
   bool hit[kCellsPerLane];
-  int64_t zhi[kCellsPerLane];
-  uint64_t zlo[kCellsPerLane];
+  ulonglong2 z[kCellsPerLane];
   float h0[kCellsPerLane], v0[kCellsPerLane];
 #pragma unroll
   for (int i = 0; i < kCellsPerLane; ++i) {
-    hit[i] = in[i] && (whi[i] != 0 || wlo[i] != 0);
-    zhi[i] = 0;
-    zlo[i] = 0;
+    hit[i] = w[i].x != 0 || w[i].y != 0;
+    z[i] = make_ulonglong2(0u, 0u);
     h0[i] = 0.0f;
     v0[i] = 1.0f;
     if (hit[i]) {
-      zhi[i] = (int64_t)it.L.fx[kFxZhi * fs + cell[i]];
-      zlo[i] = it.L.fx[kFxZlo * fs + cell[i]];
+      z[i] = reinterpret_cast<const ulonglong2*>(it.L.fx + kFxWords * cell[i])[1];
       h0[i] = it.L.h[cell[i]];
       v0[i] = it.L.v[cell[i]];
     }
   }
 #pragma unroll
   for (int i = 0; i < kCellsPerLane; ++i)
-    if (hit[i]) update_cell(it, cell[i], whi[i], wlo[i], zhi[i], zlo[i], h0[i], v0[i]);
+    if (hit[i])
+      update_cell(it, cell[i], (int64_t)w[i].x, w[i].y, (int64_t)z[i].x, z[i].y, h0[i], v0[i]);
 }
 
 // ------------------------------------------------------- wall rule: counts
@@ -435,16 +454,18 @@ __global__ __launch_bounds__(kT) void k_fuse_chunk(Item it, uint32_t chunks) {
   }
   agg_clear<kT>(tab);
   __syncthreads();
-  chunk_body<kT, 1>(it, blockIdx.x, tab);
+  int n0 = 0;
+  chunk_body<kT, 1>(it, blockIdx.x, tab, n0);
 }
 
 __global__ __launch_bounds__(kNT2) void k_fuse_tile(Item it) { tile_body_group(it, blockIdx.x); }
 
-__global__ __launch_bounds__(kThreadsBatch) void k_fuse_chunk_b(const Batch* bt) {
+__global__ __launch_bounds__(kThreadsBatch, 4) void k_fuse_chunk_b(const Batch* bt) {
   __shared__ AggTable tab;
   agg_clear<kThreadsBatch>(tab);
   __syncthreads();
   const UnitFinder units(bt, kBChunk), moves(bt, kBMove);
+  int n0 = 0;
   for (int64_t w = blockIdx.x; w < moves.total() + units.total(); w += gridDim.x) {
     int64_t unit;
     if (w < moves.total()) {
@@ -452,7 +473,7 @@ __global__ __launch_bounds__(kThreadsBatch) void k_fuse_chunk_b(const Batch* bt)
       move_body<kThreadsBatch>(bt->items[i], unit);
     } else {
       const int i = units.find(w - moves.total(), unit);
-      chunk_body<kThreadsBatch, kPointsBatch>(bt->items[i], unit, tab);
+      chunk_body<kThreadsBatch, kPointsBatch>(bt->items[i], unit, tab, n0);
     }
   }
 }

@@ -3,7 +3,8 @@ fused cell: the points' float32 terms, their integers at the call's shifts, the
 integer sums, and the float32 update from them.  Here the sums are formed in
 Python integers from numpy float32 terms and the cells are compared as bits, at
 frame sizes around the chunks of pass 1 (256 points in small frames, 1024 in
-larger ones, and the batched call's), with one cell taking a whole chunk, with
+larger ones, and the batched call's, also with one workgroup for all chunks),
+with one cell taking a whole chunk, with
 more distinct cells than a chunk's table has slots, over the range of terms
 (low words, rounding, negative heights, a term below half a unit), and after a
 move in the same call."""
@@ -110,11 +111,11 @@ CASES = [("rings", 1), ("rings", 255), ("rings", 256), ("rings", 257), ("rings",
          ("rings", 65536), ("rings", 65537), ("range", 5000)]
 
 
-@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("batched", [False, True, '{"grid_chunk": 1}'])
 @pytest.mark.parametrize("kind,n", CASES)
 def test_fused_cells_bitwise(dev, kind, n, batched):
     from paper_2204_12876_amd import BatchEntry, ElevationMap, PipelineBatch, _emx
-    print("[case] fusion sums", kind, n, "batched" if batched else "plain", flush=True)
+    print("[case] fusion sums", kind, n, "batched" if batched else "plain", batched, flush=True)
     rng = np.random.default_rng(n + len(kind))
     side, r = 300, 0.05
     params = dict(nx=side, ny=side - 11, resolution=r, noise_alpha=1e-4 if kind != "range" else 3e-3,
@@ -137,7 +138,7 @@ def test_fused_cells_bitwise(dev, kind, n, batched):
     cell = torch.full((n,), -7, dtype=torch.int32, device=dev)
     acc = torch.full((n,), 7, dtype=torch.uint8, device=dev)
     if batched:
-        pb = PipelineBatch(device=dev)
+        pb = PipelineBatch(None if batched is True else batched, device=dev)
         pb.run([BatchEntry(m, *pts, pose, 900, center=(cx, cy), out_cell=cell, out_accept=acc,
                            stages=_emx.STAGE_MOVE | _emx.STAGE_FUSE)])
     else:
