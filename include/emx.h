@@ -405,8 +405,8 @@ emx_status emx_import_state(emx_map* map, const void* d_src, void* stream);
  *     run in the same order on that map: the per-point and per-cell
  *     arithmetic is the same, the fusion's sums are integer sums (any order
  *     gives the same bits), and every float32 sum has a fixed order.
- *   - The tuning selects only launch geometry (persistent grid sizes) and the
- *     clearing segment length.  It never changes results.
+ *   - The tuning selects only launch geometry (grid sizes).  It never changes
+ *     results.
  *   - Every map option of the plain calls is served: time and outlier
  *     variance, the wall rule (its counts take scratch, see
  *     emx_batch_scratch_bytes), the upper bound layer and the exclusion area. */
@@ -432,11 +432,11 @@ typedef struct {
 } emx_batch_item;
 
 /* Create a batch executor.  tuning_json: NULL, or a flat JSON object whose
- * optional integer keys are the persistent grid sizes in workgroups
- * ("grid_move", "grid_chunk", "grid_tile", "grid_setup", "grid_march",
- * "grid_cells"), the clearing segment length "seg" (1..255) and "graph" (0
- * runs the launches directly instead of a cached graph).  Other keys are
- * ignored.
+ * optional integer keys are the largest grid sizes in workgroups
+ * ("grid_move", without effect since moves run with the chunks, "grid_chunk",
+ * "grid_tile", "grid_setup", "grid_march", "grid_cells"), "seg" (1..255),
+ * which enters only the scratch sizes below, and "graph" (0 runs the launches
+ * directly instead of a cached graph).  Other keys are ignored.
  * The executor allocates two pinned host tables and a capture stream. */
 emx_status emx_batch_create(const char* tuning_json, emx_batch** out);
 emx_status emx_batch_destroy(emx_batch* batch); /* waits for its last batch */

@@ -1,9 +1,10 @@
 """Autotuner of the batched executor's launch geometry.
 
-The batched kernels are persistent: each stage runs a fixed number of
-workgroups that walk the batch's work units.  The tuning picks those counts
-per stage and the clearing segment length (ray samples per queued entry).  It
-never changes results: every candidate yields the same bits.
+Each batched stage runs a fixed number of workgroups that take the batch's work
+units in turn.  The tuning picks those counts per stage ("grid_move" and "seg" no
+longer reach a launch and are kept for their form: moves run with the chunks, and
+clearing's lists are in LDS).  It never changes results: every candidate yields
+the same bits.
 
 Search: coordinate descent from the library defaults.  Each knob in turn is
 set to each of its candidate values with the others held, the fastest is

@@ -25,7 +25,7 @@ __device__ __forceinline__ int64_t xcd_unit(int64_t b, int64_t n) {
   return x * q + (x < r ? x : r) + b / kXcds;
 }
 
-// The k-th unit of workgroup b in a persistent launch of g workgroups over n
+// The k-th unit of workgroup b in a launch of g workgroups over n
 // units, or -1 past its share.  With g a multiple of 8, the g/8 workgroups of
 // XCD x walk that XCD's contiguous range in turn; otherwise units go round
 // robin (b, b + g, ...).

@@ -7,7 +7,7 @@
 //
 // Every kernel body works on one `Item`: one map with one frame.  It is called
 // either from a plain launch (the Item passed by value, one workgroup per unit
-// of work) or from a batched persistent launch that looks its units up in a
+// of work) or from a batched launch that looks its units up in a
 // device-resident `Batch` table.  The arithmetic is the same code either way,
 // so a map's results are identical alone and in a batch.
 #pragma once

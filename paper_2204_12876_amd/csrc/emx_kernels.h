@@ -2,7 +2,7 @@
 //
 // Plain launchers take one Item by value and launch one workgroup per unit of
 // work.  Batched launchers take a device-resident Batch and a fixed grid of
-// persistent workgroups, so that a captured graph can be replayed for any
+// workgroups that take units in turn, so that a captured graph can be replayed for any
 // batch that fits the table.
 #pragma once
 
