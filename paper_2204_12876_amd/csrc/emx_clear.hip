@@ -20,7 +20,7 @@
 //   - Loads come in two rounds: validity, then the update time, normal z, height
 //     and variance of valid cells (or the upper bound of invalid ones).
 //   - The caller's removed-cell mask is zeroed here.
-// march: one workgroup per 64, 128 or (in a batch) 256 rays.
+// march: one workgroup per 32, 64, 128 or (in a batch) 256 rays.
 //   - The ray is cut into groups of Item::grp consecutive samples, at most 7
 //     cells of travel, and spans of four groups.  Lower bounds of a group's
 //     cells and height come from the ray's line, widened by more than the
@@ -72,11 +72,16 @@ constexpr int kNTc = 256;
 // 128 would leave fewer than 4 workgroups to a CU (a whole call, 60k rays on
 // 200 x 200: 12.0 against 14.6 us; 100k on 2000 x 2000: 34.6 against 38.9; 200k:
 // the same; 300k on 400 x 400: 18.5 against 17) and with an upper bound layer,
-// where most samples over unseen ground act (400 x 400: 22 against 27 us).
+// where most samples over unseen ground act (400 x 400: 22 against 27 us).  32 for
+// the fewest, where 64 leave compute units idle (13k rays on 1770 x 1979: 21.9
+// against 23.7 us; 40k on 847 x 1070: 15.3 against 16.2; 60k on 200 x 200: 12.6
+// against 11.4).
 constexpr int kRaysPlain = 128;
 constexpr int kRaysShort = 64;
+constexpr int kRaysFew = 32;
 constexpr int kRaysBatch = 256;
-constexpr int64_t kShortRays = 1 << 17;  // the line: 4 x 256 workgroups of 128
+constexpr int64_t kShortRays = 1 << 17;  // 4 x 256 workgroups of 128
+constexpr int64_t kFewRays = 3 << 14;    // 6 x 256 workgroups of 32
 // Maps up to this size load a cell's fields without waiting for its validity: the
 // 16 bytes that most cells then load for nothing cost less than the round trip
 // (128 x 128: 6.1 -> 5.1 us, 400 x 400 with the bound: 6.6 -> 5.5 us).
@@ -608,10 +613,14 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || it.n <= 0) return err;
   TimedLaunch tl("k_clear_march", stream);
-  const bool few = it.L.ub || it.n <= kShortRays;
-  const int rays = few ? kRaysShort : kRaysPlain;
-  hipLaunchKernelGGL(few ? k_clear_march<kRaysShort> : k_clear_march<kRaysPlain>,
-                     dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream, it);
+  const auto go = [&](auto kernel, int rays) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream,
+                       it);
+  };
+  if (it.L.ub) go(k_clear_march<kRaysShort>, kRaysShort);
+  else if (it.n <= kFewRays) go(k_clear_march<kRaysFew>, kRaysFew);
+  else if (it.n <= kShortRays) go(k_clear_march<kRaysShort>, kRaysShort);
+  else go(k_clear_march<kRaysPlain>, kRaysPlain);
   return hipGetLastError();
 }
 

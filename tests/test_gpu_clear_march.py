@@ -55,6 +55,7 @@ CASES = [
     (333, 290, 1.0, (150.0, 140.0), 330, 4000, 0.02, False),   # few cells to remove
     (500, 500, 1.0, (250.0, 250.0), 245, 1024, 0.8, True),     # lists fill up
     (3, 3, 1.0, (1.5, 1.5), 5, 1, 1.0, False),
+    (200, 200, 1.0, (100.0, 100.0), 98, (3 << 14) + 1, 0.8, True),  # workgroups of 64 rays
     (200, 200, 1.0, (100.0, 100.0), 98, (1 << 17) + 1, 0.8, True),  # workgroups of 128 rays
 ]
 
