@@ -125,14 +125,14 @@ def frame_bytes(n: float, C: float, touched: float, updated: float, entering: fl
         cell they hit (8 B);
       fuse_tile: prior h, v read and h, v, t_upd, valid written for each
         updated cell (8 + 13 B);
-      clear_setup: the points, and h, t_upd, valid per cell for the block
-        maxima (9 B); clear_march: each cell's h, v, t_upd, valid and normal
+      clear_setup: h, t_upd, valid per cell for the block maxima (9 B);
+      clear_march: the points, and each cell's h, v, t_upd, valid and normal
         read once (25 B);
       cells: normals and traversability from h, valid (5 B in, 16 B out);
       move (a frame whose centre cell changes): the ring turns and the cells
       entering the map are written once (29 B each)."""
     return {"fuse_chunk": 12 * n + 8 * touched, "fuse_tile": 21 * updated,
-            "clear_setup": 12 * n + 9 * C, "clear_march": 25 * C, "cells": 21 * C,
+            "clear_setup": 9 * C, "clear_march": 12 * n + 25 * C, "cells": 21 * C,
             "move": 29 * entering}
 
 
