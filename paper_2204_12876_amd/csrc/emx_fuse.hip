@@ -50,11 +50,11 @@ namespace {
 
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;   // lanes without an accepted point
 
-// The integer X = round(x * 2^S) (ties to even) of a finite float32 x, as
-// X = hi * 2^32 + lo with 0 <= lo < 2^32.  Every step is exact in float64: x has
-// 24 significant bits and the choice of S keeps |X| < 2^94.
-__device__ __forceinline__ void fx_split(float x, int S, int64_t& hi, uint64_t& lo) {
-  const double d = rint(ldexp((double)x, S));
+// The integer X = round(x * 2^S) (ties to even) of an x with 24 significant bits,
+// as X = hi * 2^32 + lo with 0 <= lo < 2^32.  Every step is exact in float64: the
+// choice of S keeps |X| < 2^94.
+__device__ __forceinline__ void fx_split(double x, int S, int64_t& hi, uint64_t& lo) {
+  const double d = rint(ldexp(x, S));
   const double h = floor(d * 0x1p-32);
   hi = (int64_t)h;
   lo = (uint64_t)(uint32_t)fma(h, -0x1p32, d);
@@ -191,7 +191,10 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
         fx_split(w, it.fxw, hi, v[kFxWlo]);
         v[kFxWhi] = (uint64_t)hi;
         if (hi == 0 && v[kFxWlo] == 0) v[kFxWlo] = 1;  // an accepted point adds at least one unit
-        fx_split(w * e[j].rz, it.fxz, hi, v[kFxZlo]);
+        // a term past float32's range counts as 2^128, the power above it (w itself
+        // is bounded by 1/sp2 of the nearest point, which is in range)
+        const float u = w * e[j].rz;
+        fx_split(isinf(u) ? copysign(0x1p128, (double)u) : (double)u, it.fxz, hi, v[kFxZlo]);
         v[kFxZhi] = (uint64_t)hi;
       }
     }
