@@ -115,6 +115,12 @@ __device__ __forceinline__ void atomic_min_f32(float* a, float v) {
   else atomicMax(reinterpret_cast<unsigned int*>(a), __float_as_uint(v));
 }
 
+// Whether q lowers the bound b, in the order of atomic_min_f32: of the two zeros the
+// negative one is the lower.
+__device__ __forceinline__ bool lowers(float q, float b) {
+  return q < b || (__float_as_uint(q) == 0x80000000u && __float_as_uint(b) == 0u);
+}
+
 // A cell can be removed only if it is valid, older than the minimum age and
 // has a normal (its validity, update time and normal z given).
 __device__ __forceinline__ bool clearable(const Item& it, uint8_t valid, int32_t t_upd, float nz) {
@@ -191,7 +197,8 @@ __device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step) 
   const float tx = r.dx * scale, ty = r.dy * scale;
   const float ex = (fabsf(ox) + fabsf(tx)) * 0x1p-19f;
   const float ey = (fabsf(oy) + fabsf(ty)) * 0x1p-19f;
-  const float ez = (fabsf(oz) + fabsf(r.dz)) * 0x1p-19f;
+  // (the least denormal: a bound of -0.0 must not look equal to a maximum of 0.0)
+  const float ez = fmaf(fabsf(oz) + fabsf(r.dz), 0x1p-19f, 0x1p-149f);
   Line l;
   l.dx = tx * rk;
   l.dy = ty * rk;
@@ -308,7 +315,7 @@ __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int k
     for (int u = 0; u < kUnroll; ++u) {
       const float hd = rec[u] - qz[u];
       if (cand[u] & (hd > 0.0f) & (!kPair || (hd * hd) > v[u])) remove |= 1u << u;
-      if (kBound && (cand[u] & isnan(rec[u]) & (qz[u] < v[u]))) bound |= 1u << u;
+      if (kBound && (cand[u] & isnan(rec[u]) & lowers(qz[u], v[u]))) bound |= 1u << u;
     }
     while (remove | bound) {
       const int u = __builtin_ctz(remove | bound);
@@ -323,7 +330,7 @@ __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int k
         const float an2dd = it.c.an2 * ((r.dx * r.dx + r.dy * r.dy) + r.dz * r.dz);
         const float dot = (r.dx * it.L.nx[pc] + r.dy * it.L.ny[pc]) + r.dz * it.L.nz[pc];
         if (below && (dot * dot) > an2dd) clear_cell(it, pc, q.iy * it.c.nx + q.ix);
-      } else if (q.qz < it.L.ub[pc]) {  // another ray may have lowered it further
+      } else if (lowers(q.qz, it.L.ub[pc])) {  // another ray may have lowered it further
         atomic_min_f32(it.L.ub + pc, q.qz);
       }
       remove &= ~(1u << u);
