@@ -179,7 +179,7 @@ def make_frame(x_ptr: int, y_ptr: int, z_ptr: int, n: int, pose, t_ms: int) -> F
     f = Frame.from_buffer_copy(
         _FRAME_HEAD + np.asarray(pose, dtype=np.float64).reshape(12).tobytes() + _FRAME_TAIL)
     f.x, f.y, f.z = x_ptr, y_ptr, z_ptr
-    f.n = n
+    f.n = int(n)
     f.t_ms = int(t_ms)
     return f
 
