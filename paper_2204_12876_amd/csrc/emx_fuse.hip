@@ -246,8 +246,7 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
     }
   }
   __syncthreads();
-  // the table's cells to the map, the table back to zero (the lanes that read a key
-  // are in the wave that resets it, and read it first)
+  // the table's cells to the map, the table back to zero
   const int n1 = tab.n;
   const int items = (n1 - n0) * kFxWords;
   n0 = n1;
@@ -260,6 +259,10 @@ __device__ __forceinline__ void chunk_body(const Item& it, int64_t chunk, AggTab
       atomicAdd((unsigned long long*)(it.L.fx + kFxWords * (int64_t)c + k), t);
       tab.v[k][s] = 0ull;
     }
+    // a slot's four lanes lie in one wave: all have read its key before the first of
+    // them resets it (order for the compiler; no instructions)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     if (k == 0) {
       it.fs.tcnt[tile_of_cell(it, c)] = 1u;
       tab.key[s] = 0u;
