@@ -30,9 +30,9 @@
 //     first, the same way, against the superblocks.  This is exact pruning: it
 //     never skips a sample that could act, and costs no sample evaluation.
 //   - Three phases hand lists in LDS to each other, so that every phase has an
-//     equal share for each thread whatever the rays' lengths: spans (one ray
-//     per thread), groups (one surviving span per thread; rays of one span take
-//     theirs in the first phase), samples (one surviving group per thread).  One
+//     equal share for each thread whatever the rays' lengths: spans (one ray, or a
+//     part of one, per thread), groups (one surviving span per thread; rays of one
+//     span take theirs in the first phase), samples (one surviving group per thread).  One
 //     thread per ray through all phases was 1.5 times slower on 400 x 400 maps:
 //     the longest ray's chain of lookups, a microsecond each, set the time.
 //   - Every sample of a surviving group is evaluated exactly and compared
@@ -73,21 +73,38 @@ constexpr int kNTc = 256;
 // 200 x 200: 12.0 against 14.6 us; 100k on 2000 x 2000: 34.6 against 38.9; 200k:
 // the same; 300k on 400 x 400: 18.5 against 17) and with an upper bound layer,
 // where most samples over unseen ground act (400 x 400: 22 against 27 us).  32 for
-// the fewest, where 64 leave compute units idle (13k rays on 1770 x 1979: 21.9
-// against 23.7 us; 40k on 847 x 1070: 15.3 against 16.2; 60k on 200 x 200: 12.6
-// against 11.4).
+// the fewest, where 64 leave compute units idle: 32 against 64, 13k rays on 1770 x
+// 1979 21.9 against 23.7 us, 40k on 847 x 1070 15.3 against 16.2, but 60k on 200 x 200
+// 12.6 against 11.4.  (With consecutive rays; the other form below gains the most at
+// the same widths.)
 constexpr int kRaysPlain = 128;
 constexpr int kRaysShort = 64;
 constexpr int kRaysFew = 32;
 constexpr int kRaysBatch = 256;
 constexpr int64_t kShortRays = 1 << 17;  // 4 x 256 workgroups of 128
 constexpr int64_t kFewRays = 3 << 14;    // 6 x 256 workgroups of 32
+// Where rays can be long (samples to a map side) and the workgroups are few, the
+// march takes its other form (kLong): a workgroup's rays come from several parts of
+// the frame, since a LiDAR's beam is a run of rays of one length and a workgroup that
+// holds only long ones sets the march's time; and all of its threads share its rays'
+// spans, where a thread to each ray left the others waiting for rounds of eight spans.
+// A whole call, one form against the other: 13k LiDAR rays on 1770 x 1979 cells 27.6
+// -> 23.3 us, 60k on 2000 x 2000 35.7 -> 29.5, 178k on 827 x 749 30.4 -> 22.5, 300k on
+// 1500 x 1500 46.3 -> 35.0, 600k on 2000 x 2000 68 -> 61.  With more workgroups than
+// the chip holds they balance each other, and consecutive rays share more of their
+// lookups (spread against consecutive: 4M on 2000 x 2000 237 against 229; 800k camera
+// and LiDAR rays on 1200 x 1000 34 against 32; 500k on 520 x 520 28 against 25), and
+// where a ray has few spans to share the other form's one barrier more shows (300k on
+// 400 x 400: 18.8 against 18.4; with the bound 24.0 against 23.1).
+constexpr double kLongRay = 512.0;     // samples to the longer side
+constexpr double kSpreadRays = 384.0;  // rays to one of those samples
+constexpr int kRunDense = 32;          // runs; 16 share fewer lookups (100k rays 5% slower)
 // Maps up to this size load a cell's fields without waiting for its validity: the
 // 16 bytes that most cells then load for nothing cost less than the round trip
 // (128 x 128: 6.1 -> 5.1 us, 400 x 400 with the bound: 6.6 -> 5.5 us).
 constexpr int64_t kAllCells = 1 << 18;
 constexpr int kSpanGroups = 4;  // groups in a span
-constexpr int kSpans = 8;       // spans of a ray looked up together
+constexpr int kSpans = 8;       // spans of a ray that a thread looks up together
 
 // A ray: direction from the sensor origin (Pose32::t), 1/K correctly rounded
 // in double, the last sample that can lie in the map, and the end point's cell.
@@ -424,14 +441,16 @@ __device__ __forceinline__ void setup_body(const Item& it, int unit, float* s_ma
 
 // ------------------------------------------------------------------- march
 // Arrays by field: lanes that read different rays then meet different banks.
-template <int kRays>
+template <int kRays, int kParts>
 struct MarchShared {
   float dx[kRays], dy[kRays], dz[kRays];
   double rK[kRays];
   int k1[kRays], end_cell[kRays];
   float line[7][kRays];  // of the groups, for rays of more than one span
+  // the samples of such rays, none for others (where several threads share a ray)
+  int from[kParts > 1 ? kRays : 1], to[kParts > 1 ? kRays : 1];
   // entries: ray << 24 | first sample
-  uint32_t spans[kSpans * kRays];
+  uint32_t spans[kSpans * kRays * kParts];
   uint32_t groups[kSpanGroups * (kRays + kNTc)];
   int nspans, ngroups;
 };
@@ -439,8 +458,9 @@ struct MarchShared {
 // Appends the steps of each lane's `bits` (kN of them) to a list with room for
 // them, by one LDS atomic per wave (an atomic per lane with its own count would
 // be expanded into a loop over the lanes).  The j-th steps of all lanes come
-// together: neighbouring rays, whose lookups share cache lines.  Every lane of
-// the wave calls it.
+// together: neighbouring rays, whose lookups share cache lines.  The lanes of a
+// wave that call it are those from lane 0 up to some lane: all, or in workgroups of
+// 32 rays the first half in the march's first phase.
 template <int kN>
 __device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, uint32_t ray, int k,
                                        int step) {
@@ -466,16 +486,34 @@ __device__ __forceinline__ void append(uint32_t* list, int* n, uint32_t bits, ui
   }
 }
 
-// Rays [kRays unit, kRays unit + kRays) of the item.  The counts in s are zero
-// on entry and on return (every thread passes a barrier after they were reset).
-template <int kRays, bool kPair>
-__device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchShared<kRays>& s) {
+// The ray in slot `slot` of workgroup `unit` of `units`, which takes runs of kRun
+// consecutive rays from kRays / kRun parts of the frame.
+template <int kRun>
+__device__ __forceinline__ int64_t spread_ray(int64_t unit, int64_t units, int slot) {
+  return ((int64_t)(slot / kRun) * units + unit) * kRun + slot % kRun;
+}
+
+// Threads that share the spans of a ray.
+template <int kRays, bool kLong>
+constexpr int parts_of() {
+  return kLong ? kNTc / kRays : 1;
+}
+
+// The rays of workgroup `unit` of the item: consecutive ones, a thread to the spans
+// of each; or with kLong runs from all over the frame (spread_ray, `units`
+// workgroups), all threads sharing their spans.  The counts in s are zero on entry
+// and on return (every thread passes a barrier after they were reset).
+template <int kRays, bool kLong, bool kPair>
+__device__ __forceinline__ void march_body(const Item& it, int64_t unit, int64_t units,
+                                           MarchShared<kRays, parts_of<kRays, kLong>()>& s) {
+  constexpr int kParts = parts_of<kRays, kLong>();
   const int tid = threadIdx.x;
-  const int64_t i = unit * kRays + tid;
   const int grp = it.grp, span = kSpanGroups * it.grp;
   Ray r;
   int k = 1, k1 = 0;  // the ray's first sample that no span covers yet, its last
   if (tid < kRays) {
+    const int64_t i =
+        kLong ? spread_ray<kRunDense>(unit, units, tid) : unit * kRays + tid;
     uint32_t gb = 0;
     int first = 1;
     if (i < it.n && ray_of(it, i, r, first)) {
@@ -502,17 +540,29 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, MarchSh
       }
     }
     append<kSpanGroups>(s.groups, &s.ngroups, gb, (uint32_t)tid, first, grp);
+    if (kParts > 1) {
+      s.from[tid] = k;
+      s.to[tid] = k1;
+    }
+  }
+  int slot = tid;
+  if (kParts > 1) {
+    __syncthreads();
+    slot = tid % kRays;
+    k = s.from[slot] + tid / kRays * (kSpans * span);
+    k1 = s.to[slot];
+    if (k <= k1) r = Ray{s.dx[slot], s.dy[slot], s.dz[slot], 0, s.rK[slot], k1};
   }
   bool more = true;
   while (more) {
-    // spans: at most kSpans of each long ray
+    // spans: at most kSpans of each long ray's share
     uint32_t bits = 0;
     if (k <= k1)
       bits = k1 - k < 2 * span ? (k1 - k < span ? 1u : 3u)  // straight to the groups
                                : may_act<kSpans>(line_of<kSuperLog>(it, r, span), k, k1, span,
                                                  it.L.smax, it.sbx, it.sby);
-    append<kSpans>(s.spans, &s.nspans, bits, (uint32_t)tid, k, span);
-    k += kSpans * span;
+    append<kSpans>(s.spans, &s.nspans, bits, (uint32_t)slot, k, span);
+    k += kParts * kSpans * span;
     more = __syncthreads_or(k <= k1);
     const int ns = s.nspans;
     int b = 0;
@@ -562,12 +612,12 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
 
 // The maxima are read through the caches: they are small and shared by every
 // workgroup, and staging them in LDS per workgroup costs more than it saves.
-template <int kRays>
+template <int kRays, bool kLong>
 __global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
-  __shared__ MarchShared<kRays> s;
+  __shared__ MarchShared<kRays, parts_of<kRays, kLong>()> s;
   if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
-  march_body<kRays, true>(it, blockIdx.x, s);
+  march_body<kRays, kLong, true>(it, blockIdx.x, gridDim.x, s);
 }
 
 __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
@@ -584,14 +634,14 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
 }
 
 __global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
-  __shared__ MarchShared<kRaysBatch> s;
+  __shared__ MarchShared<kRaysBatch, 1> s;
   if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
   const UnitFinder units(bt, kBRays);
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
     int64_t unit;
     const int i = units.find(w, unit);
-    march_body<kRaysBatch, false>(bt->items[i], unit, s);
+    march_body<kRaysBatch, false, false>(bt->items[i], unit, 0, s);
   }
 }
 
@@ -623,14 +673,19 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || it.n <= 0) return err;
   TimedLaunch tl("k_clear_march", stream);
+  const int side = it.c.nx > it.c.ny ? it.c.nx : it.c.ny;
+  const double samples = (double)side / (double)it.c.inv_r * (double)it.c.inv_step;
+  const bool far = samples >= kLongRay && (double)it.n <= kSpreadRays * samples;
   const auto go = [&](auto kernel, int rays) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream,
                        it);
   };
-  if (it.L.ub) go(k_clear_march<kRaysShort>, kRaysShort);
-  else if (it.n <= kFewRays) go(k_clear_march<kRaysFew>, kRaysFew);
-  else if (it.n <= kShortRays) go(k_clear_march<kRaysShort>, kRaysShort);
-  else go(k_clear_march<kRaysPlain>, kRaysPlain);
+  if (it.L.ub || (it.n > kFewRays && it.n <= kShortRays))
+    go(far ? k_clear_march<kRaysShort, true> : k_clear_march<kRaysShort, false>, kRaysShort);
+  else if (it.n <= kFewRays)
+    go(far ? k_clear_march<kRaysFew, true> : k_clear_march<kRaysFew, false>, kRaysFew);
+  else
+    go(far ? k_clear_march<kRaysPlain, true> : k_clear_march<kRaysPlain, false>, kRaysPlain);
   return hipGetLastError();
 }
 
