@@ -107,16 +107,16 @@ Consts make_consts(const emx_params& p) {
 }
 
 // One buffer set: seven 4-byte layers, two byte layers, the clearing maxima per
-// block and superblock, the upper bound layer if the map keeps one, then
-// the fusion's fixed-point sums (four words of 8 bytes per cell); each
-// 256-aligned.
+// block and superblock (each with a spare one, which the march reads on maps of one
+// column of them), the upper bound layer if the map keeps one, then the fusion's
+// fixed-point sums (four words of 8 bytes per cell); each 256-aligned.
 size_t set_layout(const emx_params& p, char* base, Layers* L) {
   const size_t C = (size_t)p.nx * (size_t)p.ny;
   const size_t l4 = align256(C * 4);
   const size_t l1 = align256(C);
   const size_t nb = (size_t)blocks_of(p.nx, kBlockLog) * blocks_of(p.ny, kBlockLog);
   const size_t ns = (size_t)blocks_of(p.nx, kSuperLog) * blocks_of(p.ny, kSuperLog);
-  const size_t lb = align256(nb * 4) + align256(ns * 4);
+  const size_t lb = align256((nb + 1) * 4) + align256((ns + 1) * 4);
   if (L && base) {
     L->h = (float*)(base + 0 * l4);
     L->v = (float*)(base + 1 * l4);
@@ -128,7 +128,7 @@ size_t set_layout(const emx_params& p, char* base, Layers* L) {
     L->valid = (uint8_t*)(base + 7 * l4);
     L->mark = (uint8_t*)(base + 7 * l4 + l1);
     L->cmax = (float*)(base + 7 * l4 + 2 * l1);
-    L->smax = (float*)(base + 7 * l4 + 2 * l1 + align256(nb * 4));
+    L->smax = (float*)(base + 7 * l4 + 2 * l1 + align256((nb + 1) * 4));
     L->ub = p.upper_bound ? (float*)(base + 7 * l4 + 2 * l1 + lb) : nullptr;
     L->fx = (uint64_t*)(base + 7 * l4 + 2 * l1 + lb + (p.upper_bound ? l4 : 0));
   }

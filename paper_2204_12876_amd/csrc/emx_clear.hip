@@ -232,7 +232,9 @@ __device__ __forceinline__ Line line_of(const Item& it, const Ray& r, int step) 
 // j-th) may hold a sample below the maximum of its block (`mx`, w x h blocks).  A
 // step's samples lie in the 2 x 2 blocks from its line's on, two 8-byte lookups;
 // clamping keeps every in-map cell among them.  Every lookup is requested before
-// any is used.  Maps of a single row or column of blocks are not looked up.
+// any is used.  Where there is one column the pair's second value is the next row's
+// (past the last row, set_layout's spare one), and where there is one row the second
+// pair is the first: a value too many only keeps a step.
 struct __attribute__((packed, aligned(4))) Pair {
   float a, b;
 };
@@ -243,8 +245,8 @@ __device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int st
   uint32_t live = 0;
 #pragma unroll
   for (int j = 0; j < kN; ++j) live |= (k + j * step <= k1) ? 1u << j : 0u;
-  if (w < 2 || h < 2) return live;
-  const float xm = (float)(w - 2), ym = (float)(h - 2);
+  const float xm = (float)max(w - 2, 0), ym = (float)max(h - 2, 0);
+  const float* up = mx + (h > 1 ? w : 0);
   Pair lo[kN], hi[kN];
   float z[kN];
 #pragma unroll
@@ -255,7 +257,7 @@ __device__ __forceinline__ uint32_t may_act(const Line& l, int k, int k1, int st
     z[j] = fmaf(kf, l.dz, l.z);
     const uint32_t o = (__umul24(y, w) + (uint32_t)x) * 4u;
     lo[j] = *(const Pair*)((const char*)mx + o);
-    hi[j] = *(const Pair*)((const char*)(mx + w) + o);
+    hi[j] = *(const Pair*)((const char*)up + o);
   }
   uint32_t bits = 0;
 #pragma unroll
