@@ -172,9 +172,10 @@ emx_status make_item(const emx_map* m, const emx_frame* f, Item* it) {
   it->sbx = blocks_of(m->p.nx, kSuperLog);
   it->sby = blocks_of(m->p.ny, kSuperLog);
   // a sample travels at most ray_step along an axis; short steps stop at 32
-  // samples to a group, so that one thread's share of a long ray stays small
+  // samples to a group, so that one thread's share of a long ray stays small, and
+  // long ones (fewer than 3) are marched without groups
   const double per = floor(7.0 * m->p.resolution / (double)m->p.ray_step);
-  it->grp = per < 1.0 ? 1 : (per > 32.0 ? 32 : (int)per);
+  it->grp = per < 3.0 ? 0 : (per > 32.0 ? 32 : (int)per);
   it->fs.tcnt = m->ctl;
   if (!f) return EMX_OK;
   for (int k = 0; k < 12; ++k)

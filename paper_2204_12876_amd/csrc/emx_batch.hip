@@ -72,8 +72,9 @@ bool json_int(const char* js, const char* key, int* out) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// grid: zero, count, chunk (with the moves), tile, variance, setup, march, cells
-constexpr int kGrids = 8;
+// grid: zero, count, chunk (with the moves), tile, variance, setup, march, sparse march,
+// cells
+constexpr int kGrids = 9;
 
 struct GraphKey {
   void* scratch;
@@ -353,7 +354,8 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
     tab->off[kBVar][i + 1] = tab->off[kBVar][i] + (var ? var_units(cells) : 0);
     tab->off[kBSetup][i + 1] =
         tab->off[kBSetup][i] + (clear && (it.n > 0 || it.out_cleared) ? setup_units(it) : 0);
-    tab->off[kBRays][i + 1] = tab->off[kBRays][i] + (clear ? ray_units(it.n) : 0);
+    tab->off[kBRays][i + 1] = tab->off[kBRays][i] + (clear ? ray_units(it) : 0);
+    tab->off[kBSparse][i + 1] = tab->off[kBSparse][i] + (clear ? sparse_units(it) : 0);
     tab->off[kBCells][i + 1] =
         tab->off[kBCells][i] +
         ((st & (EMX_STAGE_NORMALS | EMX_STAGE_TRAV)) ? cells_units(it.c.nx, it.c.ny) : 0);
@@ -375,7 +377,8 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   key.grid[4] = cap_opt(t.grid_cells, tab->off[kBVar][n]);
   key.grid[5] = cap(t.grid_setup, tab->off[kBSetup][n]);
   key.grid[6] = cap(t.grid_march, tab->off[kBRays][n]);
-  key.grid[7] = cap(t.grid_cells, tab->off[kBCells][n]);
+  key.grid[7] = cap_opt(t.grid_march, tab->off[kBSparse][n]);
+  key.grid[8] = cap(t.grid_cells, tab->off[kBCells][n]);
 
   // ---- enqueue: the table upload, then a cached graph or the same launches
   hipStream_t st = (hipStream_t)stream;
@@ -384,8 +387,8 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   if (e != hipSuccess) return hip_fail(e, "pipeline_batch: table upload");
   auto enqueue = [&](hipStream_t q) -> hipError_t {
     hipError_t r = launch_fuse_batch(d_tab, key.grid, q);
-    if (r == hipSuccess) r = launch_clear_batch(d_tab, key.grid[5], key.grid[6], q);
-    if (r == hipSuccess) r = launch_cells_batch(d_tab, key.grid[7], q);
+    if (r == hipSuccess) r = launch_clear_batch(d_tab, key.grid[5], key.grid[6], key.grid[7], q);
+    if (r == hipSuccess) r = launch_cells_batch(d_tab, key.grid[8], q);
     return r;
   };
   if (t.graph) {

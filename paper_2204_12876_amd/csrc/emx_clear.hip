@@ -37,8 +37,11 @@
 //     the longest ray's chain of lookups, a microsecond each, set the time.
 //   - Every sample of a surviving group is evaluated exactly and compared
 //     with its cell's record, eight samples' records requested together (4M
-//     rays: 260 against 273 us for half groups of four); the few below it read
-//     the cell's variance and normal.
+//     rays: 260 against 273 us for half groups of four; four, where longer steps
+//     leave a group no more: 600k rays on 2000 x 2000 with steps of two cells 63
+//     against 67); the few below it read the cell's variance and normal.
+//   - Steps so long that a group would hold fewer than three samples take a march
+//     without groups (sparse march, below).
 //   - A sample that removes its cell resets the cell to the prior on the spot
 //     (and flags it in the caller's mask).  Of what it resets the march reads
 //     only the variance, of a cell that it may be about to remove: a ray that
@@ -293,9 +296,10 @@ __device__ __forceinline__ Sample sample_of(const Item& it, const Ray& r, int k,
   return q;
 }
 
-constexpr int kUnroll = 8;
+constexpr int kUnroll = 8;  // samples evaluated together
+constexpr int kHalf = 4;    // in groups of up to four
 
-// Samples [ka, kb] of ray r against the map, kUnroll at a time.  Their cells are
+// Samples [ka, kb] of ray r against the map, kU at a time.  Their cells are
 // found without branches, then their clearing records are all requested
 // together: the height, or -inf for a cell no ray may clear, which fails hd > 0
 // for every finite sample height.  With kPair the record also holds the
@@ -306,16 +310,16 @@ constexpr int kUnroll = 8;
 // every position.  Without pairs that loop reads the variance from the layer:
 // another ray may have removed the cell meanwhile, but then it is removed
 // whatever this ray finds.
-template <bool kBound, bool kPair>
+template <int kU, bool kBound, bool kPair>
 __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int ka, int kb) {
   const float2 lim = make_float2(__uint_as_float(__float_as_uint(it.c.nxf) - 1u),
                                  __uint_as_float(__float_as_uint(it.c.nyf) - 1u));
-  for (int k = ka; k <= kb; k += kUnroll) {
-    float qz[kUnroll];
-    bool cand[kUnroll];
-    float rec[kUnroll], v[kUnroll];
+  for (int k = ka; k <= kb; k += kU) {
+    float qz[kU];
+    bool cand[kU];
+    float rec[kU], v[kU];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
+    for (int u = 0; u < kU; ++u) {
       const Sample q = sample_of(it, r, k + u, lim);
       const uint32_t cell = __umul24(q.iy, it.c.nx) + (uint32_t)q.ix;
       qz[u] = q.qz;
@@ -331,7 +335,7 @@ __device__ __forceinline__ void test_samples(const Item& it, const Ray& r, int k
     }
     uint32_t remove = 0, bound = 0;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
+    for (int u = 0; u < kU; ++u) {
       const float hd = rec[u] - qz[u];
       if (cand[u] & (hd > 0.0f) & (!kPair || (hd * hd) > v[u])) remove |= 1u << u;
       // lowers(), but for a pair of zeros in the other order, which the loop below
@@ -591,8 +595,9 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, int64_t
         const Ray q = {s.dx[w], s.dy[w], s.dz[w], s.end_cell[w], s.rK[w], s.k1[w]};
         const int ka = (int)(e & 0xFFFFFFu);
         const int kb = min(ka + grp - 1, q.k1);
-        if (it.L.ub) test_samples<true, true>(it, q, ka, kb);
-        else test_samples<false, kPair>(it, q, ka, kb);
+        if (it.L.ub) test_samples<kUnroll, true, true>(it, q, ka, kb);
+        else if (grp > kHalf) test_samples<kUnroll, false, kPair>(it, q, ka, kb);
+        else test_samples<kHalf, false, kPair>(it, q, ka, kb);
       }
       __syncthreads();  // the groups have been read
       if (tid == 0) s.ngroups = 0;
@@ -602,6 +607,130 @@ __device__ __forceinline__ void march_body(const Item& it, int64_t unit, int64_t
     if (tid == 0) s.nspans = 0;
     __syncthreads();
   }
+}
+
+// ------------------------------------------------------------- sparse march
+// For steps so long that fewer than three samples lie within 7 cells (Item::grp is
+// 0): a group would hold one or two, and its lookups cost more than they spare.  A
+// workgroup's rays are cut into runs of eight samples, one per thread at a time,
+// found by a search in the prefix of the rays' runs.  Each sample is compared with
+// the maximum of its own block, and the few below it with their cells.
+// What bounds it: on small frames the chain of round trips, on large ones VALU issue
+// (50 registers, 8 waves to a SIMD; eight records requested together like the dense
+// march took 104 and 10 to 30% longer).  A whole call against the dense march with
+// groups of one sample: 300k rays on 400 x 400 cells, steps of 4 cells 23.4 -> 17.1 us
+// (a queue of segments took 17.1), of 12 cells 20.6 -> 14.6 (14.6); 600k on 2000 x
+// 2000, 4 cells 80 -> 53 (56), 20 cells 80 -> 33 (36).  At steps of 2 cells the dense
+// march is the better one (600k on 2000 x 2000: 65 against 113), and so the line is
+// drawn at three samples.
+template <int kRays>
+struct SparseShared {
+  float dx[kRays], dy[kRays], dz[kRays];
+  double rK[kRays];
+  int k0[kRays], k1[kRays], end_cell[kRays];
+  int first[kRays];  // runs of the rays before
+  int sum[kNTc / 64];
+};
+
+// Rays come from all over the frame (spread_ray), in workgroups of 128 and, up to
+// kShortRays and kFewRays, of 64 and 32: a beam's rays are of one length here too.
+// Runs of 16 against 32 rays: 600k on 2000 x 2000, steps of 4 cells 53 against 57 us;
+// consecutive rays 69.
+constexpr int kRunSparse = 16;
+
+// Samples [ka, kb] (at most kUnroll) of ray r.
+template <bool kBound, bool kPair>
+__device__ __forceinline__ void sparse_samples(const Item& it, const Ray& r, int ka, int kb) {
+  const float2 lim = make_float2(__uint_as_float(__float_as_uint(it.c.nxf) - 1u),
+                                 __uint_as_float(__float_as_uint(it.c.nyf) - 1u));
+  uint32_t act = 0;
+  float qz[kUnroll], m[kUnroll];
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    const Sample q = sample_of(it, r, ka + u, lim);
+    const uint32_t cell = __umul24(q.iy, it.c.nx) + (uint32_t)q.ix;
+    m[u] = it.L.cmax[__umul24(q.iy >> kBlockLog, it.bx) + (uint32_t)(q.ix >> kBlockLog)];
+    qz[u] = q.qz;
+    act |= ((ka + u <= kb) & q.in & ((int)cell != r.end_cell)) ? 1u << u : 0u;
+  }
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u)  // (equal: zeros of either sign, see lowers)
+    if (!(qz[u] <= m[u])) act &= ~(1u << u);
+  while (act) {
+    const Sample q = sample_of(it, r, ka + __builtin_ctz(act), lim);
+    act &= act - 1u;
+    const uint32_t lc = __umul24(q.iy, it.c.nx) + (uint32_t)q.ix;
+    const int64_t pc = pcell(it.c, q.ix, q.iy);
+    float h, v = 0.0f;
+    if (kPair) {
+      const float2 p = *(const float2*)((const char*)it.L.clr + lc * 8u);
+      h = p.x;
+      v = p.y;
+    } else {
+      h = *(const float*)((const char*)it.L.clr + lc * 4u);
+    }
+    const float hd = h - q.qz;
+    if (kBound && isnan(h)) {
+      if (lowers(q.qz, v) && lowers(q.qz, it.L.ub[pc])) atomic_min_f32(it.L.ub + pc, q.qz);
+    } else if (hd > 0.0f) {
+      if (!kPair) v = it.L.v[pc];  // (see test_samples)
+      const float an2dd = it.c.an2 * ((r.dx * r.dx + r.dy * r.dy) + r.dz * r.dz);
+      if ((hd * hd) > v) {
+        const float dot = (r.dx * it.L.nx[pc] + r.dy * it.L.ny[pc]) + r.dz * it.L.nz[pc];
+        if ((dot * dot) > an2dd) clear_cell(it, pc, (int)lc);
+      }
+    }
+  }
+}
+
+// The rays of workgroup `unit` of `units` of the item.  Ends with a barrier.
+template <int kRays, bool kBound, bool kPair>
+__device__ __forceinline__ void sparse_body(const Item& it, int64_t unit, int64_t units,
+                                            SparseShared<kRays>& s) {
+  const int tid = threadIdx.x;
+  int n = 0;  // the ray's runs
+  if (tid < kRays) {
+    const int64_t i = spread_ray<kRunSparse>(unit, units, tid);
+    Ray r;
+    int k0 = 1;
+    if (i < it.n && ray_of(it, i, r, k0)) {
+      s.dx[tid] = r.dx;
+      s.dy[tid] = r.dy;
+      s.dz[tid] = r.dz;
+      s.rK[tid] = r.rK;
+      s.k0[tid] = k0;
+      s.k1[tid] = r.k1;
+      s.end_cell[tid] = r.end_cell;
+      n = (r.k1 - k0) / kUnroll + 1;
+    }
+  }
+  const int lane = tid & 63, wave = tid >> 6;
+  int x = n;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) s.sum[wave] = x;
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kNTc / 64; ++w) {
+    before += w < wave ? s.sum[w] : 0;
+    total += s.sum[w];
+  }
+  if (tid < kRays) s.first[tid] = before + x - n;
+  __syncthreads();
+  for (int g = tid; g < total; g += kNTc) {
+    int w = 0;  // the last ray with first <= g: the one that has run g
+#pragma unroll
+    for (int h = kRays / 2; h > 0; h >>= 1)
+      if (s.first[w + h] <= g) w += h;
+    const Ray q = {s.dx[w], s.dy[w], s.dz[w], s.end_cell[w], s.rK[w], s.k1[w]};
+    const int ka = s.k0[w] + (g - s.first[w]) * kUnroll;
+    sparse_samples<kBound, kPair>(it, q, ka, min(ka + kUnroll - 1, q.k1));
+  }
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------- launches
@@ -620,6 +749,13 @@ __global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
   if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
   march_body<kRays, kLong, true>(it, blockIdx.x, gridDim.x, s);
+}
+
+template <int kRays>
+__global__ __launch_bounds__(kNTc, 8) void k_clear_sparse(Item it) {
+  __shared__ SparseShared<kRays> s;
+  if (it.L.ub) sparse_body<kRays, true, true>(it, blockIdx.x, gridDim.x, s);
+  else sparse_body<kRays, false, true>(it, blockIdx.x, gridDim.x, s);
 }
 
 __global__ __launch_bounds__(kNTc) void k_clear_setup_b(const Batch* bt) {
@@ -647,6 +783,19 @@ __global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
   }
 }
 
+__global__ __launch_bounds__(kNTc, 8) void k_clear_sparse_b(const Batch* bt) {
+  __shared__ SparseShared<kRaysPlain> s;
+  const UnitFinder units(bt, kBSparse);
+  for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
+    int64_t unit;
+    const int i = units.find(w, unit);
+    const Item& it = bt->items[i];
+    const int64_t of = (it.n + kRaysPlain - 1) / kRaysPlain;
+    if (it.L.ub) sparse_body<kRaysPlain, true, true>(it, unit, of, s);
+    else sparse_body<kRaysPlain, false, false>(it, unit, of, s);
+  }
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -660,8 +809,13 @@ size_t clear_scratch_bytes(int64_t max_points, int seg) {
   return align256((size_t)cap * 64 * 8) + align256((size_t)max_points * 16);
 }
 
+int64_t sparse_units(const Item& it) {
+  return it.grp > 0 ? 0 : (it.n + kRaysPlain - 1) / kRaysPlain;
+}
 int64_t setup_units(const Item& it) { return (int64_t)it.sbx * it.sby; }
-int64_t ray_units(int64_t n) { return (n + kRaysBatch - 1) / kRaysBatch; }
+int64_t ray_units(const Item& it) {
+  return it.grp > 0 ? (it.n + kRaysBatch - 1) / kRaysBatch : 0;
+}
 
 hipError_t launch_clear(const Item& it, hipStream_t stream) {
   // with no rays the setup still zeroes the caller's mask
@@ -682,6 +836,12 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream,
                        it);
   };
+  if (it.grp == 0) {
+    if (it.n <= kFewRays) go(k_clear_sparse<kRaysFew>, kRaysFew);
+    else if (it.n <= kShortRays) go(k_clear_sparse<kRaysShort>, kRaysShort);
+    else go(k_clear_sparse<kRaysPlain>, kRaysPlain);
+    return hipGetLastError();
+  }
   if (it.L.ub || (it.n > kFewRays && it.n <= kShortRays))
     go(far ? k_clear_march<kRaysShort, true> : k_clear_march<kRaysShort, false>, kRaysShort);
   else if (it.n <= kFewRays)
@@ -692,7 +852,7 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
 }
 
 hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_march,
-                              hipStream_t stream) {
+                              int grid_sparse, hipStream_t stream) {
   {
     TimedLaunch tl("k_clear_setup_b", stream);
     hipLaunchKernelGGL(k_clear_setup_b, dim3(grid_setup), dim3(kNTc), 0, stream, d_batch);
@@ -702,6 +862,10 @@ hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_mar
   {
     TimedLaunch tl("k_clear_march_b", stream);
     hipLaunchKernelGGL(k_clear_march_b, dim3(grid_march), dim3(kNTc), 0, stream, d_batch);
+  }
+  if (grid_sparse > 0) {  // no item needs it: no launch
+    TimedLaunch tl("k_clear_sparse_b", stream);
+    hipLaunchKernelGGL(k_clear_sparse_b, dim3(grid_sparse), dim3(kNTc), 0, stream, d_batch);
   }
   return hipGetLastError();
 }

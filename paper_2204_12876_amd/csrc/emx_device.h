@@ -126,7 +126,8 @@ struct Item {
   int tiles_x, T, B;
   int bx, by;        // clearing blocks
   int sbx, sby;      // clearing superblocks
-  int grp;           // clearing samples to a group: at most 7 cells of travel
+  int grp;           // clearing samples to a group: at most 7 cells of travel; 0 if these
+                     // would be fewer than 3 (each sample by itself)
   int32_t index;     // position in its batch
 };
 
@@ -136,7 +137,8 @@ constexpr int kMaxItems = 64;
 // kBZero, kBCount: the wall/edge rule's per-cell counts (zeroed, then
 // counted); kBVar: the per-cell time and outlier variance after the fusion.
 enum BatchStage {
-  kBMove = 0, kBZero, kBCount, kBChunk, kBTile, kBVar, kBSetup, kBRays, kBCells, kBNum
+  kBMove = 0, kBZero, kBCount, kBChunk, kBTile, kBVar, kBSetup, kBRays, kBSparse, kBCells,
+  kBNum
 };
 
 // Only the header and the first n items are uploaded for a batch of n.

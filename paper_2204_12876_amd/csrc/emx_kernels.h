@@ -51,12 +51,15 @@ hipError_t launch_fuse_batch(const Batch* d_batch, const int grid[5], hipStream_
 // ---------------------------------------------------------------- clearing
 size_t clear_scratch_bytes(int64_t max_points, int seg);
 // The setup's work units are the item's superblocks (with no rays only if a
-// removed-cell mask must be zeroed), the batched march's its rays by 256.
+// removed-cell mask must be zeroed), the batched march's its rays by 256, or for
+// long ray steps (Item::grp 0) the sparse march's its rays by 128.
 int64_t setup_units(const Item& it);
-int64_t ray_units(int64_t n);
+int64_t ray_units(const Item& it);
+int64_t sparse_units(const Item& it);
 hipError_t launch_clear(const Item& it, hipStream_t stream);
+// A zero grid_sparse skips that launch.
 hipError_t launch_clear_batch(const Batch* d_batch, int grid_setup, int grid_march,
-                              hipStream_t stream);
+                              int grid_sparse, hipStream_t stream);
 
 // --------------------------------------------------------------- per cell
 int64_t cells_units(int nx, int ny);
