@@ -12,10 +12,10 @@
 //     variances if a map uses time or outlier variance, clearing setup and
 //     march, then normals + traversability.
 // Every launch finds its work in the table, so a graph depends only on the
-// scratch address and the grid sizes.  Each stage's grid
-// is the tuned size capped at the stage's work rounded up to a power of two,
-// so a small batch does not launch thousands of idle workgroups, and few
-// distinct graphs arise.  Captured graphs are kept in a small LRU cache.
+// scratch address and the grid sizes.  These follow the batch's points and cells in
+// a few wide steps (grid_step), at most the tuned sizes, so a small batch does not
+// launch thousands of idle workgroups, and batches of any mix of sizes share a few
+// graphs.  Captured graphs are kept in a small LRU cache.
 // Two pinned tables alternate: the host fills one while the other may still
 // be read by the previous batch's copy.
 //
@@ -26,8 +26,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdio>
+#include <initializer_list>
 #include <new>
 
 #include "emx_host.h"
@@ -40,7 +42,7 @@ namespace {
 // dispatch balances units better than two workgroups per compute unit that take
 // them in turn, and a unit's first loads start while others run), and one per
 // four tiles of pass 2, which are the smallest units.  Fixed sizes for large
-// batches keep their graphs few: only pass 2's grid follows the batch.  Against 2
+// batches keep their graphs few.  Against 2
 // (chunk, tile), 4 (cells), 8 (setup) and 16 (march) workgroups per compute unit,
 // a batch of 16 maps takes 104 -> 24 us in pass 2, 67 -> 55 us in the stencils,
 // 91 -> 82 us in pass 1 and 137 -> 128 us in the march.
@@ -88,10 +90,18 @@ struct GraphKey {
   }
 };
 
-int pow2_at_least(int64_t x) {
-  int g = 1;
-  while (g < x && g < (1 << 30)) g <<= 1;
-  return g;
+// The grid for `units` units of work: 256, 1024, 4096, 16384 or 65536, enough for
+// one unit to a workgroup up to 4096 and for two above, where a workgroup more or
+// less in flight no longer matters.  A batch has two such sizes, of its points and of
+// its cells, and every stage's grid is a fixed part of one of them: with a size of
+// its own for each stage, in powers of two, batches of 1 to 8 of a server's 64
+// robots met 74 sets of grids, and 30% of them captured a graph anew (16 are kept);
+// with these 7 (4000 random batches, counted on the host).  Mixed batches of 1 to 4
+// maps, each waited for: 111 -> 104 us; a batch of one size runs the same.
+int grid_step(int64_t units) {
+  int64_t g = 256;
+  while (g < 65536 && g * (g < 4096 ? 1 : 2) < units) g *= 4;
+  return (int)g;
 }
 
 }  // namespace
@@ -361,24 +371,35 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
         ((st & (EMX_STAGE_NORMALS | EMX_STAGE_TRAV)) ? cells_units(it.c.nx, it.c.ny) : 0);
   }
 
-  // ---- grids: the tuned size, capped at the stage's work (power of two)
+  // ---- grids: parts of two sizes, at most the tuned ones (a ray unit is a fourth of
+  // a chunk's points, a tile a fourth of a setup's or stencil's cells)
   const Tuning& t = b->tune;
-  auto cap = [](int tuned, int64_t units) {
-    return (int)(units < 1 ? 1 : (pow2_at_least(units) < tuned ? pow2_at_least(units) : tuned));
+  const auto total = [&](int stage) { return tab->off[stage][n]; };
+  const auto largest = [](std::initializer_list<int64_t> x) {
+    return *std::max_element(x.begin(), x.end());
   };
-  // stages that only some maps use are skipped (grid 0) when none does
-  auto cap_opt = [&](int tuned, int64_t units) { return units < 1 ? 0 : cap(tuned, units); };
+  const int pts = grid_step(largest({4 * (total(kBMove) + total(kBChunk)), 4 * total(kBCount),
+                                     total(kBRays), total(kBSparse)}));
+  const int cells = grid_step(largest({total(kBTile), total(kBZero), total(kBVar),
+                                       4 * total(kBSetup), 4 * total(kBCells)}));
+  // a stage without work: one workgroup, or no launch if only some maps use the stage
+  const auto grid = [&](int tuned, int size, int64_t units) {
+    return units < 1 ? 1 : (size < tuned ? size : tuned);
+  };
+  const auto grid_opt = [&](int tuned, int size, int64_t units) {
+    return units < 1 ? 0 : grid(tuned, size, units);
+  };
   GraphKey key;
   key.scratch = d_scratch;
-  key.grid[0] = cap_opt(t.grid_cells, tab->off[kBZero][n]);
-  key.grid[1] = cap_opt(t.grid_chunk, tab->off[kBCount][n]);
-  key.grid[2] = cap(t.grid_chunk, tab->off[kBMove][n] + tab->off[kBChunk][n]);
-  key.grid[3] = cap(t.grid_tile, tab->off[kBTile][n]);
-  key.grid[4] = cap_opt(t.grid_cells, tab->off[kBVar][n]);
-  key.grid[5] = cap(t.grid_setup, tab->off[kBSetup][n]);
-  key.grid[6] = cap(t.grid_march, tab->off[kBRays][n]);
-  key.grid[7] = cap_opt(t.grid_march, tab->off[kBSparse][n]);
-  key.grid[8] = cap(t.grid_cells, tab->off[kBCells][n]);
+  key.grid[0] = grid_opt(t.grid_cells, cells, total(kBZero));
+  key.grid[1] = grid_opt(t.grid_chunk, pts / 4, total(kBCount));
+  key.grid[2] = grid(t.grid_chunk, pts / 4, total(kBMove) + total(kBChunk));
+  key.grid[3] = grid(t.grid_tile, cells, total(kBTile));
+  key.grid[4] = grid_opt(t.grid_cells, cells, total(kBVar));
+  key.grid[5] = grid(t.grid_setup, cells / 4, total(kBSetup));
+  key.grid[6] = grid(t.grid_march, pts, total(kBRays));
+  key.grid[7] = grid_opt(t.grid_march, pts, total(kBSparse));
+  key.grid[8] = grid(t.grid_cells, cells / 4, total(kBCells));
 
   // ---- enqueue: the table upload, then a cached graph or the same launches
   hipStream_t st = (hipStream_t)stream;
