@@ -1,10 +1,10 @@
 """Autotuner of the batched executor's launch geometry.
 
 Each batched stage runs a fixed number of workgroups that take the batch's work
-units in turn.  The tuning picks those counts per stage ("grid_move" and "seg" no
-longer reach a launch and are kept for their form: moves run with the chunks, and
-clearing's lists are in LDS).  It never changes results: every candidate yields
-the same bits.
+units in turn.  The tuning picks those counts per stage.  It never changes
+results: every candidate yields the same bits.  "grid_move" and "seg" are part of a
+tuning but reach no launch (moves run with the chunks, and clearing's lists are in
+LDS): they are not searched, since a difference found there could only be noise.
 
 Search: coordinate descent from the library defaults.  Each knob in turn is
 set to each of its candidate values with the others held, the fastest is
@@ -22,7 +22,7 @@ from __future__ import annotations
 import json
 import time
 
-# 65536 means one workgroup per work unit for every batch of this size class.
+# Each knob's candidates.  65536 leaves the size to the library's own rule.
 SPACE = {
     "grid_chunk": [256, 512, 1024, 2048, 4096, 65536],
     "grid_tile": [256, 512, 1024, 2048, 4096, 65536],
@@ -32,6 +32,8 @@ SPACE = {
     "grid_cells": [256, 512, 1024, 2048, 8192, 65536],
     "seg": [16, 32, 64, 128],
 }
+NO_LAUNCH = ("grid_move", "seg")
+SEARCHED = {k: v for k, v in SPACE.items() if k not in NO_LAUNCH}
 
 
 def time_tuning(run_batch, tuning: dict, reps: int = 8, repeats: int = 3, device=None) -> float:
@@ -58,7 +60,7 @@ def time_tuning(run_batch, tuning: dict, reps: int = 8, repeats: int = 3, device
     return times[len(times) // 2]
 
 
-def autotune(run_batch, start: dict, space: dict = SPACE, reps: int = 8, max_rounds: int = 3,
+def autotune(run_batch, start: dict, space: dict = SEARCHED, reps: int = 8, max_rounds: int = 3,
              device=None, log=None):
     """Coordinate descent over ``space`` from ``start``; returns (best, seconds, history)."""
     best = dict(start)
