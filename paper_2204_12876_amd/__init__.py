@@ -36,11 +36,16 @@ def aligned_empty(nbytes: int, device, align: int = 256) -> torch.Tensor:
     return raw[off:off + max(1, nbytes)]
 
 
+# the current stream's handle without a Stream object around it (0.12 instead of 1.9 us a
+# call), where this torch has the function; it is not part of torch's public interface
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    # the current stream's handle, without a Stream object around it
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
     index = device.index
-    return torch._C._cuda_getCurrentRawStream(
-        torch.cuda.current_device() if index is None else index)
+    return _raw_stream(torch.cuda.current_device() if index is None else index)
 
 
 def _f32(t: torch.Tensor, device) -> torch.Tensor:

@@ -30,3 +30,18 @@ def test_frame_pose_forms(pose):
 def test_frame_pose_of_another_size_is_refused(pose):
     with pytest.raises(ValueError):
         _emx.make_frame(0, 0, 0, 1, pose, 0)
+
+
+def test_stream_without_the_private_function(monkeypatch):
+    """Another torch may not have the raw lookup: the public one serves."""
+    import torch
+
+    import paper_2204_12876_amd as emx
+
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(emx, "_raw_stream", None, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream)
+    assert emx._stream(torch.device("cuda:0")) == 1234
