@@ -468,9 +468,9 @@ size_t emx_batch_scratch_bound(const emx_batch* batch, const emx_params* largest
  *              address, key width and grid sizes, so keep reusing the same
  *              buffer.  A scratch buffer must not be shared by batches in
  *              flight at the same time.
- *   Each stage's grid is at most the tuned size, and follows the batch's
- *   points or cells in steps of four, so that batches of all sizes need few
- *   graphs.
+ *   Each stage's grid is at most the tuned size and follows the batch's work:
+ *   in powers of two of its points and of its cells in a graph, so that
+ *   batches of all sizes need few graphs, else of each stage's own units.
  *   Every item is checked before anything is enqueued; on an error no map
  *   changes.  Moves commit the maps' new centres when the call returns OK.
  *   The call may wait on the host for the batch before last to release its

@@ -12,10 +12,10 @@
 //     variances if a map uses time or outlier variance, clearing setup and
 //     march, then normals + traversability.
 // Every launch finds its work in the table, so a graph depends only on the
-// scratch address and the grid sizes.  These follow the batch's points and cells in
-// a few wide steps (grid_step), at most the tuned sizes, so a small batch does not
-// launch thousands of idle workgroups, and batches of any mix of sizes share a few
-// graphs.  Captured graphs are kept in a small LRU cache.
+// scratch address and the grid sizes.  These are at most the tuned sizes and follow
+// the batch's work, so a small batch does not launch thousands of idle workgroups:
+// in a few steps of its points and its cells (grid_step), so that batches of any mix
+// of sizes share a few graphs.  Captured graphs are kept in a small LRU cache.
 // Two pinned tables alternate: the host fills one while the other may still
 // be read by the previous batch's copy.
 //
@@ -90,18 +90,25 @@ struct GraphKey {
   }
 };
 
-// The grid for `units` units of work: 256, 1024, 4096, 16384 or 65536, enough for
-// one unit to a workgroup up to 4096 and for two above, where a workgroup more or
-// less in flight no longer matters.  A batch has two such sizes, of its points and of
-// its cells, and every stage's grid is a fixed part of one of them: with a size of
-// its own for each stage, in powers of two, batches of 1 to 8 of a server's 64
-// robots met 74 sets of grids, and 30% of them captured a graph anew (16 are kept);
-// with these 7 (4000 random batches, counted on the host).  Mixed batches of 1 to 4
-// maps, each waited for: 111 -> 104 us; a batch of one size runs the same.
+// The smallest power of two that holds x.
+int pow2_at_least(int64_t x) {
+  int g = 1;
+  while (g < x && g < (1 << 30)) g <<= 1;
+  return g;
+}
+
+// A captured grid for `units` units of work: the power of two that holds them, from
+// 1024 to 65536.  A batch has two such sizes, of its points and of its cells, and
+// every stage's grid is a fixed part of one of them.  With a size of its own for
+// each stage, batches of 1 to 8 of a server's 64 robots met 74 sets of grids, and 30%
+// of them captured a graph anew (16 are kept); with these they meet 15 (4000 random
+// batches, counted on the host).  Steps of four instead of two meet 7, but launch
+// up to four times the workgroups that a batch needs (8 maps of 130 to 250 cells a
+// side: 79 against 77 us).  Mixed batches of 1 to 4 maps, each waited for: 107 -> 103
+// us.
 int grid_step(int64_t units) {
-  int64_t g = 256;
-  while (g < 65536 && g * (g < 4096 ? 1 : 2) < units) g *= 4;
-  return (int)g;
+  const int g = pow2_at_least(units);
+  return g < 1024 ? 1024 : (g > 65536 ? 65536 : g);
 }
 
 }  // namespace
@@ -371,8 +378,10 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
         ((st & (EMX_STAGE_NORMALS | EMX_STAGE_TRAV)) ? cells_units(it.c.nx, it.c.ny) : 0);
   }
 
-  // ---- grids: parts of two sizes, at most the tuned ones (a ray unit is a fourth of
-  // a chunk's points, a tile a fourth of a setup's or stencil's cells)
+  // ---- grids, at most the tuned ones.  In a graph they are parts of two sizes (a ray
+  // unit is a fourth of a chunk's points, a tile a fourth of a setup's or stencil's
+  // cells); launched directly each stage has its own (a server's batch of 8 maps 1.5%
+  // faster than with the parts).
   const Tuning& t = b->tune;
   const auto total = [&](int stage) { return tab->off[stage][n]; };
   const auto largest = [](std::initializer_list<int64_t> x) {
@@ -383,11 +392,12 @@ emx_status emx_pipeline_batch(emx_batch* b, const emx_batch_item* items, int32_t
   const int cells = grid_step(largest({total(kBTile), total(kBZero), total(kBVar),
                                        4 * total(kBSetup), 4 * total(kBCells)}));
   // a stage without work: one workgroup, or no launch if only some maps use the stage
-  const auto grid = [&](int tuned, int size, int64_t units) {
+  const auto grid = [&](int tuned, int part, int64_t units) {
+    const int size = t.graph ? part : pow2_at_least(units);
     return units < 1 ? 1 : (size < tuned ? size : tuned);
   };
-  const auto grid_opt = [&](int tuned, int size, int64_t units) {
-    return units < 1 ? 0 : grid(tuned, size, units);
+  const auto grid_opt = [&](int tuned, int part, int64_t units) {
+    return units < 1 ? 0 : grid(tuned, part, units);
   };
   GraphKey key;
   key.scratch = d_scratch;

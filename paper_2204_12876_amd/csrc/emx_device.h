@@ -141,10 +141,12 @@ enum BatchStage {
   kBNum
 };
 
-// Only the header and the first n items are uploaded for a batch of n.
+// Only the header and the first n items are uploaded for a batch of n.  Units fit 32
+// bits: the smallest hold 128 points or 256 cells, of 64 items of less than 2^31
+// points and at most 2^28 cells each.
 struct Batch {
   int n;
-  int64_t off[kBNum][kMaxItems + 1];
+  int32_t off[kBNum][kMaxItems + 1];
   Item items[kMaxItems];
 };
 
@@ -298,17 +300,15 @@ class UnitFinder {
   __device__ __forceinline__ int64_t total() const { return total_; }
   // The item of unit w < total(), and the unit's number within it.
   __device__ __forceinline__ int find(int64_t w, int64_t& unit) const {
-    const int i = __builtin_amdgcn_readfirstlane(__popcll(__ballot(end_ <= w)));
-    const int prev = i > 0 ? i - 1 : 0;
-    const int64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)end_, prev);
-    const int64_t hi = __builtin_amdgcn_readlane((int)(end_ >> 32), prev);
-    unit = w - (i > 0 ? ((hi << 32) | lo) : 0);
+    const int i = __builtin_amdgcn_readfirstlane(__popcll(__ballot(end_ <= (int)w)));
+    const int before = __builtin_amdgcn_readlane(end_, i > 0 ? i - 1 : 0);
+    unit = (int)w - (i > 0 ? before : 0);
     return i;
   }
 
  private:
   int n_;
-  int64_t total_, end_;
+  int total_, end_;
 };
 
 }  // namespace emx

@@ -39,7 +39,7 @@ def test_mixed_batches_share_graphs(dev, most):
         pb.run([entry(int(i), k + 1) for i in pick])
     torch.cuda.synchronize()
     runs, captures = pb.stats()
-    assert runs == 121 and captures - start <= 10, captures
+    assert runs == 121 and captures - start <= 16, captures
     pb.close()
     for m in maps:
         m.close()
