@@ -143,11 +143,12 @@ emx_status emx_params_check(const emx_params* params);
  * 32x8-cell fusion tile.  Returns 0 for invalid parameters. */
 size_t emx_state_bytes(const emx_params* params);
 
-/* Device scratch bytes emx_fuse_points and emx_clear_visibility need for
- * frames of up to max_points points (one buffer serves both calls, which use
- * it in turn; the fusion's part is the wall rule's per-cell counts, 4 bytes
- * per cell with wall_min_count > 0, else none).  Returns 0 for invalid
- * parameters or max_points < 0. */
+/* Device scratch bytes that emx_fuse_points and emx_clear_visibility ask for, for
+ * frames of up to max_points points (one buffer serves both calls, in turn).  The
+ * fusion's part is the wall rule's per-cell counts, 4 bytes per cell with
+ * wall_min_count > 0, else none.  The clearing's part, about 106 bytes a point, is
+ * the size of a queue that it no longer keeps: it asks for the bytes and leaves
+ * them untouched.  Returns 0 for invalid parameters or max_points < 0. */
 size_t emx_scratch_bytes(const emx_params* params, int64_t max_points);
 
 /* Bytes of the packed export format: the layers in identifier order, each

@@ -18,9 +18,11 @@
 //     271 against 285 us); a batch keeps 4 bytes, which is what bounds its setup
 //     (16 maps: 39 -> 28 us, the march the same).
 //   - Loads come in two rounds: validity, then the update time, normal z, height
-//     and variance of valid cells (or the upper bound of invalid ones).
+//     and variance of valid cells (or the upper bound of invalid ones); on maps of up
+//     to kAllCells all in one.
 //   - The caller's removed-cell mask is zeroed here.
-// march: one workgroup per 32, 64, 128 or (in a batch) 256 rays.
+// march: one workgroup per 32, 64, 128 or (in a batch) 256 rays, consecutive ones or,
+// where rays can be long, from all over the frame (kLong).
 //   - The ray is cut into groups of Item::grp consecutive samples, at most 7
 //     cells of travel, and spans of four groups.  Lower bounds of a group's
 //     cells and height come from the ray's line, widened by more than the
