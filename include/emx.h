@@ -224,7 +224,8 @@ emx_status emx_move_map(emx_map* map, double cx, double cy, void* stream);
  *   The sums are formed exactly, in fixed point.  A point's float32 terms
  *     w = 1/sp2;  u = w * rz,  rz = (R20*xs + R21*ys) + R22*zs  (zm = rz + tz)
  *   are rounded to integers at the scales 2^Sw and 2^Su (ties to even; a w
- *   that rounds to zero counts as one unit) and summed as integers.  The
+ *   that rounds to zero counts as one unit, a u past float32's range as 2^128
+ *   with its sign) and summed as integers.  The
  *   shifts are chosen per call so that no sum can overflow:
  *     Sw = 93 - ceil(log2 n) - Ew,  2^(Ew-1) <= wmax < 2^Ew,
  *     wmax = (1 + 2^-10) * float32(1 / float32(alpha * float32(min_range^2))),
@@ -299,8 +300,9 @@ emx_status emx_move_fuse_points(emx_map* map, double cx, double cy, const emx_fr
  * Normals and traversability are left for the next per-cell pass.
  * Upper bound (Sec. II-H, maps with upper_bound = 1): the same samples, in
  * cells that are invalid when the call starts, lower the cell's bound to q.z:
- * upper[c] = min(upper[c], q.z over those samples).  A minimum has no order,
- * so the layer is deterministic.  Cells enter with +inf (init, move).
+ * upper[c] = min(upper[c], q.z over those samples).  A minimum has no order
+ * (of the two zeros the negative one is the lower), so the layer is
+ * deterministic.  Cells enter with +inf (init, move).
  *   d_scratch:     >= emx_scratch_bytes(params, frame->n) bytes, 256-aligned;
  *                  may be NULL when n = 0.
  *   d_out_cleared: optional uint8[nx*ny], set to 1 for removed cells, 0 else. */

@@ -22,7 +22,7 @@
 //     to kAllCells all in one.
 //   - The caller's removed-cell mask is zeroed here.
 // march: one workgroup per 32, 64, 128 or (in a batch) 256 rays, consecutive ones or,
-// where rays can be long, from all over the frame (kLong).
+// where rays can be long, from several parts of the frame (kLongRay).
 //   - The ray is cut into groups of Item::grp consecutive samples, at most 7
 //     cells of travel, and spans of four groups.  Lower bounds of a group's
 //     cells and height come from the ray's line, widened by more than the
@@ -89,21 +89,27 @@ constexpr int kRaysBatch = 256;
 constexpr int64_t kShortRays = 1 << 17;  // 4 x 256 workgroups of 128
 constexpr int64_t kFewRays = 3 << 14;    // 6 x 256 workgroups of 32
 // Where rays can be long (samples to a map side) and the workgroups are few, the
-// march takes its other form (kLong): a workgroup's rays come from several parts of
-// the frame, since a LiDAR's beam is a run of rays of one length and a workgroup that
-// holds only long ones sets the march's time; and all of its threads share its rays'
-// spans, where a thread to each ray left the others waiting for rounds of eight spans.
-// A whole call, one form against the other: 13k LiDAR rays on 1770 x 1979 cells 27.6
-// -> 23.3 us, 60k on 2000 x 2000 35.7 -> 29.5, 178k on 827 x 749 30.4 -> 22.5, 300k on
-// 1500 x 1500 46.3 -> 35.0, 600k on 2000 x 2000 68 -> 61.  With more workgroups than
-// the chip holds they balance each other, and consecutive rays share more of their
-// lookups (spread against consecutive: 4M on 2000 x 2000 237 against 229; 800k camera
-// and LiDAR rays on 1200 x 1000 34 against 32; 500k on 520 x 520 28 against 25), and
-// where a ray has few spans to share the other form's one barrier more shows (300k on
-// 400 x 400: 18.8 against 18.4; with the bound 24.0 against 23.1).
-constexpr double kLongRay = 512.0;     // samples to the longer side
-constexpr double kSpreadRays = 384.0;  // rays to one of those samples
-constexpr int kRunDense = 32;          // runs; 16 share fewer lookups (100k rays 5% slower)
+// march takes another form: a workgroup's rays come from several parts of the frame,
+// since a LiDAR's beam is a run of rays of one length and a workgroup that holds only
+// long ones sets the march's time; and all of its threads share its rays' spans, where
+// a thread to each ray left the others waiting for rounds of eight spans.  A whole
+// call, consecutive against shared: 13k LiDAR rays on 1770 x 1979 cells 27.6 -> 23.3
+// us, 60k on 2000 x 2000 35.7 -> 29.5, 178k on 827 x 749 30.4 -> 22.5, 300k on 1500 x
+// 1500 46.3 -> 35.0, 600k on 2000 x 2000 68 -> 61.  With more workgroups than the chip
+// holds they balance each other, and consecutive rays share more of their lookups (4M
+// on 2000 x 2000 229 against 237; 800k camera and LiDAR rays on 1200 x 1000 32 against
+// 34; 500k on 520 x 520 25 against 28), and where a ray has few spans to share the one
+// barrier more shows (with the bound, 300k on 400 x 400: 23.1 against 25.5; 43k on 250 x
+// 250: 15.9 against 16.2).  Between the two, two runs of 64 rays and a thread to each
+// ray: 600k LiDAR rays on 900 x 900 41.4 -> 32.2 us, 400k on 700 x 700 32.9 -> 27.5, 300k
+// camera and LiDAR rays on 400 x 400 20.1 -> 19.2, but 800k on 1200 x 1000 34.2 against
+// 33.9 and 4M LiDAR rays 231 against 226.  The shortest side where it still pays: 200k
+// LiDAR rays on 330 x 330 22.0 -> 18.8, 100k on 350 x 350 18.8 -> 18.4.
+constexpr double kLongRay = 320.0;     // samples to the longer side
+constexpr double kSharedRays = 384.0;  // rays to one of those samples: all threads share spans
+constexpr double kSpreadRays = 896.0;  // runs of 64
+constexpr int kRunShared = 32;         // runs; 16 share fewer lookups (100k rays 5% slower)
+constexpr int kRunSpread = 64;
 // Maps up to this size load a cell's fields without waiting for its validity: the
 // 16 bytes that most cells then load for nothing cost less than the round trip
 // (128 x 128: 6.1 -> 5.1 us, 400 x 400 with the bound: 6.6 -> 5.5 us).
@@ -501,27 +507,20 @@ __device__ __forceinline__ int64_t spread_ray(int64_t unit, int64_t units, int s
   return ((int64_t)(slot / kRun) * units + unit) * kRun + slot % kRun;
 }
 
-// Threads that share the spans of a ray.
-template <int kRays, bool kLong>
-constexpr int parts_of() {
-  return kLong ? kNTc / kRays : 1;
-}
-
-// The rays of workgroup `unit` of the item: consecutive ones, a thread to the spans
-// of each; or with kLong runs from all over the frame (spread_ray, `units`
-// workgroups), all threads sharing their spans.  The counts in s are zero on entry
-// and on return (every thread passes a barrier after they were reset).
-template <int kRays, bool kLong, bool kPair>
+// The rays of workgroup `unit` of the item: consecutive ones (kRun 0), or runs of
+// kRun from all over the frame (spread_ray, `units` workgroups), with kParts threads
+// to the spans of each.  The counts in s are zero on entry and on return (every
+// thread passes a barrier after they were reset).
+template <int kRays, int kRun, int kParts, bool kPair>
 __device__ __forceinline__ void march_body(const Item& it, int64_t unit, int64_t units,
-                                           MarchShared<kRays, parts_of<kRays, kLong>()>& s) {
-  constexpr int kParts = parts_of<kRays, kLong>();
+                                           MarchShared<kRays, kParts>& s) {
   const int tid = threadIdx.x;
   const int grp = it.grp, span = kSpanGroups * it.grp;
   Ray r;
   int k = 1, k1 = 0;  // the ray's first sample that no span covers yet, its last
   if (tid < kRays) {
     const int64_t i =
-        kLong ? spread_ray<kRunDense>(unit, units, tid) : unit * kRays + tid;
+        kRun > 0 ? spread_ray<(kRun > 0 ? kRun : 1)>(unit, units, tid) : unit * kRays + tid;
     uint32_t gb = 0;
     int first = 1;
     if (i < it.n && ray_of(it, i, r, first)) {
@@ -745,12 +744,12 @@ __global__ __launch_bounds__(kNTc) void k_clear_setup(Item it) {
 
 // The maxima are read through the caches: they are small and shared by every
 // workgroup, and staging them in LDS per workgroup costs more than it saves.
-template <int kRays, bool kLong>
+template <int kRays, int kRun, int kParts>
 __global__ __launch_bounds__(kNTc) void k_clear_march(Item it) {
-  __shared__ MarchShared<kRays, parts_of<kRays, kLong>()> s;
+  __shared__ MarchShared<kRays, kParts> s;
   if (threadIdx.x == 0) s.nspans = s.ngroups = 0;
   __syncthreads();
-  march_body<kRays, kLong, true>(it, blockIdx.x, gridDim.x, s);
+  march_body<kRays, kRun, kParts, true>(it, blockIdx.x, gridDim.x, s);
 }
 
 template <int kRays>
@@ -781,7 +780,7 @@ __global__ __launch_bounds__(kNTc) void k_clear_march_b(const Batch* bt) {
   for (int64_t w = blockIdx.x; w < units.total(); w += gridDim.x) {
     int64_t unit;
     const int i = units.find(w, unit);
-    march_body<kRaysBatch, false, false>(bt->items[i], unit, 0, s);
+    march_body<kRaysBatch, 0, 1, false>(bt->items[i], unit, 0, s);
   }
 }
 
@@ -833,9 +832,11 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
   TimedLaunch tl("k_clear_march", stream);
   const int side = it.c.nx > it.c.ny ? it.c.nx : it.c.ny;
   const double samples = (double)side / (double)it.c.inv_r * (double)it.c.inv_step;
-  const bool far = samples >= kLongRay && (double)it.n <= kSpreadRays * samples;
-  const auto go = [&](auto kernel, int rays) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + rays - 1) / rays)), dim3(kNTc), 0, stream,
+  const double rays = (double)it.n / samples;
+  const bool far = samples >= kLongRay && rays <= kSharedRays;
+  const bool near = !(samples >= kLongRay && rays <= kSpreadRays);
+  const auto go = [&](auto kernel, int width) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + width - 1) / width)), dim3(kNTc), 0, stream,
                        it);
   };
   if (it.grp == 0) {
@@ -844,12 +845,21 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
     else go(k_clear_sparse<kRaysPlain>, kRaysPlain);
     return hipGetLastError();
   }
+  const auto form = [&](auto consecutive, auto shared, int rays) {
+    if (far) go(shared, rays);
+    else go(consecutive, rays);
+  };
   if (it.L.ub || (it.n > kFewRays && it.n <= kShortRays))
-    go(far ? k_clear_march<kRaysShort, true> : k_clear_march<kRaysShort, false>, kRaysShort);
+    form(k_clear_march<kRaysShort, 0, 1>,
+         k_clear_march<kRaysShort, kRunShared, kNTc / kRaysShort>, kRaysShort);
   else if (it.n <= kFewRays)
-    go(far ? k_clear_march<kRaysFew, true> : k_clear_march<kRaysFew, false>, kRaysFew);
+    form(k_clear_march<kRaysFew, 0, 1>, k_clear_march<kRaysFew, kRunShared, kNTc / kRaysFew>,
+         kRaysFew);
+  else if (far || near)
+    form(k_clear_march<kRaysPlain, 0, 1>,
+         k_clear_march<kRaysPlain, kRunShared, kNTc / kRaysPlain>, kRaysPlain);
   else
-    go(far ? k_clear_march<kRaysPlain, true> : k_clear_march<kRaysPlain, false>, kRaysPlain);
+    go(k_clear_march<kRaysPlain, kRunSpread, 1>, kRaysPlain);
   return hipGetLastError();
 }
 

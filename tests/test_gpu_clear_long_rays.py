@@ -77,11 +77,12 @@ def test_batched_march_equals_every_sample(dev, case, ub):  # noqa: F811
 
 # nx, ny, step / r, sensor, reach, n, valid, flat; how often the frame is repeated
 LONG = [
-    ((600, 590, 1.0, (6.0, 8.0), 800, 3000, 0.5, True), 2),      # 32 rays, spread
-    ((600, 590, 1.0, (6.0, 8.0), 800, 3000, 0.5, True), 20),     # 64 rays, spread
-    ((600, 590, 1.0, (6.0, 8.0), 800, 3001, 0.5, True), 50),     # 128 rays, spread
-    ((600, 590, 1.0, (6.0, 8.0), 800, 3001, 0.5, True), 90),     # 128 rays, consecutive
-    ((500, 490, 1.0, (6.0, 8.0), 700, 3000, 0.5, True), 20),     # 64 rays, consecutive
+    ((600, 590, 1.0, (6.0, 8.0), 800, 3000, 0.5, True), 2),      # 32 rays, shared spans
+    ((600, 590, 1.0, (6.0, 8.0), 800, 3000, 0.5, True), 20),     # 64 rays, shared spans
+    ((600, 590, 1.0, (6.0, 8.0), 800, 3001, 0.5, True), 50),     # 128 rays, shared spans
+    ((600, 590, 1.0, (6.0, 8.0), 800, 3001, 0.5, True), 90),     # 128 rays, runs of 64
+    ((600, 590, 1.0, (6.0, 8.0), 800, 3001, 0.5, True), 200),    # 128 rays, consecutive
+    ((300, 310, 1.0, (6.0, 8.0), 400, 3000, 0.5, True), 20),     # 64 rays, consecutive
     ((2300, 40, 1.0, (3.0, 20.0), 2290, 600, 0.5, True), 1),     # over 64 spans to a ray
     ((200, 190, 0.05, (3.0, 20.0), 260, 600, 0.5, True), 1),     # over 4000 samples to a ray
 ]
