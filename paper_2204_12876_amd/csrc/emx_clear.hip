@@ -101,11 +101,14 @@ constexpr int64_t kFewRays = 3 << 14;    // 6 x 256 workgroups of 32
 // 34; 500k on 520 x 520 25 against 28), and where a ray has few spans to share the one
 // barrier more shows (with the bound, 300k on 400 x 400: 23.1 against 25.5; 43k on 250 x
 // 250: 15.9 against 16.2).  Between the two, two runs of 64 rays and a thread to each
-// ray: 600k LiDAR rays on 900 x 900 41.4 -> 32.2 us, 400k on 700 x 700 32.9 -> 27.5, 300k
-// camera and LiDAR rays on 400 x 400 20.1 -> 19.2, but 800k on 1200 x 1000 34.2 against
-// 33.9 and 4M LiDAR rays 231 against 226.  The shortest side where it still pays: 200k
-// LiDAR rays on 330 x 330 22.0 -> 18.8, 100k on 350 x 350 18.8 -> 18.4.
+// ray: 600k LiDAR rays on 900 x 900 41.4 -> 32.2 us, 400k on 700 x 700 32.9 -> 27.5, but
+// 800k camera and LiDAR rays on 1200 x 1000 34.2 against 33.9 and 4M LiDAR rays 231
+// against 226.  On shorter maps only while the chip holds all workgroups at once: 200k
+// LiDAR rays on 400 x 400 23.0 -> 20.0, on 330 x 330 22.0 -> 18.8, but 300k camera and
+// LiDAR rays on 400 x 400 the same to 1% slower.
 constexpr double kLongRay = 320.0;     // samples to the longer side
+constexpr double kLongMap = 448.0;     // the same, with more rays than ...
+constexpr int64_t kHeldRays = 1 << 18; // ... 7 workgroups of 128 for each of 256 CUs (2^17.8)
 constexpr double kSharedRays = 384.0;  // rays to one of those samples: all threads share spans
 constexpr double kSpreadRays = 896.0;  // runs of 64
 constexpr int kRunShared = 32;         // runs; 16 share fewer lookups (100k rays 5% slower)
@@ -834,7 +837,7 @@ hipError_t launch_clear(const Item& it, hipStream_t stream) {
   const double samples = (double)side / (double)it.c.inv_r * (double)it.c.inv_step;
   const double rays = (double)it.n / samples;
   const bool far = samples >= kLongRay && rays <= kSharedRays;
-  const bool near = !(samples >= kLongRay && rays <= kSpreadRays);
+  const bool near = !(samples >= (it.n > kHeldRays ? kLongMap : kLongRay) && rays <= kSpreadRays);
   const auto go = [&](auto kernel, int width) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((it.n + width - 1) / width)), dim3(kNTc), 0, stream,
                        it);
